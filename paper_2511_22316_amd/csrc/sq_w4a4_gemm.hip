@@ -10,26 +10,10 @@
 // (64 * K * 256 < 2^31 for K <= 131040, the limit of the entry point) and the epilogue shifts it
 // out.  The split into even and odd codes permutes the contraction index the same way on both
 // operands, which a dot product does not see.
-#include "sq_common.h"
-
+#include "sq_gemm_tile.h"
+#include "sq_w4a4_fp6.h"
 
 namespace sq {
-
-// LDS tile of one operand: rows of BKB bytes (2*BKB codes), stored as 16-byte chunks.
-// Chunk c of row r sits at chunk slot r*CPR + (c ^ swz(r)).  The LDS of this part serves a
-// 16-byte read of sixteen lanes per cycle from 64 banks (256 bytes): with swz(r) = (r / 2) % 8 for
-// rows of 128 bytes (two rows per 256 bytes) and (r / 4) % 4 for rows of 64 bytes, the sixteen
-// consecutive rows that read the same logical chunk land in sixteen different 16-byte bank groups
-// (SQ_LDS_BANK_CONFLICT reads 0 for the kernel; with swz(r) = r % 8, which would be right for 32
-// banks, it read 46 % of the LDS-active cycles -- at no difference in time: LDS is a third busy).
-template <int BKB>
-__device__ __forceinline__ int lds_chunk_slot(int row, int chunk)
-{
-    constexpr int CPR = BKB / 16;
-    static_assert(CPR == 4 || CPR == 8, "tile row must be 64 or 128 bytes");
-    const int swz = (CPR == 8) ? ((row >> 1) & 7) : ((row >> 2) & 3);
-    return row * CPR + (chunk ^ swz);
-}
 
 __device__ __forceinline__ void widen_chunk(const uint4 w, v4i &first, v4i &second)
 {
@@ -49,20 +33,6 @@ __device__ __forceinline__ void load_to_lds_16(const void *gptr, uint32_t lds_ad
                  : "memory", "m0");
 }
 
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// s_barrier without the memory fence of __syncthreads (which would wait for every outstanding
-// global -> LDS load).  The wave's own LDS reads are drained first.
-__device__ __forceinline__ void block_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // The same load, issued only if a < b (both wave-uniform).  The branch lives inside the assembly
 // so that the surrounding loop body stays one basic block for the instruction scheduler.
 __device__ __forceinline__ void load_to_lds_16_if(const void *gptr, uint32_t lds_addr, int a, int b)
@@ -76,50 +46,6 @@ __device__ __forceinline__ void load_to_lds_16_if(const void *gptr, uint32_t lds
                  :
                  : "v"(gptr), "s"(lds_addr), "s"(a), "s"(b)
                  : "memory", "m0", "scc");
-}
-
-// Ring of NS stages, L loads per wave and tile, `rem` tiles exist beyond the one that must have
-// landed (rem may be negative).  Loads complete in order, so that tile is in LDS once at most
-// min(rem, NS - 2) * L loads are outstanding: wait for the largest count first and step down only
-// in the last turns.  Then the LDS reads are drained and the waves meet at the barrier.
-template <int L, int NS>
-__device__ __forceinline__ void wait_tile_and_barrier(int rem)
-{
-    constexpr int D = NS - 2;
-    static_assert(D >= 1 && D <= 4 && D * L < 64, "vmcnt is a 6-bit counter; at most four levels");
-    constexpr int d0 = D, d1 = D > 1 ? D - 1 : 0, d2 = D > 2 ? D - 2 : 0, d3 = D > 3 ? D - 3 : 0;
-    asm volatile("s_waitcnt vmcnt(%1)\n\t"
-                 "s_cmp_ge_i32 %0, %2\n\t"
-                 "s_cbranch_scc1 .Lsq_landed_%=\n\t"
-                 "s_waitcnt vmcnt(%3)\n\t"
-                 "s_cmp_ge_i32 %0, %4\n\t"
-                 "s_cbranch_scc1 .Lsq_landed_%=\n\t"
-                 "s_waitcnt vmcnt(%5)\n\t"
-                 "s_cmp_ge_i32 %0, %6\n\t"
-                 "s_cbranch_scc1 .Lsq_landed_%=\n\t"
-                 "s_waitcnt vmcnt(%7)\n\t"
-                 "s_cmp_ge_i32 %0, %8\n\t"
-                 "s_cbranch_scc1 .Lsq_landed_%=\n\t"
-                 "s_waitcnt vmcnt(0)\n"
-                 ".Lsq_landed_%=:\n\t"
-                 "s_waitcnt lgkmcnt(0)\n\t"
-                 "s_barrier"
-                 :
-                 : "s"(rem), "n"(d0 * L), "n"(d0), "n"(d1 * L), "n"(d1), "n"(d2 * L), "n"(d2), "n"(d3 * L), "n"(d3)
-                 : "memory", "scc");
-}
-
-// XCD-contiguous ids, then groups of 8 row-tiles walked column by column: the tiles resident on
-// one XCD at a time share a few row panels and a few column panels in its L2.
-__device__ __forceinline__ void tile_of_workgroup(int tiles_m, int tiles_n, int &bm, int &bn)
-{
-    const int id = xcd_contiguous_id(blockIdx.x, tiles_m * tiles_n);
-    constexpr int GM = 8;
-    const int group = id / (GM * tiles_n);
-    const int gm = min(GM, tiles_m - group * GM);
-    const int in_group = id - group * GM * tiles_n;
-    bm = group * GM + in_group % gm;
-    bn = in_group / gm;
 }
 
 // Epilogue of one wave.  32x32 accumulator layout: lane holds column (lane % 32); register e
@@ -910,22 +836,24 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         if (wide <= 128) choice = (2 * wide <= 256) ? 5 : 2;
     }
     // 128x256 or 256x256 tiles: one workgroup per CU either way, so the time goes with the number
-    // of rounds of 256 tiles; a 256x256 tile takes about 1.8 times as long as a 128x256 one (twice
-    // the work at a slightly better rate).  Measured with random codes on shapes from 1024 x 11008
-    // to 8192 x 28672.
+    // of rounds of 256 tiles.  On the 6-bit float instruction (cases 18 and 19) a 256x256 tile takes about 1.6 times as
+    // long as a 128x256 one (K = 4096 / 8192 / 11008, all CUs busy: 42.3 / 74.6 / 98 against 28.0 / 46.8 / 60.2 us),
+    // on the int8 instruction (cases 16 and 4) 1.85 times.
     if (choice < 0) {
         const int64_t n_small = (int64_t)((Ti + 127) / 128) * ((N + 255) / 256);
         const int64_t n_large = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
         const int64_t rounds_small = (n_small + 255) / 256, rounds_large = (n_large + 255) / 256;
-        // (the 128x256 tile with four loading waves.  Case 16, eight multiplying waves of 64x64: attn_proj
-        // 32.0 -> 31.5 us, mlp_down 74.5 -> 73.4 us against case 1, the same tile with the loads in the
-        // multiplying waves.  Case 17, four multiplying waves of 64x128 -- half the widening per MFMA, and
-        // the four loading waves keep eight waves on the CU: attn_proj 31.0 -> 30.7 us, mlp_down 72.2 -> 68.8 us
-        // against case 16 for the GEMM alone; without loading waves that wave shape, case 0, is slower than
-        // both.  Behind the rotate kernel, as a layer, attn_proj is 0.3 us slower with it (41.5 -> 41.8 us) and
-        // mlp_down 2.2 us faster (98.6 -> 96.4 us): its gain grows with the number of K tiles, 16 against 43
-        // here, and turns positive at about 20 of them.)
-        choice = (20 * rounds_small > 37 * rounds_large) ? 4 : (K >= 6144 ? 17 : 16);
+        const bool prefer_large = 5 * rounds_small > 8 * rounds_large;
+        // The gain of the 6-bit form is power, and its loop is the longer one in cycles: it pays once the K loop
+        // dominates and most of the CUs work (us, int8 against 6-bit: T = 1024, K = 768, N = 8192 11.6 / 12.3;
+        // K = 2048 18.6 / 18.3; K = 8192 51.5 / 48.4; 162 tiles of 128x256: K = 4096 24.6 / 25.1, K = 8192 42.9 / 41.9;
+        // 256x256 tiles, T = 3000, N = 11008: K = 768 43.2 / 41.6, K = 2048 80.0 / 68.2).
+        const bool small_pays = K >= 5120 || (K >= 2048 && n_small >= 192);
+        if (prefer_large && K >= 1024 && sq::w4a4_fp6_takes(true, Ti, K, N)) choice = 19;
+        else if (!prefer_large && small_pays && sq::w4a4_fp6_takes(false, Ti, K, N)) choice = 18;
+        // (case 16: the 128x256 tile with four loading waves, 32.0 -> 31.5 us at T = 2048, K = N = 4096 against case 1,
+        // the same tile with the loads in the multiplying waves)
+        else choice = (20 * rounds_small > 37 * rounds_large) ? 4 : 16;
     }
     switch (choice) {
         case 0: return sq::launch_main<2, 2, 2, 4, 128, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
@@ -937,13 +865,14 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         case 10: return sq::launch_main<2, 2, 1, 1, 128, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 11: return sq::launch_main<2, 2, 1, 2, 128, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 16: return sq::launch_main<2, 4, 2, 2, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
-        case 17: return sq::launch_main<2, 2, 2, 4, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 14: if (K % 512 == 0) return sq::launch_main<2, 2, 1, 1, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 15: if (K % 512 == 0) return sq::launch_main<2, 2, 1, 2, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 7: if (Ti <= 32) return sq::launch_skinny<1, 1, 16>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 8: if (Ti <= 32) return sq::launch_skinny<1, 2, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 9: if (Ti <= 32) return sq::launch_skinny<1, 1, 8>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 13: if (Ti <= 64) return sq::launch_skinny<2, 1, 8>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
+        case 18: if (sq::w4a4_fp6_takes(false, Ti, K, N)) return sq::launch_w4a4_fp6(false, Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
+        case 19: if (sq::w4a4_fp6_takes(true, Ti, K, N)) return sq::launch_w4a4_fp6(true, Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         default: break;
     }
     return sq::launch_main<2, 4, 2, 2, 128, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);

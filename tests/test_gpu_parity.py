@@ -361,6 +361,37 @@ def test_gemm_every_tile_launch_shape(oracle, case, T, K, N):
     assert half_ulp_distance(Yg, Yo).max() <= 1
 
 
+@pytest.mark.parametrize("case,T,K,N", [
+    # 128 x 256 tiles: exactly one, then overlapping last tiles in both directions, an odd number of K tiles
+    (18, 128, 768, 256), (18, 129, 768, 257), (18, 300, 1280, 520), (18, 200, 2048, 700),
+    # 256 x 256 tiles: the same, and more tiles than CUs (a workgroup walks over several)
+    (19, 256, 768, 256), (19, 257, 1280, 257), (19, 300, 1024, 520), (19, 513, 2048, 300), (19, 2100, 768, 8300),
+    (19, 4100, 1024, 4500),
+    # the longest K: sums of the offset codes up to 225 K, just below 2^24
+    (18, 128, 65536, 256), (19, 256, 65536, 256)])
+def test_gemm_six_bit_float_kernel(oracle, case, T, K, N):
+    """The tile kernel on the 6-bit float instruction, forced through the debug option: int32 accumulators bit-exact
+    (extreme codes included), Y within one fp16 ulp."""
+    print(f"case gemm six-bit launch shape {case} T={T} K={K} N={N}", flush=True)
+    import paper_2511_22316_amd as sq
+    g = np.random.default_rng(case + T + K + N)
+    sx = g.uniform(0.05, 4.0, T).astype(np.float32)
+    sw = g.uniform(1e-6, 5e-5, N).astype(np.float32)
+    inputs = [(synth.random_codes(T, K, 500 + T), synth.random_codes(N, K, 600 + N))]
+    if T * K * N < 1 << 33:      # all (-8)(-8) and all (-8) * 7: the ends of the range
+        low, high = np.full((T, K // 2), 0x88, np.uint8), np.full((N, K // 2), 0x77, np.uint8)
+        inputs += [(low, np.full((N, K // 2), 0x88, np.uint8)), (low, high)]
+    for Qx, Qw in inputs:
+        Yo, acco = oracle.gemm(Qx, sx, Qw, sw)
+        sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, case + 1)
+        try:
+            Yg, accg = run_gemm(Qx, sx, Qw, sw)
+        finally:
+            sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, 0)
+        assert np.array_equal(accg, acco)
+        assert half_ulp_distance(Yg, Yo).max() <= 1
+
+
 def test_gemm_seeded_random_shapes_bit_exact(oracle):
     """Thirty shapes drawn from a seed (T up to 700, K a multiple of 32 up to 2304, N up to 3000, a
     third of them with at most 64 tokens): whatever kernel and launch shape the dispatcher picks,
