@@ -357,7 +357,7 @@ static sq_status rotate_quantize_any(const void *X, int64_t T, int32_t K, int64_
     if (T == 0) return SQ_OK;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // matrix-core kernel for the shapes it covers (n2 in {32, 64, 128}, n1 <= 128); the plain-FMA
+    // matrix-core kernels for the shapes they cover (n2 in {32, 64, 128}, 8 <= n1 <= 128); the plain-FMA
     // kernel takes every other shape.  The debug option SQ_DEBUG_ROTQ_PLAIN_KERNEL forces the latter.
     const bool force_generic = sq::debug_option(SQ_DEBUG_ROTQ_PLAIN_KERNEL) != 0;
     if (!force_generic && prep.plan_ok) {
@@ -382,6 +382,13 @@ static sq_status rotate_quantize_any(const void *X, int64_t T, int32_t K, int64_
                                    static_cast<const __half *>(prepared ? frag2 : R2), Q, scales, xrot_dbg, st,
                                    &status, prepared))
             return status;
+        // Every other pair the matrix cores can take, at any token count.  Plain-FMA kernel / this one, us in a stream of
+        // calls: 48 x 64, T = 1001 45.3 / 11.6; 36 x 64, T = 2048 59.4 / 12.1; 97 x 64, T = 16 43.0 / 16.4; 85 x 128,
+        // T = 2048 855 / 39; 8 x 32 .. 33 x 32 at T <= 500 10.1 - 11.9 / 10.4 - 11.5 (both below the host's time).
+        if (sq::rotq_any_covers(n1, n2))
+            return sq::rotq_any_launch(static_cast<const __half *>(X), ldx, (int)T, n1, n2, plan,
+                                       static_cast<const __half *>(R1), static_cast<const __half *>(R2), Q, scales,
+                                       xrot_dbg, static_cast<__half *>(xout), ldo, st);
     }
     const size_t lds = sizeof(float) * 2 * (size_t)K;
     if (!sq::allow_large_lds(reinterpret_cast<const void *>(sq::rotate_quantize_generic_kernel)))

@@ -38,13 +38,19 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // (z0, z1) -> hi = their fp16 truncations packed in one dword, lo = fp16 of the exact remainders
 // z - hi (the mixed-precision FMA reads the fp16 half directly, and the difference is exact)
+// NEAREST: both halves rounded to nearest instead (one instruction too): 23 bits instead of 21.
+template <bool NEAREST = false>
 __device__ __forceinline__ void split_pair(float z0, float z1, uint32_t &hi, uint32_t &lo)
 {
-    hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(z0, z1));
+    auto pack = [](float a, float b) -> uint32_t {
+        if constexpr (NEAREST) return __builtin_bit_cast(uint32_t, v2h{(_Float16)a, (_Float16)b});
+        else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+    };
+    hi = pack(z0, z1);
     float r0, r1;
     asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi), "v"(z0));
     asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi), "v"(z1));
-    lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r0, r1));
+    lo = pack(r0, r1);
 }
 
 // max(m, |a[0]|, ..., |a[15]|), as four independent chains of two steps each (one long chain of
@@ -77,6 +83,7 @@ struct RotqShape {
     static constexpr int CPRX = N2 / 8;           // 16-byte chunks per tile row
     static constexpr int ROW_CHUNKS = N1 * CPRX;  // 16-byte chunks of one token row
     static constexpr int LPT = (ROW_CHUNKS + 63) / 64;    // wave-wide loads per token row
+    static constexpr int LPT_MIN = ((N1P - 31) * CPRX + 63) / 64;   // at least, of any n1 with this many row blocks
     static constexpr int NSX = NSX_;              // ring of token tiles
     static constexpr int TILE_BYTES = N1P * N2 * 2;
     static constexpr int LO_STEP_BYTES = N1P * 32;        // side tile: [step][row p][16 fp16]
@@ -89,6 +96,7 @@ struct RotqShape {
     static constexpr int OFF_LO = OFF_R1F + R1F_BYTES;                // [TPP][side tiles][qsteps][LO_STEP]
     // after the side tiles (runtime size): [TPP][128] float, [2][TPP][4] float
     static constexpr int TAIL_BYTES = TPP * (kRotqMaxSlots * 4 + 32);
+    static constexpr int ROW_SCALE_BYTES = 2 * TPP * 4;               // behind those, where n1 is an argument
     // sides: side tiles per token slot, 2 (they alternate from token to token, one barrier per
     // token) or 1 (less LDS, a second barrier per token)
     static constexpr int lds_bytes(int qsteps, int sides)
@@ -121,17 +129,23 @@ struct RotqShape {
 // sides: side tiles per token slot (RotqShape::side_tiles).
 // CLIP: the quantizer has a clipping ratio below one (plan.clip): entries beyond the end levels
 // are clamped to them.  Without it nothing can lie beyond them and the clamp is not compiled in.
-template <int N1, int N2, int QS_MAX, int NSX_, bool R1LDS, bool PREPARED, bool F16OUT = false, bool CLIP = false>
+// ANY_N1: the number of rows is the argument n1_arg, N1 - 31 .. N1 (N1 a multiple of 32) and at least 8;
+// R1, R2 as they are.  A row whose rotated values leave the range of fp16 is scaled by a power of two; Z is split
+// with both halves rounded to nearest.
+template <int N1, int N2, int QS_MAX, int NSX_, bool R1LDS, bool PREPARED, bool F16OUT = false, bool CLIP = false,
+          bool ANY_N1 = false>
 __device__ __forceinline__ void rotate_quantize_mfma_body(
     const __half *__restrict__ X, int64_t ldx, int T, const RotqPlan &plan,
     const __half *__restrict__ R1, const __half *__restrict__ R2, uint8_t *__restrict__ Q,
     float *__restrict__ scales, float *__restrict__ xrot, const int g0, const int stride, uint4 *smem_u4,
-    const int sides, __half *__restrict__ xout = nullptr, int64_t ldo = 0)
+    const int sides, __half *__restrict__ xout = nullptr, int64_t ldo = 0, const int n1_arg = N1)
 {
     using S = RotqShape<N1, N2, NSX_, R1LDS>;
     constexpr bool prepared = PREPARED;
     constexpr int N1P = S::N1P, MB = S::MB, NCB = S::NCB, TPP = S::TPP, KSA = S::KSA, KSB = S::KSB;
-    constexpr int CPRX = S::CPRX, LPT = S::LPT, NSX = S::NSX, K = N1 * N2;
+    constexpr int CPRX = S::CPRX, LPT = S::LPT, NSX = S::NSX;
+    static_assert(!ANY_N1 || (!PREPARED && N1 % 32 == 0), "rows padded to the MFMA block, R1 and R2 as they are");
+    const int n1 = ANY_N1 ? n1_arg : N1, K = n1 * N2;
     static_assert(QS_MAX == 4 || QS_MAX == 8, "64 or 128 q-slots");
     char *lds = reinterpret_cast<char *>(smem_u4);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)smem_u4;
@@ -160,6 +174,8 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
     const int off_gv = S::OFF_LO + TPP * sides * lo_bytes;
     const int side_mask = sides - 1;                         // 1: the two tiles alternate, 0: one tile
     const int off_red = off_gv + TPP * kRotqMaxSlots * 4;    // [2][TPP][4] floats
+    // ANY_N1: what the row in the tile of a token slot was divided by, a power of two (1 nearly always)
+    float *row_scale = reinterpret_cast<float *>(lds + off_red + 32 * TPP);        // [2][TPP]
 
     const int groups = (T + TPP - 1) / TPP;
     // does this wave's token exist in group grp (the last group may be partial)?
@@ -172,7 +188,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
             for (int part = 0; part < LPT; ++part) {
                 const int c = part * 64 + lane;
-                if (c < S::ROW_CHUNKS) {
+                if (c < n1 * CPRX) {
                     const int r = c / CPRX, pc = c % CPRX;
                     dma_16(row + r * N2 + ((pc ^ swz<CPRX>(r)) * 8),
                            __builtin_amdgcn_readfirstlane(dst0 + part * 1024));
@@ -239,10 +255,34 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
             }
         }
         __builtin_amdgcn_wave_barrier();
+        float down = 1.0f;
+        if constexpr (ANY_N1) {
+            // two channels near the largest fp16 value may rotate into one beyond it: the whole row is
+            // divided by a power of two then, which moves nothing but the subnormals of a row that large
+            float top = 0.f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (gs_tile[u] >= 0) top = fmaxf(top, fabsf(gv[lane + 64 * u]));
+            float up = 1.0f;
+            if (__any(top > 65504.0f)) {
+                const int e = min((int)(__float_as_uint(wave_max(top)) >> 23) - 127 - 14, 24);
+                up = __uint_as_float((uint32_t)(127 + e) << 23);
+                down = __uint_as_float((uint32_t)(127 - e) << 23);
+                for (int c = lane; c < n1 * CPRX; c += 64) {
+                    v8h *chunk16 = reinterpret_cast<v8h *>(xt + 16 * c);
+                    v8h v = *chunk16;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[k] = (_Float16)((float)v[k] * down);
+                    *chunk16 = v;
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (lane == 0) row_scale[(side & 1) * TPP + tok_slot] = up;
+        }
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             if (gs_tile[u] >= 0) {
-                const float v = gv[lane + 64 * u];
+                const float v = ANY_N1 ? gv[lane + 64 * u] * down : gv[lane + 64 * u];
                 const __half hi = __float2half_rn(v);
                 *reinterpret_cast<__half *>(xt + gs_tile[u]) = hi;
                 *reinterpret_cast<__half *>(lo_t + gs_lo[u]) = __float2half_rn(v - __half2float(hi));
@@ -289,6 +329,23 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 return g ? hi_g : lo_g;
             }
         };
+        // Any number of rows: elements base + 8g .. +7 of row `row`, zeros behind its end.  The load starts at any
+        // element (two-byte alignment); what would reach past the end of the matrix -- in its last row alone, as
+        // a row holds at least eight elements -- is fetched further down and shifted.
+        auto chunk_any = [&](int row, int base) {
+            const int col = base + 8 * g, at = row * n1 + col, from = min(at, n1 * n1 - 8);
+            v4u w;
+            __builtin_memcpy(&w, R1 + from, 16);
+            const int sh = at - from, valid = n1 - col;
+            if (sh & 4) w = v4u{w[2], w[3], 0u, 0u};
+            if (sh & 2) w = v4u{w[1], w[2], w[3], 0u};
+            if (sh & 1)
+                w = v4u{__builtin_amdgcn_alignbit(w[1], w[0], 16), __builtin_amdgcn_alignbit(w[2], w[1], 16),
+                        __builtin_amdgcn_alignbit(w[3], w[2], 16), w[3] >> 16};
+#pragma unroll
+            for (int d = 0; d < 4; ++d) w[d] = valid >= 2 * d + 2 ? w[d] : valid == 2 * d + 1 ? (w[d] & 0xFFFFu) : 0u;
+            return __builtin_bit_cast(v8h, w);
+        };
         auto zero_unless = [&](bool keep, const v8h v) {
             const v4u w = __builtin_bit_cast(v4u, v);
             const v4u z = {keep ? w[0] : 0u, keep ? w[1] : 0u, keep ? w[2] : 0u, keep ? w[3] : 0u};
@@ -323,6 +380,11 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
         auto load_raw1 = [&](int nb, v8h (&dst)[MB][2]) {
 #pragma unroll
             for (int blk = 0; blk < MB; ++blk) {
+                if constexpr (ANY_N1) {
+                    dst[blk][0] = chunk_any(min(32 * blk + l32, n1 - 1), 32 * nb);
+                    dst[blk][1] = chunk_any(min(32 * blk + l32, n1 - 1), 32 * nb + 16);
+                    continue;
+                }
                 const __half *row = R1 + min(32 * blk + l32, N1 - 1) * N1;
                 if (nb == 0) {
                     dst[blk][0] = chunk(row, std::integral_constant<int, 0>{}, CN1{});
@@ -385,13 +447,14 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
         // order, so it has landed once the entries are here.  The barrier is the bare instruction:
         // the fence of __syncthreads would wait for every load above.  (Zeros: padding rows p >= N1
         // of every ring tile, and the side tiles.)
-        if (N1P > N1) {
-            constexpr int PAD_CHUNKS = (N1P - N1) * CPRX;
-            for (int c = tid; c < TPP * NSX * PAD_CHUNKS; c += 256) {
-                const int tile = c / PAD_CHUNKS, r = c % PAD_CHUNKS;
-                *reinterpret_cast<uint4 *>(lds + S::OFF_X + tile * S::TILE_BYTES + (N1 * CPRX + r) * 16) = uint4{0, 0, 0, 0};
+        if (N1P > n1) {
+            const int pad_chunks = (N1P - n1) * CPRX;
+            for (int c = tid; c < TPP * NSX * pad_chunks; c += 256) {
+                const int tile = c / pad_chunks, r = c % pad_chunks;
+                *reinterpret_cast<uint4 *>(lds + S::OFF_X + tile * S::TILE_BYTES + (n1 * CPRX + r) * 16) = uint4{0, 0, 0, 0};
             }
         }
+        if (ANY_N1 && tid < 2 * TPP) row_scale[tid] = 1.0f;
         for (int c = tid; c < TPP * sides * lo_bytes / 16; c += 256)
             *reinterpret_cast<uint4 *>(lds + S::OFF_LO + c * 16) = uint4{0, 0, 0, 0};
 
@@ -422,7 +485,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                         dst[(2 * blk) * kWave] = raw1[0][blk][0];
                         dst[(2 * blk + 1) * kWave] = raw1[0][blk][1];
                     } else {
-                        const bool keep = 32 * blk + l32 < N1;
+                        const bool keep = 32 * blk + l32 < n1;
                         const v16f c = block_t(zero_unless(keep, raw1[0][blk][0]), zero_unless(keep, raw1[0][blk][1]));
                         dst[(2 * blk) * kWave] = to_frag(c, 0);
                         dst[(2 * blk + 1) * kWave] = to_frag(c, 1);
@@ -437,7 +500,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 if (ALTERNATE && nb + 1 < MB) load_raw1(nb + 1, raw1[(nb + 1) & 1]);
 #pragma unroll
                 for (int blk = 0; blk < MB; ++blk) {
-                    const bool keep = 32 * blk + l32 < N1;
+                    const bool keep = 32 * blk + l32 < n1;
                     const v16f c = block_t(zero_unless(keep, raw1[set][blk][0]), zero_unless(keep, raw1[set][blk][1]));
                     r1f[nb][2 * blk] = to_frag(c, 0);
                     r1f[nb][2 * blk + 1] = to_frag(c, 1);
@@ -568,6 +631,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
                 for (int e = 0; e < 16; ++e) accz[mb][e] *= fz;
         }
+        if constexpr (ANY_N1) fz_inv *= row_scale[par * TPP + tok_slot];
 
         // ---- stage B: Y^T = Z^T R1, Z = hi + lo; the split of step ks+1 is issued between the
         // MFMAs of step ks -----------------------------------------------------------------
@@ -579,7 +643,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             uint32_t hi, lo;
-            split_pair(accz[0][2 * e], accz[0][2 * e + 1], hi, lo);
+            split_pair<ANY_N1>(accz[0][2 * e], accz[0][2 * e + 1], hi, lo);
             zh[e] = hi;
             zl[e] = lo;
         }
@@ -612,7 +676,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                         if (j < NMB || true) {
                             const int ks1 = ks + 1, mb1 = ks1 >> 1, r1 = 8 * (ks1 & 1);
                             uint32_t hi, lo;
-                            split_pair(accz[mb1][r1 + 2 * e], accz[mb1][r1 + 2 * e + 1], hi, lo);
+                            split_pair<ANY_N1>(accz[mb1][r1 + 2 * e], accz[mb1][r1 + 2 * e + 1], hi, lo);
                             zh_n[e] = hi;
                             zl_n[e] = lo;
                         }
@@ -642,7 +706,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
         // wave per token the owner also requested the row after it, which may still be in flight
         // (rows complete in order); with turns, every other request of this wave is older.
         if (owns(it + 1)) {
-            if (NCB == 1 && has_row(grp + 2 * stride)) wait_loads_le<LPT>();
+            if (NCB == 1 && has_row(grp + 2 * stride)) wait_loads_le<ANY_N1 ? S::LPT_MIN : LPT>();
             else wait_loads_le<0>();
             if (has_row(grp + stride)) givens(slot1, par ^ 1);
         }
@@ -663,7 +727,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
             for (int nb = 0; nb < MB; ++nb) {
                 const int po = 32 * nb + l32;
-                if (po < N1) {
+                if (po < n1) {
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
                         xrot[(int64_t)t * K + po * N2 + 32 * cb + 8 * (e / 4) + 4 * g + (e % 4)] =
@@ -700,7 +764,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 const int po = 32 * nb + l32;
                 const v2h lo2 = {(_Float16)(accy[nb][4 * rg] * inv), (_Float16)(accy[nb][4 * rg + 1] * inv)};
                 const v2h hi2 = {(_Float16)(accy[nb][4 * rg + 2] * inv), (_Float16)(accy[nb][4 * rg + 3] * inv)};
-                if (live && po < N1)
+                if (live && po < n1)
                     *reinterpret_cast<uint2 *>(xout + (int64_t)t * ldo + po * N2 + 32 * cb + 8 * rg + 4 * g) =
                         uint2{__builtin_bit_cast(uint32_t, lo2), __builtin_bit_cast(uint32_t, hi2)};
                 return;
@@ -723,7 +787,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 const uint32_t d0 = (s02[0] | (s02[1] << 16)) ^ 0x88888888u;     // rg = 0 (g = 0) or 2 (g = 1)
                 const uint32_t d1 = (s13[0] | (s13[1] << 16)) ^ 0x88888888u;     // rg = 1 (g = 0) or 3 (g = 1)
                 const int po = 32 * nb + l32;
-                if (live && po < N1)
+                if (live && po < n1)
                     *reinterpret_cast<uint2 *>(Q + (int64_t)t * (K / 2) + po * (N2 / 2) + 16 * cb + 8 * g) = uint2{d0, d1};
             }
         };

@@ -54,6 +54,13 @@ bool rotq_mfma_dispatch_f16(const __half *X, int64_t ldx, int T, int n1, int n2,
                             const __half *R1, const __half *R2, __half *xout, int64_t ldo, hipStream_t st,
                             sq_status *status);
 
+// The same for any other pair with 8 <= n1 <= 128 and n2 = 32, 64 or 128 (sq_rotq_any.hip): R1 and R2 as they are.
+// xout not null: fp16 output [T, ldo], no quantizer.
+bool rotq_any_covers(int n1, int n2);
+sq_status rotq_any_launch(const __half *X, int64_t ldx, int T, int n1, int n2, const RotqPlan &plan, const __half *R1,
+                          const __half *R2, uint8_t *Q, float *scales, float *xrot, __half *xout, int64_t ldo,
+                          hipStream_t st);
+
 // Shapes the matrix-core kernel covers, and its operand fragments of R1 / R2 in the order the
 // lanes hold them (sizes in bytes; both multiples of 1024).
 bool rotq_mfma_covers(int n1, int n2);

@@ -11,8 +11,8 @@ import numpy as np
 import pytest
 
 from paper_2511_22316_amd import synth
-from parity_util import CODE_FLIP_FRACTION, SCALE_TOL, codes_of, dev, host
-from test_gpu_w4a16 import check_w4a16, run_w4a16
+from parity_util import CODE_FLIP_FRACTION, SCALE_TOL, check_codes, check_rotation, codes_of, dev, host, run_rotate_quantize
+from test_gpu_w4a16 import check_rotated_f16, check_w4a16, run_rotate_fp16, run_w4a16
 
 pytestmark = pytest.mark.gpu
 
@@ -450,3 +450,57 @@ def test_decode_path_captured_in_a_graph_replays_correctly(oracle):
         sq.sq_w4a4_gemm(Qe, se, Qw, sw, Ye)
         torch.cuda.synchronize()
         assert torch.equal(got[0], Qe) and torch.equal(got[1], se) and torch.equal(got[2], Ye), f"replay with shift {shift}"
+
+
+# rows at the edges of the 32-row blocks, odd ones among them, and token counts around a pass of the workgroup
+@pytest.mark.parametrize("n1,n2,T,P", [(8, 32, 1, 4), (9, 32, 37, 3), (31, 32, 4100, 64), (33, 32, 5, 16), (127, 32, 9, 64),
+                                       (13, 64, 3, 64), (48, 64, 1001, 16), (65, 64, 2, 0), (96, 64, 33, 64), (97, 64, 19, 8),
+                                       (126, 64, 600, 32), (11, 128, 40, 64), (63, 128, 7, 64), (85, 128, 530, 16),
+                                       (96, 128, 16, 64), (111, 128, 300, 0), (127, 128, 3, 64)])
+@pytest.mark.parametrize("bits,clip", [(4, 1.0), (3, 0.85)])
+def test_rotation_with_any_number_of_rows(oracle, n1, n2, T, P, bits, clip):
+    print(f"case any rows {n1}x{n2} T={T} P={P} bits={bits} clip={clip}", flush=True)
+    cfg = synth.LayerConfig(f"any_{n1}x{n2}", T, n1, n2, 16, P, "student_t3" if n1 % 2 else "normal", 2, 300.0, 0.01, 20.0,
+                            0.02, 500 + n1 + n2)
+    L = synth.layer(cfg)
+    if P == 64 and n1 * n2 >= 512:           # channels on as many different columns as there are
+        g = np.random.default_rng(n1)
+        chans = np.array([g.integers(0, n1) * n2 + c % n2 for c in range(128)])
+        chans = np.unique(chans)
+        chans = g.permutation(chans)[: len(chans) // 2 * 2].astype(np.int32)
+        L = synth.Layer(cfg, L.X, chans[0::2].copy(), chans[1::2].copy(),
+                        g.uniform(-3.1, 3.1, len(chans) // 2).astype(np.float32), L.R1, L.R2, L.R1_f64, L.R2_f64)
+    rows = np.unique(np.concatenate([np.arange(min(T, 3)), [T - 1], np.random.default_rng(1).integers(0, T, 24)]))
+    xo = oracle.rotate(L.X[rows], L.giv_i, L.giv_j, L.giv_theta, L.R1, L.R2)
+    if clip == 1.0 and bits == 4:
+        Qg, sg, xg = run_rotate_quantize(L)
+        Qo, so = oracle.quantize_rows(xo)
+        check_codes(Qg[rows], sg[rows], Qo, so)
+        check_rotated_f16(run_rotate_fp16(L)[rows],
+                          oracle.rotate_f16(L.X[rows], L.giv_i, L.giv_j, L.giv_theta, L.R1, L.R2), xo)
+    else:
+        Qg, sg, xg = run_variant(L, bits, clip, want_xrot=True)
+        Qo, so = oracle.quantize_rows_variant(xo, bits, clip)
+        check_variant_codes(Qg[rows], sg[rows], Qo, so, bits)
+    check_rotation(xg[rows], xo)
+
+
+@pytest.mark.parametrize("n1,n2", [(20, 32), (48, 64), (85, 128)])
+def test_rotated_outliers_beyond_fp16(oracle, n1, n2):
+    """Channels at the largest fp16 value that rotate into one beyond it (up to 4 x 65504 over a chain of pairs),
+    in some rows and not in others: the fp32 rows, steps and codes are as accurate as anywhere."""
+    print(f"case outliers beyond fp16 {n1}x{n2}", flush=True)
+    T, K = 23, n1 * n2
+    cfg = synth.LayerConfig(f"beyond_{n1}x{n2}", T, n1, n2, 16, 3, "normal", 2, 50.0, 0.01, 20.0, 0.02, 900 + n1)
+    L = synth.layer(cfg)
+    X = L.X.copy()
+    X[::3, 5] = X[::3, K - 7] = X[::3, 77] = X[::3, 200] = 65504.0
+    X[1, 5], X[1, K - 7] = 65504.0, -65504.0             # rotates into a zero and one value beyond
+    gi, gj = np.array([5, 77, 5], np.int32), np.array([K - 7, 200, 77], np.int32)
+    gt = np.array([np.pi / 4, np.pi / 4, np.pi / 4], np.float32)
+    Lb = synth.Layer(cfg, X, gi, gj, gt, L.R1, L.R2, L.R1_f64, L.R2_f64)
+    Qg, sg, xg = run_rotate_quantize(Lb)
+    xo = oracle.rotate(X, gi, gj, gt, L.R1, L.R2)
+    Qo, so = oracle.quantize_rows(xo)
+    check_rotation(xg, xo)
+    check_codes(Qg, sg, Qo, so)
