@@ -568,7 +568,7 @@ __global__ __launch_bounds__(NW *kWave) void w4a4_gemm_skinny_kernel(
 
 // ------------------------------------------------------------------------------------------
 // Generic kernel: any K % 32 == 0 (zero-fills the last partial K tile).  Tiles are staged through
-// registers; used only for shapes the main kernel does not take.
+// registers; used only for K the tile kernel does not take (no multiple of 128).
 // ------------------------------------------------------------------------------------------
 template <int FM, int FN, int BKB>
 __global__ __launch_bounds__(256) void w4a4_gemm_generic_kernel(
@@ -788,7 +788,7 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         return SQ_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     __half *Yh = static_cast<__half *>(Y);
-    if ((K % 256) != 0) return sq::launch_generic(Qx, sx, (int)T, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+    if ((K % 128) != 0) return sq::launch_generic(Qx, sx, (int)T, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
     // Kernel choice, from few tokens to many.  The two large tile shapes run eight waves per CU
     // (two per SIMD): the VALU work of widening nibbles issues nearly twice as fast from two waves
     // as from one.  256x256 tiles (64x128 per wave: fewer VALU ops per MFMA) or 128x256 tiles,
@@ -797,6 +797,19 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     const int forced = sq::debug_option(SQ_DEBUG_GEMM_LAUNCH_SHAPE) - 1;
     const int Ti = (int)T;
     int choice = forced;
+    // Odd multiples of 128: the tile kernel with K tiles of 128 codes.  The plain staging of the generic kernel pays a
+    // memory round trip per K tile (us, generic / here): K = 3200, T = 1, N = 4096 20.0 / 8.9; T = 1000, N = 4096 29.2 / 19.0;
+    // T = 8000, N = 27000 824 / 618; K = 10880, T = 100, N = 300 65.1 / 24.3.
+    // 64x64 tiles while two of them per CU take the whole product (T = 300, N = 4096, K = 3200: 12.6 against 15.3 us with
+    // 128x128 tiles); 256x256 tiles once every CU has one and K is long (T = 4000, N = 4096: K = 3200 47.8 against 53.1
+    // us with 128x128 tiles, K = 10880 132 against 154; K = 640, N = 27000 111 against 94 us).
+    if ((K % 256) != 0) {
+        const int64_t n64 = (int64_t)((Ti + 63) / 64) * ((N + 63) / 64);
+        const int64_t n256 = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
+        if (n64 <= 512) return sq::launch_main<2, 2, 1, 1, 64, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        if (n256 >= 256 && K >= 2048) return sq::launch_main<4, 2, 2, 4, 64, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        return sq::launch_main<2, 2, 2, 2, 64, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+    }
     // At most 64 tokens: one pass over the weights by the decode-shaped kernel; its launch shape
     // (token blocks, channels per workgroup, K split) keeps about eight waves on every CU.
     // From 33 tokens on (17 with very many channels) and 10240 channels on, 64x64 / 64x128 tiles of

@@ -361,6 +361,21 @@ def test_gemm_every_tile_launch_shape(oracle, case, T, K, N):
     assert half_ulp_distance(Yg, Yo).max() <= 1
 
 
+# one K tile, fewer than the ring has stages, many; 64x64, 128x128 and 256x256 output tiles with ragged ends
+@pytest.mark.parametrize("T,K,N", [(1, 128, 1), (65, 128, 300), (33, 384, 700), (64, 640, 32768), (65, 384, 32700), (300, 896, 4097),
+                                   (1025, 640, 4200), (4100, 2176, 4000), (257, 2176, 65500)])
+def test_gemm_odd_multiples_of_128(oracle, T, K, N):
+    print(f"case gemm K an odd multiple of 128: T={T} K={K} N={N}", flush=True)
+    g = np.random.default_rng(T + K + N)
+    sx = g.uniform(0.05, 4.0, T).astype(np.float32)
+    sw = g.uniform(1e-6, 5e-4, N).astype(np.float32)
+    Qx, Qw = synth.random_codes(T, K, 700 + T), synth.random_codes(N, K, 800 + N)
+    Yo, acco = oracle.gemm(Qx, sx, Qw, sw)
+    Yg, accg = run_gemm(Qx, sx, Qw, sw)
+    assert np.array_equal(accg, acco)
+    assert half_ulp_distance(Yg, Yo).max() <= 1
+
+
 @pytest.mark.parametrize("case,T,K,N", [
     # 128 x 256 tiles: exactly one, then overlapping last tiles in both directions, an odd number of K tiles
     (18, 128, 768, 256), (18, 129, 768, 257), (18, 300, 1280, 520), (18, 200, 2048, 700),
