@@ -7,6 +7,7 @@ first call raises.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional
 
@@ -15,6 +16,8 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libsinglequant.so")
 _lib = None
+_torch = None
+_I32, _F32 = np.dtype(np.int32), np.dtype(np.float32)
 
 SQ_OK = 0
 
@@ -30,7 +33,7 @@ def library_path() -> str:
 
 
 def _load():
-    global _lib
+    global _lib, _torch
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError(
@@ -40,7 +43,8 @@ def _load():
         # passes around belongs to that copy.  Loaded the other way round (this library, which
         # names the runtime of the ROCm installation, before torch) the process ends up with two
         # runtimes, and the one the library talks to reports "no ROCm-capable device".
-        import torch  # noqa: F401
+        import torch
+        _torch = torch
         lib = C.CDLL(_LIB_PATH)
         lib.sq_rotate_quantize.restype = C.c_int
         lib.sq_rotate_quantize.argtypes = [
@@ -166,27 +170,37 @@ def _dev_ptr(t) -> Optional[int]:
 
 
 def _stream_handle(stream) -> Optional[int]:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    # (the handle itself: building the Stream object around it costs 2.7 us a call, ten times as much)
+    if stream is not None:
+        return stream.cuda_stream or None
+    return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device()) or None
 
 
-def _host(a, dtype):
-    return None if a is None else np.ascontiguousarray(a, dtype=dtype)
+def _bytes(a, dtype) -> Optional[bytes]:
+    if a is None:
+        return None
+    if type(a) is not np.ndarray or a.dtype != dtype:
+        a = np.asarray(a, dtype=dtype)
+    return a.tobytes()
+
+
+def _givens(giv_i, giv_j, giv_theta):
+    """The list as the C entries read it during the call (as bytes: ndarray.ctypes costs 0.6 us an array) and its
+    length."""
+    gi = _bytes(giv_i, _I32)
+    return gi, _bytes(giv_j, _I32), _bytes(giv_theta, _F32), 0 if gi is None else len(gi) // 4
 
 
 def sq_rotate_quantize(X, giv_i, giv_j, giv_theta, R1, R2, Q, scales, xrot_dbg=None, stream=None) -> None:
     """X fp16 [T, K] (row stride = X.stride(0)); giv_* host sequences of equal length P;
     R1 fp16 [n1, n1]; R2 fp16 [n2, n2]; outputs Q uint8 [T, K/2], scales fp32 [T],
     optional xrot_dbg fp32 [T, K].  All tensors are device tensors owned by the caller."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     T, K = int(X.shape[0]), int(X.shape[1])
     ldx = int(X.stride(0)) if T > 1 else K
     code = _load().sq_rotate_quantize(
         _dev_ptr(X), T, K, ldx,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(R1), int(R1.shape[0]), _dev_ptr(R2), int(R2.shape[0]),
         _dev_ptr(Q), _dev_ptr(scales), _dev_ptr(xrot_dbg), _stream_handle(stream))
     _check(code)
@@ -195,14 +209,12 @@ def sq_rotate_quantize(X, giv_i, giv_j, giv_theta, R1, R2, Q, scales, xrot_dbg=N
 def sq_rotate_quantize_variant(X, giv_i, giv_j, giv_theta, R1, R2, bits, clip_ratio, Q, scales, xrot_dbg=None,
                                stream=None) -> None:
     """sq_rotate_quantize with the quantizer at ``bits`` bits (2..4) and a clipping ratio in (0, 1]."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     T, K = int(X.shape[0]), int(X.shape[1])
     ldx = int(X.stride(0)) if T > 1 else K
     code = _load().sq_rotate_quantize_variant(
         _dev_ptr(X), T, K, ldx,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(R1), int(R1.shape[0]), _dev_ptr(R2), int(R2.shape[0]), int(bits), float(clip_ratio),
         _dev_ptr(Q), _dev_ptr(scales), _dev_ptr(xrot_dbg), _stream_handle(stream))
     _check(code)
@@ -212,12 +224,15 @@ def sq_prepared_rotation_bytes(n1: int, n2: int) -> int:
     return int(_load().sq_prepared_rotation_bytes(int(n1), int(n2)))
 
 
+_prepared_bytes = functools.lru_cache(maxsize=256)(sq_prepared_rotation_bytes)      # a function of two sizes alone
+
+
 def sq_prepare_rotation(R1, R2, prepared, stream=None) -> None:
     """R1 fp16 [n1, n1], R2 fp16 [n2, n2]; prepared: any device tensor of at least
     sq_prepared_rotation_bytes(n1, n2) bytes, written here and passed to
     sq_rotate_quantize_prepared together with n1 and n2."""
     n1, n2 = int(R1.shape[0]), int(R2.shape[0])
-    need = sq_prepared_rotation_bytes(n1, n2)
+    need = _prepared_bytes(int(n1), int(n2))
     if prepared is not None and need > 0 and prepared.numel() * prepared.element_size() < need:
         raise ValueError("prepared is smaller than sq_prepared_rotation_bytes")
     _check(_load().sq_prepare_rotation(_dev_ptr(R1), n1, _dev_ptr(R2), n2, _dev_ptr(prepared),
@@ -227,17 +242,15 @@ def sq_prepare_rotation(R1, R2, prepared, stream=None) -> None:
 def sq_rotate_quantize_prepared(X, giv_i, giv_j, giv_theta, prepared, n1, n2, Q, scales, xrot_dbg=None,
                                 stream=None) -> None:
     """As sq_rotate_quantize, with the output of sq_prepare_rotation in place of R1 and R2."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     T, K = int(X.shape[0]), int(X.shape[1])
     ldx = int(X.stride(0)) if T > 1 else K
-    need = sq_prepared_rotation_bytes(n1, n2)
+    need = _prepared_bytes(int(n1), int(n2))
     if prepared is not None and need > 0 and prepared.numel() * prepared.element_size() < need:
         raise ValueError("prepared is smaller than sq_prepared_rotation_bytes")
     code = _load().sq_rotate_quantize_prepared(
         _dev_ptr(X), T, K, ldx,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(prepared), int(n1), int(n2),
         _dev_ptr(Q), _dev_ptr(scales), _dev_ptr(xrot_dbg), _stream_handle(stream))
     _check(code)
@@ -286,15 +299,13 @@ def sq_w4a4_gemm_decode(Qx, sx, Qw_tiled, sw, Y, acc_dbg=None, stream=None) -> N
 def sq_rotate_fp16(X, giv_i, giv_j, giv_theta, R1, R2, Xrot, stream=None) -> None:
     """Weight-only setting: the rotated rows as fp16, no quantizer.  X fp16 [T, K]; Xrot fp16
     [T, K] (row stride = Xrot.stride(0)); the rest as sq_rotate_quantize."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     T, K = int(X.shape[0]), int(X.shape[1])
     ldx = int(X.stride(0)) if T > 1 else K
     ldo = int(Xrot.stride(0)) if T > 1 else K
     code = _load().sq_rotate_fp16(
         _dev_ptr(X), T, K, ldx,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(R1), int(R1.shape[0]), _dev_ptr(R2), int(R2.shape[0]), _dev_ptr(Xrot), ldo, _stream_handle(stream))
     _check(code)
 
@@ -338,8 +349,7 @@ def sq_decode_layer(X, giv_i, giv_j, giv_theta, prepared, n1, n2, Qw, sw, Y, wor
     """sq_rotate_quantize_prepared followed by sq_w4a4_gemm in one launch, for at most 32 tokens.
     workspace: device tensor of at least sq_decode_layer_workspace_bytes(T, K) bytes whose first
     16 bytes were zero before the first call (every call leaves them zero again)."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     T, K = int(X.shape[0]), int(X.shape[1])
     N = int(Qw.shape[0])
     ldx = int(X.stride(0)) if T > 1 else K
@@ -347,13 +357,12 @@ def sq_decode_layer(X, giv_i, giv_j, giv_theta, prepared, n1, n2, Qw, sw, Y, wor
     need = sq_decode_layer_workspace_bytes(T, K)
     if workspace is not None and need > 0 and workspace.numel() * workspace.element_size() < need:
         raise ValueError("workspace is smaller than sq_decode_layer_workspace_bytes")
-    need_p = sq_prepared_rotation_bytes(n1, n2)
+    need_p = _prepared_bytes(int(n1), int(n2))
     if prepared is not None and need_p > 0 and prepared.numel() * prepared.element_size() < need_p:
         raise ValueError("prepared is smaller than sq_prepared_rotation_bytes")
     code = _load().sq_decode_layer(
         _dev_ptr(X), T, K, ldx,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(prepared), int(n1), int(n2),
         _dev_ptr(Qw), _dev_ptr(sw), N, _dev_ptr(Y), ldy, _dev_ptr(workspace), _stream_handle(stream))
     _check(code)
@@ -368,19 +377,17 @@ def sq_decode_layer_status(workspace=None, stream=None) -> None:
 def sq_decode_layer_static(X, giv_i, giv_j, giv_theta, prepared, n1, n2, Qw, sw, Y, stream=None) -> None:
     """sq_decode_layer with the workspace inside the library (no device allocation anywhere on
     the way: the binding passes pointers of existing tensors only)."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     T, K = int(X.shape[0]), int(X.shape[1])
     N = int(Qw.shape[0])
     ldx = int(X.stride(0)) if T > 1 else K
     ldy = int(Y.stride(0)) if T > 1 else max(N, 1)
-    need_p = sq_prepared_rotation_bytes(n1, n2)
+    need_p = _prepared_bytes(int(n1), int(n2))
     if prepared is not None and need_p > 0 and prepared.numel() * prepared.element_size() < need_p:
         raise ValueError("prepared is smaller than sq_prepared_rotation_bytes")
     code = _load().sq_decode_layer_static(
         _dev_ptr(X), T, K, ldx,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(prepared), int(n1), int(n2),
         _dev_ptr(Qw), _dev_ptr(sw), N, _dev_ptr(Y), ldy, _stream_handle(stream))
     _check(code)
@@ -389,16 +396,14 @@ def sq_decode_layer_static(X, giv_i, giv_j, giv_theta, prepared, n1, n2, Qw, sw,
 def sq_prepare_weights(W, giv_i, giv_j, giv_theta, R1, R2, workspace, Qw, sw, stream=None) -> None:
     """W fp16 [K, N] (row stride = W.stride(0)); workspace fp16 with at least N*K elements;
     outputs Qw uint8 [N, K/2], sw fp32 [N].  Givens list and R1, R2 as in sq_rotate_quantize."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     K, N = int(W.shape[0]), int(W.shape[1])
     ldw = int(W.stride(0)) if K > 1 else max(N, 1)
     if workspace is not None and workspace.numel() < N * K:
         raise ValueError("workspace holds fewer than N*K elements")
     code = _load().sq_prepare_weights(
         _dev_ptr(W), K, N, ldw,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(R1), int(R1.shape[0]), _dev_ptr(R2), int(R2.shape[0]),
         _dev_ptr(workspace), _dev_ptr(Qw), _dev_ptr(sw), _stream_handle(stream))
     _check(code)
@@ -407,16 +412,14 @@ def sq_prepare_weights(W, giv_i, giv_j, giv_theta, R1, R2, workspace, Qw, sw, st
 def sq_prepare_weights_variant(W, giv_i, giv_j, giv_theta, R1, R2, bits, clip_ratio, workspace, Qw, sw,
                                stream=None) -> None:
     """sq_prepare_weights with the quantizer at ``bits`` bits (2..4) and a clipping ratio in (0, 1]."""
-    gi, gj, gt = _host(giv_i, np.int32), _host(giv_j, np.int32), _host(giv_theta, np.float32)
-    P = 0 if gi is None else int(gi.size)
+    gi, gj, gt, P = _givens(giv_i, giv_j, giv_theta)
     K, N = int(W.shape[0]), int(W.shape[1])
     ldw = int(W.stride(0)) if K > 1 else max(N, 1)
     if workspace is not None and workspace.numel() < N * K:
         raise ValueError("workspace holds fewer than N*K elements")
     code = _load().sq_prepare_weights_variant(
         _dev_ptr(W), K, N, ldw,
-        None if gi is None else gi.ctypes.data, None if gj is None else gj.ctypes.data,
-        None if gt is None else gt.ctypes.data, P,
+        gi, gj, gt, P,
         _dev_ptr(R1), int(R1.shape[0]), _dev_ptr(R2), int(R2.shape[0]), int(bits), float(clip_ratio),
         _dev_ptr(workspace), _dev_ptr(Qw), _dev_ptr(sw), _stream_handle(stream))
     _check(code)
