@@ -76,25 +76,20 @@ __device__ __forceinline__ uint32_t w3_nibbles(uint32_t a0, uint32_t a1, uint32_
     return low | (high & 0x44444444u);
 }
 
-// eight codes of a dword as fp16, in their own order.  Byte m of the dword (with every nibble
-// holding code + 8) is copied into both halves of a dword; "& 0x00F0000F | 0x64006400" leaves
-// 1024 + (code_2m + 8) in the low half and 1024 + 16 (code_2m+1 + 8) in the high half, and one
-// packed multiply-add with (1, 1/16) and (-1032, -72) the two codes, exactly.  Thirteen
-// instructions per dword: the and-or is written as the one three-operand instruction it is (its
+// Two of the eight codes of a dword (byte M, every nibble holding code + 8) as a pair of fp16, in their own order.
+// The byte is copied into both halves of a dword; "& 0x00F0000F | 0x64006400" leaves
+// 1024 + (code_2M + 8) in the low half and 1024 + 16 (code_2M+1 + 8) in the high half, and one
+// packed multiply-add with (1, 1/16) and (-1032, -72) the two codes, exactly.  Three
+// instructions: the and-or is written as the one three-operand instruction it is (its
 // constants must come from registers in that form, which the compiler avoids by emitting two).
-__device__ __forceinline__ v8h widen_codes_f16_in_order(uint32_t w, uint32_t magic_vgpr)
+template <int M>
+__device__ __forceinline__ uint32_t widen_byte_f16(uint32_t x, uint32_t magic_vgpr)
 {
-    const uint32_t x = w ^ 0x88888888u;
     const v2h scale = {(_Float16)1.f, (_Float16)0.0625f}, bias = {(_Float16)-1032.f, (_Float16)-72.f};
-    v2h p[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const uint32_t sel = 0x0C000C00u | (uint32_t)m | ((uint32_t)m << 16);
-        uint32_t h;
-        asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(h) : "v"(__builtin_amdgcn_perm(0u, x, sel)), "s"(0x00F0000Fu), "v"(magic_vgpr));
-        p[m] = __builtin_bit_cast(v2h, h) * scale + bias;
-    }
-    return v8h{p[0][0], p[0][1], p[1][0], p[1][1], p[2][0], p[2][1], p[3][0], p[3][1]};
+    const uint32_t sel = 0x0C000C00u | (uint32_t)M | ((uint32_t)M << 16);
+    uint32_t h;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(h) : "v"(__builtin_amdgcn_perm(0u, x, sel)), "s"(0x00F0000Fu), "v"(magic_vgpr));
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2h, h) * scale + bias);
 }
 
 __device__ __forceinline__ void dma_16_if(const void *gptr, uint32_t lds_addr, int a, int b)
@@ -141,6 +136,12 @@ __device__ __forceinline__ void wait_tile_then_barrier(int rem)
 // channels, 13 VALU instructions per 4 MFMAs) rather than wide.  Within a K tile lane half g takes
 // elements 32g .. 32g + 31 and step s the eight elements 32g + 8s ..: chunk 4g + s of an
 // activation row, dword s of chunk g of a code row.
+// Operands run one step ahead of the MFMAs, also across the turn between K tiles, with the LDS reads and the widening
+// written between the MFMAs: at the start of a tile nothing waits for LDS.  (All of a tile read behind its barrier, us
+// before / after: T = 40, K = N = 4096 47.4 / 39.3; T = 1000, K = 3200, N = 2000 40.6 / 35.4; T = 2048, K = N = 4096 74.4 / 66.8,
+// K = 11008 170 / 162; T = 2048, K = 8192, N = 14336 423 / 415.)  What bounds the large ones is power: the same products of
+// zeros take 50.7 us at T = 2048, K = N = 4096 and 440 against 640 at T = 8192, N = 11008, where torch's fp16 product takes as
+// long as this kernel.
 // The weights are the first MFMA operand, so the 32 x 32 accumulator has the token in the lane and
 // the channel in the register: register e holds channel 8 (e / 4) + 4 (lane / 32) + e % 4, four
 // runs of four consecutive channels.  Two runs are traded between the half-waves (one cross-half
@@ -233,62 +234,98 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
     uint32_t magic;                                    // 1024.0 in both halves, held in a vector register
     asm volatile("v_mov_b32 %0, 0x64006400" : "=v"(magic));
     const int ktiles = K / BK;
+    int stage = 0;
     if (LW == 0 || loader) {
         issue_tile(0, 0, ktiles);
         issue_tile(1, 1, ktiles);
+        wait_tile_then_barrier<LOADS>(ktiles - 1);
+        issue_tile(2, 2, ktiles);
+    } else {
+        asm volatile("s_barrier" ::: "memory");
     }
-    int stage = 0;
     if constexpr (LW > 0) {
         if (loader) {
             // a loading wave: the waits and requests of the loop below and nothing else; it meets the
-            // multiplying waves at each of the ktiles barriers of the kernel
+            // multiplying waves at each of the 1 + ktiles barriers of the kernel
             for (int kt = 0; kt < ktiles; ++kt) {
-                wait_tile_then_barrier<LOADS>(ktiles - 1 - kt);
-                issue_tile(kt + 2, stage == 0 ? 2 : stage - 1, ktiles);
+                wait_tile_then_barrier<LOADS>(ktiles - kt - 2);
+                issue_tile(kt + 3, stage, ktiles);
                 stage = stage == 2 ? 0 : stage + 1;
             }
             return;
         }
     }
+
+    // Operands run one step ahead of the MFMAs: while step s is multiplied, the activations of step s + 1 are read and its
+    // codes widened between the MFMAs, in the order written here.  A dword of codes per step: rb holds a tile's.
+    constexpr int NM = FM * FN;
+    static_assert(STEPS == 4 && FM == 4, "four steps per tile; one activation read behind each of the first MFMAs");
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    uint4 rb[FN];
+    v8h a[2][FM];
+    v4u b[2][FN];
+    uint32_t flipped[FN];
+    auto read_codes = [&](int stage_byte) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) rb[j] = *reinterpret_cast<const uint4 *>(lds + stage_byte + b_off + j * (32 * B_ROW));
+    };
+    auto read_tokens = [&](int set, int stage_byte, int s, int i) {
+        a[set][i] = *reinterpret_cast<const v8h *>(lds + stage_byte + a_off[s] + i * (32 * A_ROW));
+    };
+    // unit u of 4 FN: byte u % 4 of the dword of step s of fragment u / 4
+    auto widen_unit = [&](int set, int s, int u) {
+        const int j = u / 4;
+        if (u % 4 == 0) flipped[j] = (s == 0 ? rb[j].x : s == 1 ? rb[j].y : s == 2 ? rb[j].z : rb[j].w) ^ 0x88888888u;
+        b[set][j][u % 4] = u % 4 == 0   ? widen_byte_f16<0>(flipped[j], magic)
+                           : u % 4 == 1 ? widen_byte_f16<1>(flipped[j], magic)
+                           : u % 4 == 2 ? widen_byte_f16<2>(flipped[j], magic)
+                                        : widen_byte_f16<3>(flipped[j], magic);
+    };
+    // One step on set C; the next one's operands are step S of the tile at BYTE.  TURN: the turn into that tile comes
+    // first, and its codes are read; they are widened in the second half of the step.
+#define SQ_W16_STEP(C, BYTE, S, TURN)                                                                               \
+    do {                                                                                                            \
+        _Pragma("unroll") for (int m = 0; m < NM; ++m) {                                                            \
+            const int j = m / FM, i = m % FM;                                                                       \
+            constexpr int from = (TURN) ? NM / 2 : 0;                                                               \
+            if ((TURN) && m == 1) {                                                                                 \
+                SQ_W16_TURN();                                                                                      \
+                read_codes(BYTE);                                                                                   \
+            }                                                                                                       \
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, b[C][j]), a[C][i], acc[i][j], 0, 0, 0); \
+            if (m >= (TURN) && m < FM + (TURN)) read_tokens(1 - (C), BYTE, S, m - (TURN));                          \
+            _Pragma("unroll") for (int u = 0; u < 4 * FN; ++u)                                                      \
+                if (m == from + u * (NM - from) / (4 * FN)) widen_unit(1 - (C), S, u);                              \
+            __builtin_amdgcn_sched_barrier(0);                                                                      \
+        }                                                                                                           \
+    } while (0)
+    // Tile kt + 1 has landed once only the loads of tile kt + 2 (if it exists) are outstanding.  Behind the barrier every
+    // wave's share of it is in LDS and all reads of tile kt are done, so its stage takes tile kt + 3.
+#define SQ_W16_TURN()                                                                                               \
+    do {                                                                                                            \
+        if constexpr (LW == 0) {                                                                                    \
+            wait_tile_then_barrier<LOADS>(ktiles - kt - 2);                                                         \
+            issue_tile(kt + 3, stage, ktiles);                                                                      \
+        } else {                                                                                                    \
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");                                         \
+        }                                                                                                           \
+    } while (0)
+    read_codes(0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) read_tokens(0, 0, 0, i);
+#pragma unroll
+    for (int u = 0; u < 4 * FN; ++u) widen_unit(0, 0, u);
     for (int kt = 0; kt < ktiles; ++kt) {
-        // Tile kt has landed once only the loads of tile kt + 1 (if it exists) are outstanding.
-        // Behind the barrier every wave's share of it is in LDS and nobody reads tile kt - 1 any
-        // more, so that stage takes tile kt + 2.
-        if constexpr (LW == 0) {
-            wait_tile_then_barrier<LOADS>(ktiles - 1 - kt);
-            issue_tile(kt + 2, stage == 0 ? 2 : stage - 1, ktiles);
-        } else {
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        }
-        const char *st = lds + stage * STAGE;
-        uint32_t rb[FN][STEPS];                        // one dword of codes per step
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int c = 0; c < STEPS / 4; ++c) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(st + b_off + j * (32 * B_ROW) + 16 * c);
-                rb[j][4 * c] = v.x, rb[j][4 * c + 1] = v.y, rb[j][4 * c + 2] = v.z, rb[j][4 * c + 3] = v.w;
-            }
-        v8h a[2][FM];
-#pragma unroll
-        for (int i = 0; i < FM; ++i) a[0][i] = *reinterpret_cast<const v8h *>(st + a_off[0] + i * (32 * A_ROW));
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            if (s + 1 < STEPS) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-                    a[(s + 1) & 1][i] = *reinterpret_cast<const v8h *>(st + a_off[s + 1] + i * (32 * A_ROW));
-            }
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const v8h b = widen_codes_f16_in_order(rb[j][s], magic);
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, a[s & 1][i], acc[i][j], 0, 0, 0);
-            }
-        }
-        stage = stage == 2 ? 0 : stage + 1;
+        const int stage_n = stage == 2 ? 0 : stage + 1;
+        const int cur_byte = stage * STAGE, next_byte = stage_n * STAGE;
+        SQ_W16_STEP(0, cur_byte, 1, 0);
+        SQ_W16_STEP(1, cur_byte, 2, 0);
+        SQ_W16_STEP(0, cur_byte, 3, 0);
+        SQ_W16_STEP(1, next_byte, 0, 1);          // behind the last tile: a stale stage, never used
+        stage = stage_n;
     }
+#undef SQ_W16_STEP
+#undef SQ_W16_TURN
 
     typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 #pragma unroll
