@@ -8,10 +8,10 @@
 // Three kernels: a tile kernel for many tokens (w4a16_gemm_ring_kernel) and two decode-shaped ones,
 // for at most 32 tokens (w4a16_gemm_skinny_kernel) and for at most 16 whose rows fit in LDS
 // (w4a16_gemm_xlds_kernel).  All widen the codes to fp16 in registers, exactly, with the
-// magic-number form described at the two widening functions below.
+// magic-number form described at the widening functions below.
 // sq_pack_w3 / sq_w3a16_gemm (W3A16 of the same table) live here too: the decode-shaped kernels
 // with the codes in three bits each, expanded to nibbles in registers (w3_nibbles).
-#include "sq_common.h"
+#include "sq_gemm_tile.h"
 
 #include <type_traits>
 
@@ -107,25 +107,6 @@ __device__ __forceinline__ void dma_16_if(const void *gptr, uint32_t lds_addr, i
                  : "memory", "m0", "scc");
 }
 
-// Wait for a tile of the ring.  Behind it at most one more tile is in flight, if rem >= 1 (L loads
-// per loading wave and tile, and loads complete in order): then L loads may stay outstanding, else
-// none.  After that the wave's own LDS reads are drained and the waves meet.
-template <int L>
-__device__ __forceinline__ void wait_tile_then_barrier(int rem)
-{
-    static_assert(L > 0 && L < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%1)\n\t"
-                 "s_cmp_ge_i32 %0, 1\n\t"
-                 "s_cbranch_scc1 .Lsq16_landed_%=\n\t"
-                 "s_waitcnt vmcnt(0)\n"
-                 ".Lsq16_landed_%=:\n\t"
-                 "s_waitcnt lgkmcnt(0)\n\t"
-                 "s_barrier"
-                 :
-                 : "s"(rem), "n"(L)
-                 : "memory", "scc");
-}
-
 // Tile kernel for many tokens.  Block tile (WM FM 32) tokens x (WN FN 32) channels, WM x WN waves
 // of FM x FN fragments of 32 x 32; K walked in tiles of 64.  Both operands travel global -> LDS
 // without passing registers (16 bytes per lane), through a ring of three stages, two tiles ahead,
@@ -151,14 +132,16 @@ __device__ __forceinline__ void wait_tile_then_barrier(int rem)
 // would want another swizzle).
 // LW > 0: LW more waves that only request the tiles and wait for them; the multiplying waves then
 // issue no memory instruction inside the loop and meet the others at the barrier of each tile.
-template <int WM, int WN, int FM, int FN, int OCC, int BK, int LW>
-__global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_kernel(
+// KG: groups of WM WN waves that walk K / KG elements each, through rings of their own, and add their sums through LDS.
+template <int WM, int WN, int FM, int FN, int OCC, int BK, int LW, int KG>
+__global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_kernel(
     const __half *__restrict__ X, int64_t ldx, int T, int K, const uint8_t *__restrict__ Qw,
     const float *__restrict__ sw, int N, __half *__restrict__ Y, int64_t ldy, int tiles_m, int tiles_n,
     int vec_store)
 {
     static_assert(BK == 64, "tiles of 64 elements of K");
-    constexpr int NW = WM * WN, NS = 3, STEPS = BK / 16;     // waves; ring stages; MFMA steps per K tile
+    constexpr int NW = WM * WN, NS = 3, STEPS = BK / 16;     // waves of a group; ring stages; MFMA steps per K tile
+    static_assert(KG == 1 || LW == 0, "loading waves: one K group");
     constexpr int BM = WM * FM * 32, BN = WN * FN * 32;
     constexpr int A_ROW = 2 * BK, B_ROW = BK / 2;            // bytes of a tile row
     constexpr int A_CPR = A_ROW / 16, B_CPR = B_ROW / 16;    // 16-byte chunks per row
@@ -172,7 +155,8 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const bool loader = LW > 0 && tid / kWave >= NW;
-    const int wave = loader ? tid / kWave - NW : tid / kWave;    // a loading wave counts from 0 again
+    const int wave = (tid / kWave) % NW;                         // a loading wave counts from 0 again
+    const int kg = LW > 0 ? 0 : __builtin_amdgcn_readfirstlane(tid / kWave / NW);
     const int l32 = lane & 31, g = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
     int bm, bn;
@@ -185,6 +169,7 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
         bn = in_group / gm;
     }
     const int row0 = bm * BM, col0 = bn * BN, Kb = K / 2;
+    const int kg0 = kg * (K / KG);                               // this group's elements of K
 
     // global -> LDS.  One wave-wide load fills 64 consecutive chunk slots: A_RPL rows of activations
     // (lane l lands in row l / A_CPR, physical chunk l % A_CPR, which holds the logical chunk
@@ -196,14 +181,14 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
 #pragma unroll
     for (int u = 0; u < A_LOADS; ++u) {
         const int r = A_RPL * (wave + NL * u) + lane / A_CPR;
-        a_src[u] = X + (int64_t)min(row0 + r, T - 1) * ldx + (((lane % A_CPR) ^ ((r >> 1) & 7)) * 8);
+        a_src[u] = X + (int64_t)min(row0 + r, T - 1) * ldx + kg0 + (((lane % A_CPR) ^ ((r >> 1) & 7)) * 8);
     }
 #pragma unroll
     for (int u = 0; u < B_LOADS; ++u) {
         const int r = B_RPL * (wave + NL * u) + lane / B_CPR;
-        b_src[u] = Qw + (int64_t)min(col0 + r, N - 1) * Kb + (lane % B_CPR) * 16;
+        b_src[u] = Qw + (int64_t)min(col0 + r, N - 1) * Kb + kg0 / 2 + (lane % B_CPR) * 16;
     }
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)ring;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)ring + kg * (NS * STAGE);
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     auto issue_tile = [&](int kt, int stage, int limit) {
         const uint32_t sa = lds_base + (uint32_t)stage * STAGE;
@@ -229,17 +214,17 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
     for (int s = 0; s < STEPS; ++s)
         a_off[s] = (wm * FM * 32 + l32) * A_ROW + (((STEPS * g + s) ^ ((l32 >> 1) & 7)) * 16);
     const int b_off = A_BYTES + (wn * FN * 32 + l32) * B_ROW + g * (STEPS * 4);
-    const char *lds = reinterpret_cast<const char *>(ring);
+    const char *lds = reinterpret_cast<const char *>(ring) + kg * (NS * STAGE);
 
     uint32_t magic;                                    // 1024.0 in both halves, held in a vector register
     asm volatile("v_mov_b32 %0, 0x64006400" : "=v"(magic));
-    const int ktiles = K / BK;
+    const int ktiles = K / (KG * BK);
     int stage = 0;
     if (LW == 0 || loader) {
-        issue_tile(0, 0, ktiles);
-        issue_tile(1, 1, ktiles);
-        wait_tile_then_barrier<LOADS>(ktiles - 1);
-        issue_tile(2, 2, ktiles);
+#pragma unroll
+        for (int t = 0; t < NS - 1; ++t) issue_tile(t, t, ktiles);
+        wait_tile_and_barrier<LOADS, NS>(ktiles - 1);
+        issue_tile(NS - 1, NS - 1, ktiles);
     } else {
         asm volatile("s_barrier" ::: "memory");
     }
@@ -248,9 +233,9 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
             // a loading wave: the waits and requests of the loop below and nothing else; it meets the
             // multiplying waves at each of the 1 + ktiles barriers of the kernel
             for (int kt = 0; kt < ktiles; ++kt) {
-                wait_tile_then_barrier<LOADS>(ktiles - kt - 2);
-                issue_tile(kt + 3, stage, ktiles);
-                stage = stage == 2 ? 0 : stage + 1;
+                wait_tile_and_barrier<LOADS, NS>(ktiles - kt - 2);
+                issue_tile(kt + NS, stage, ktiles);
+                stage = stage == NS - 1 ? 0 : stage + 1;
             }
             return;
         }
@@ -259,7 +244,7 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
     // Operands run one step ahead of the MFMAs: while step s is multiplied, the activations of step s + 1 are read and its
     // codes widened between the MFMAs, in the order written here.  A dword of codes per step: rb holds a tile's.
     constexpr int NM = FM * FN;
-    static_assert(STEPS == 4 && FM == 4, "four steps per tile; one activation read behind each of the first MFMAs");
+    static_assert(STEPS == 4 && NM >= 2, "four steps per tile");
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
     uint4 rb[FN];
     v8h a[2][FM];
@@ -293,19 +278,20 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
                 read_codes(BYTE);                                                                                   \
             }                                                                                                       \
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, b[C][j]), a[C][i], acc[i][j], 0, 0, 0); \
-            if (m >= (TURN) && m < FM + (TURN)) read_tokens(1 - (C), BYTE, S, m - (TURN));                          \
+            _Pragma("unroll") for (int r = 0; r < FM; ++r)                                                          \
+                if (m == (r + (TURN) < NM ? r + (TURN) : NM - 1)) read_tokens(1 - (C), BYTE, S, r);                 \
             _Pragma("unroll") for (int u = 0; u < 4 * FN; ++u)                                                      \
                 if (m == from + u * (NM - from) / (4 * FN)) widen_unit(1 - (C), S, u);                              \
             __builtin_amdgcn_sched_barrier(0);                                                                      \
         }                                                                                                           \
     } while (0)
-    // Tile kt + 1 has landed once only the loads of tile kt + 2 (if it exists) are outstanding.  Behind the barrier every
-    // wave's share of it is in LDS and all reads of tile kt are done, so its stage takes tile kt + 3.
+    // Tile kt + 1 has landed once only the loads of the NS - 2 tiles behind it (those that exist) are outstanding.  Behind
+    // the barrier every wave's share of it is in LDS and all reads of tile kt are done, so its stage takes tile kt + NS.
 #define SQ_W16_TURN()                                                                                               \
     do {                                                                                                            \
         if constexpr (LW == 0) {                                                                                    \
-            wait_tile_then_barrier<LOADS>(ktiles - kt - 2);                                                         \
-            issue_tile(kt + 3, stage, ktiles);                                                                      \
+            wait_tile_and_barrier<LOADS, NS>(ktiles - kt - 2);                                                      \
+            issue_tile(kt + NS, stage, ktiles);                                                                     \
         } else {                                                                                                    \
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");                                         \
         }                                                                                                           \
@@ -316,7 +302,7 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
 #pragma unroll
     for (int u = 0; u < 4 * FN; ++u) widen_unit(0, 0, u);
     for (int kt = 0; kt < ktiles; ++kt) {
-        const int stage_n = stage == 2 ? 0 : stage + 1;
+        const int stage_n = stage == NS - 1 ? 0 : stage + 1;
         const int cur_byte = stage * STAGE, next_byte = stage_n * STAGE;
         SQ_W16_STEP(0, cur_byte, 1, 0);
         SQ_W16_STEP(1, cur_byte, 2, 0);
@@ -326,6 +312,33 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
     }
 #undef SQ_W16_STEP
 #undef SQ_W16_TURN
+
+    if constexpr (KG > 1) {
+        constexpr int ACC = FM * FN * 16;
+        static_assert((KG - 1) * NW * ACC * kWave * 4 <= KG * NS * STAGE, "the other groups' sums fit in the dead rings");
+        float *sums = reinterpret_cast<float *>(ring) + wave * (ACC * kWave) + lane;
+        __syncthreads();
+        if (kg > 0) {
+            float *mine = sums + (kg - 1) * (NW * ACC * kWave);
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) mine[((i * FN + j) * 16 + e) * kWave] = acc[i][j][e];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+#pragma unroll
+                    for (int o = 0; o < KG - 1; ++o)
+                        acc[i][j][e] += sums[o * (NW * ACC * kWave) + ((i * FN + j) * 16 + e) * kWave];
+    }
 
     typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -371,19 +384,19 @@ __global__ __launch_bounds__((WM * WN + LW) * kWave, OCC) void w4a16_gemm_ring_k
     }
 }
 
-template <int WM, int WN, int FM, int FN, int OCC, int BK, int LW = 0>
+template <int WM, int WN, int FM, int FN, int OCC, int BK, int LW = 0, int KG = 1>
 sq_status launch_w4a16_ring(const __half *X, int64_t ldx, int T, int K, const uint8_t *Qw, const float *sw, int N,
                             __half *Y, int64_t ldy, hipStream_t st)
 {
     constexpr int BM = WM * FM * 32, BN = WN * FN * 32;
-    constexpr size_t lds = (size_t)3 * (BM * 2 * BK + BN * BK / 2);
+    constexpr size_t lds = (size_t)3 * KG * (BM * 2 * BK + BN * BK / 2);
     static_assert(lds <= (size_t)kMaxDynamicLds, "ring does not fit in LDS");
-    auto kernel = w4a16_gemm_ring_kernel<WM, WN, FM, FN, OCC, BK, LW>;
-    if ((K % BK) != 0) return SQ_ERR_SHAPE;
+    auto kernel = w4a16_gemm_ring_kernel<WM, WN, FM, FN, OCC, BK, LW, KG>;
+    if ((K % (KG * BK)) != 0) return SQ_ERR_SHAPE;
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return SQ_ERR_LAUNCH;
     const int tiles_m = (T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int vec_store = (((uintptr_t)Y & 15) == 0 && (ldy % 8) == 0) ? 1 : 0;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_m * tiles_n)), dim3((WM * WN + LW) * kWave), lds, st, X, ldx, T, K, Qw,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_m * tiles_n)), dim3((KG * WM * WN + LW) * kWave), lds, st, X, ldx, T, K, Qw,
                        sw, N, Y, ldy, tiles_m, tiles_n, vec_store);
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
@@ -762,6 +775,19 @@ extern "C" sq_status sq_w4a16_gemm(const void *X, int64_t T, int32_t K, int64_t 
     __half *Yh = static_cast<__half *>(Y);
     const int shape = sq::debug_option(SQ_DEBUG_W4A16_LAUNCH_SHAPE);
     const int64_t tiles_large = ((T + 255) / 256) * ((N + 255) / 256);
+    // Few tiles: 64 x 128, then 128 x 128 tiles with two K groups of four waves while one workgroup per CU takes the whole
+    // product (us, 128 x 256 tiles / here: T = 100, K = N = 4096 40.2 / 19.9; T = 333 42.1 / 22.5; T = 100, K = 11008, N = 13824
+    // 100 / 57.5; T = 600, K = N = 4096 42.0 / 30.9; T = 333, N = 9000 44.3 / 35.8; T = 1000, N = 4096 45.0 / 39.9; from the next
+    // round of workgroups on the larger tiles win: T = 600, N = 9000 53.4 / 67.2).  A K tile costs such a wave what its
+    // widening takes to issue, so its fragments are tall (two or four token blocks to one of channels: T = 333, K = N = 4096 with
+    // the fragments of the 64 x 128 tile the other way round 29.9), and two waves per SIMD share it; four K groups gain
+    // little more (22.2).
+    const int64_t tiles_64x128 = ((T + 63) / 64) * ((N + 127) / 128), tiles_128 = ((T + 127) / 128) * ((N + 127) / 128);
+    const bool two_k_groups = K % 128 == 0;
+    if (two_k_groups && (shape == 3 || (shape == 0 && tiles_64x128 <= 256)))
+        return sq::launch_w4a16_ring<1, 4, 2, 1, 1, 64, 0, 2>(Xh, ldx, (int)T, K, Qw, sw, N, Yh, ldy, st);
+    if (two_k_groups && (shape == 4 || (shape == 0 && tiles_128 <= 256)))
+        return sq::launch_w4a16_ring<1, 4, 4, 1, 1, 64, 0, 2>(Xh, ldx, (int)T, K, Qw, sw, N, Yh, ldy, st);
     if (shape == 2 || (shape != 1 && tiles_large >= 192))
         return sq::launch_w4a16_ring<2, 4, 4, 2, 1, 64>(Xh, ldx, (int)T, K, Qw, sw, N, Yh, ldy, st);
     return sq::launch_w4a16_ring<1, 4, 4, 2, 1, 64, 4>(Xh, ldx, (int)T, K, Qw, sw, N, Yh, ldy, st);

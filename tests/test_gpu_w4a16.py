@@ -162,6 +162,13 @@ def test_w4a16_gemm_every_tile_kernel(oracle, shape, T, K, N):
         assert np.array_equal(goti, Yi)
 
 
+# one K tile per group, an odd number, more than the ring holds; ragged tails of both small tiles
+@pytest.mark.parametrize("T,K,N", [(1, 128, 1), (33, 384, 130), (65, 256, 129), (129, 640, 257), (200, 1152, 1000)])
+@pytest.mark.parametrize("shape", [3, 4])
+def test_w4a16_gemm_two_k_groups(oracle, shape, T, K, N):
+    test_w4a16_gemm_every_tile_kernel(oracle, shape, T, K, N)
+
+
 def test_w4a16_gemm_seeded_random_shapes(oracle):
     """Twenty shapes drawn from a seed (T up to 400, K a multiple of 64 up to 1536, N up to 1500,
     a third of them with at most 32 tokens), whatever kernel the dispatcher picks."""
