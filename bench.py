@@ -532,7 +532,7 @@ def main() -> int:
         "metric": f"layer time, rotate+quant then W4A4 GEMM, T={cfg.T} K={cfg.K} N={cfg.N} (also: rotate+quant HBM GB/s, GEMM int TOPS)",
         "value": head["layer_us"], "unit": "us", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": head["layer_us"] / 1e3, "higher_is_better": False, "scaling": "weak",
-        "vs_baseline": None, "dtype": "int4 codes on int8 MFMA, int32 accumulate; fp32 rotation",
+        "vs_baseline": None, "dtype": "int4 codes on 6-bit float or int8 MFMA, exact sums; fp32 rotation",
         "data": "synthetic",
         "config": {"workload": f"{cfg.name}: T={cfg.T} K={cfg.K} ({cfg.n1}x{cfg.n2}) N={cfg.N}, {cfg.P} Givens pairs",
                    "ring_sets": head["ring_sets"], "settle_steps_before_warmup": head["settle_steps"],

@@ -5,7 +5,7 @@
 // its LDS reads: one per two fp32 FMAs.  Here the rows of a token are padded to the 32-row blocks of the
 // matrix instruction, as they are there, and only their number is an argument; padding rows are zeros in LDS
 // that nothing is ever loaded over.  R1 has rows of n1 halves, so its chunks start at any even byte.
-// 48 x 64 at T = 1001: 45.9 us there, 6.5 us here (layer with N = 9216: 73.4 -> 37.9 us).
+// 48 x 64 at T = 1001: 45.9 us there, 10.4 us here (layer with N = 9216: 73.4 -> 37.9 us).
 //
 // Error against 64 bits, relative to the norm (P = 64): 48 x 64 1.4e-7, 85 x 128 1.5e-7, 20 x 32 1.3e-7, where the
 // plain-FMA kernel has 2.1e-7, 2.4e-7 and 1.5e-7: the split of Z rounds both halves to nearest here (with the
