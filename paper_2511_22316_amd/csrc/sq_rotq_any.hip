@@ -7,9 +7,17 @@
 // that nothing is ever loaded over.  R1 has rows of n1 halves, so its chunks start at any even byte.
 // 48 x 64 at T = 1001: 45.9 us there, 10.4 us here (layer with N = 9216: 73.4 -> 37.9 us).
 //
-// Error against 64 bits, relative to the norm (P = 64): 48 x 64 1.4e-7, 85 x 128 1.5e-7, 20 x 32 1.3e-7, where the
-// plain-FMA kernel has 2.1e-7, 2.4e-7 and 1.5e-7: the split of Z rounds both halves to nearest here (with the
-// truncated one of sq_rotq_mfma.hip it was 1.8e-7, 1.9e-7 and 1.7e-7, above that kernel's for the smallest pairs).
+// The plain-FMA kernel holds everything as fp32; the split Z and the Givens values carry scales here that keep the error
+// below that kernel's (rotate_quantize_mfma_body, ANY_N1; they cost 2 - 4 % of the kernel).  Error against 64 bits, relative
+// to the norm, P = 64 (plain-FMA kernel / here):
+//                                  48 x 64            85 x 128           20 x 32
+//   outliers of 1000, body of 1    1.8e-7 / 1.2e-7    2.5e-7 / 1.5e-7    1.3e-7 / 1.2e-7
+//   rows of 0.02 (weights)         1.8e-7 / 1.1e-7    2.5e-7 / 1.4e-7    1.3e-7 / 1.0e-7
+//   rows of 0.001                  1.8e-7 / 1.1e-7    2.5e-7 / 1.4e-7    1.3e-7 / 1.0e-7
+// and, with R2 in blocks, on columns smaller than the others of the same wave by
+//   10^-3                          1.4e-7 / 0.9e-7    1.8e-7 / 1.1e-7    1.1e-7 / 0.8e-7
+//   10^-4                          1.4e-7 / 0.9e-7    1.8e-7 / 1.1e-7    1.0e-7 / 0.8e-7
+//   10^-5                          1.4e-7 / 2.4e-7    1.8e-7 / 2.7e-7    1.0e-7 / 2.3e-7
 // Rotated values beyond the range of fp16 scale their row (rotate_quantize_mfma_body, ANY_N1).
 //
 // The operands are R1 and R2 as they are, also behind a prepared rotation (it holds copies of both): its

@@ -130,8 +130,10 @@ struct RotqShape {
 // CLIP: the quantizer has a clipping ratio below one (plan.clip): entries beyond the end levels
 // are clamped to them.  Without it nothing can lie beyond them and the clamp is not compiled in.
 // ANY_N1: the number of rows is the argument n1_arg, N1 - 31 .. N1 (N1 a multiple of 32) and at least 8;
-// R1, R2 as they are.  A row whose rotated values leave the range of fp16 is scaled by a power of two; Z is split
-// with both halves rounded to nearest.
+// R1, R2 as they are.  Three things hold more bits there than in the other pairs' instantiations, because the kernel these
+// pairs had before held all of it as fp32: Z is split with both halves rounded to nearest, and always behind a scale that
+// puts its largest entry just below 2^15; the remainders of the Givens values enter stage A times 2^11 (kRepairScale).
+// A row whose rotated values leave the range of fp16 is scaled by a power of two.
 template <int N1, int N2, int QS_MAX, int NSX_, bool R1LDS, bool PREPARED, bool F16OUT = false, bool CLIP = false,
           bool ANY_N1 = false>
 __device__ __forceinline__ void rotate_quantize_mfma_body(
@@ -142,6 +144,12 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 {
     using S = RotqShape<N1, N2, NSX_, R1LDS>;
     constexpr bool prepared = PREPARED;
+    // ANY_N1: a remainder v - fp16(v) is at most 2^-11 of the value, 16 at the largest fp16 value: times 2^11 it still fits,
+    // and what fp16 cuts off a remainder is 2^-36 at most, not 2^-25.  To match, stage A multiplies the row itself with
+    // R2 times 2^11 (its entries are at most 1; a wave that meets one of 16 or more takes R2 as it is, and the rows
+    // that the remainders meet times 2^-11), and Z comes out divided by z_unscale.
+    constexpr float kRepairScale = ANY_N1 ? 2048.0f : 1.0f;
+    float z_unscale = 1.0f;
     constexpr int N1P = S::N1P, MB = S::MB, NCB = S::NCB, TPP = S::TPP, KSA = S::KSA, KSB = S::KSB;
     constexpr int CPRX = S::CPRX, LPT = S::LPT, NSX = S::NSX;
     static_assert(!ANY_N1 || (!PREPARED && N1 % 32 == 0), "rows padded to the MFMA block, R1 and R2 as they are");
@@ -285,7 +293,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 const float v = ANY_N1 ? gv[lane + 64 * u] * down : gv[lane + 64 * u];
                 const __half hi = __float2half_rn(v);
                 *reinterpret_cast<__half *>(xt + gs_tile[u]) = hi;
-                *reinterpret_cast<__half *>(lo_t + gs_lo[u]) = __float2half_rn(v - __half2float(hi));
+                *reinterpret_cast<__half *>(lo_t + gs_lo[u]) = __float2half_rn((v - __half2float(hi)) * kRepairScale);
             }
     };
 
@@ -507,9 +515,24 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 }
             }
         }
+        if constexpr (ANY_N1) {
+            typedef uint16_t v8u16 __attribute__((ext_vector_type(8)));
+            v8u16 top = 0;
+#pragma unroll
+            for (int ks = 0; ks < KSA; ++ks)
+                top = __builtin_elementwise_max(top, __builtin_bit_cast(v8u16, r2f[ks]) & (uint16_t)0x7FFF);
+            bool large = false;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) large |= top[e] >= 0x4C00;       // 16.0
+            if (!__any(large)) {
+                z_unscale = 1.0f / kRepairScale;
+#pragma unroll
+                for (int ks = 0; ks < KSA; ++ks) r2f[ks] *= (_Float16)kRepairScale;
+            }
+        }
         // The rows of R2 that repair the Givens rounding (one per q-slot) are picked out of the
         // blocks just built, again on the matrix cores and again exactly: operand A holds a single
-        // 1 per row, at column qlist[slot], and operand B is R2 as stage A uses it.  This saves
+        // 1 (ANY_N1: 2^-11) per row, at column qlist[slot], and operand B is R2 as stage A uses it.  This saves
         // a second trip to memory behind the plan entries.
 #pragma unroll
         for (int xb = 0; xb < QS_MAX / 2; ++xb) {
@@ -521,7 +544,8 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
                 for (int ks = 0; ks < KSA; ++ks) {
                     const int d = q - 16 * ks - 8 * g;          // element of this lane's eight that is 1
-                    const uint32_t one = ((uint32_t)d < 8u) ? (0x3C00u << (16 * (d & 1))) : 0u;
+                    constexpr uint32_t kOne = ANY_N1 ? 0x1000u : 0x3C00u;     // 1 / kRepairScale
+                    const uint32_t one = ((uint32_t)d < 8u) ? (kOne << (16 * (d & 1))) : 0u;
                     const v4u a = {(d >> 1) == 0 ? one : 0u, (d >> 1) == 1 ? one : 0u,
                                    (d >> 1) == 2 ? one : 0u, (d >> 1) == 3 ? one : 0u};
                     c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), r2f[ks], c, 0, 0, 0);
@@ -620,10 +644,15 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) zmax = max_abs16(accz[mb], zmax);
         zmax = wave_max(zmax);
-        float fz_inv = 1.0f;                     // Z * fz in [2^13, 2^14) at its largest entry
-        if (!(zmax >= 1.0f && zmax < 16384.0f) && zmax > 0.f) {
+        // Outside [1, 2^14), Z * fz in [2^13, 2^14) at its largest entry.  ANY_N1: always scaled, to [2^14, 2^15), so that
+        // the lower halves' end at 2^-24 lies 2^-39 below the largest entry and columns of the same wave that are much
+        // smaller keep their bits.
+        constexpr float kUnscaledFrom = ANY_N1 ? 16384.0f : 1.0f, kUnscaledTo = ANY_N1 ? 32768.0f : 16384.0f;
+        constexpr int kTopExponent = ANY_N1 ? 14 : 13;
+        float fz_inv = 1.0f;
+        if (!(zmax >= kUnscaledFrom && zmax < kUnscaledTo) && zmax > 0.f) {
             const int ez = (int)((__float_as_uint(zmax) >> 23) & 0xFF) - 127;
-            const int sh = max(-100, min(100, 13 - ez));
+            const int sh = max(-100, min(100, kTopExponent - ez));
             const float fz = __uint_as_float((uint32_t)(127 + sh) << 23);
             fz_inv = __uint_as_float((uint32_t)(127 - sh) << 23);
 #pragma unroll
@@ -631,7 +660,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
                 for (int e = 0; e < 16; ++e) accz[mb][e] *= fz;
         }
-        if constexpr (ANY_N1) fz_inv *= row_scale[par * TPP + tok_slot];
+        if constexpr (ANY_N1) fz_inv *= row_scale[par * TPP + tok_slot] * z_unscale;
 
         // ---- stage B: Y^T = Z^T R1, Z = hi + lo; the split of step ks+1 is issued between the
         // MFMAs of step ks -----------------------------------------------------------------

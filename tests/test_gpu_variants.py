@@ -485,6 +485,47 @@ def test_rotation_with_any_number_of_rows(oracle, n1, n2, T, P, bits, clip):
     check_rotation(xg[rows], xo)
 
 
+# What a pair without an instantiation of its own keeps of fp32: the relative error (2-norm) stays below that of
+# n1 + n2 roundings of 2^-24 each that add up as independent ones do, where
+#   columns: half of the columns are r times smaller than the others (R2 in blocks of 16 x 16, so the same wave has both)
+#   channels: all channels are r small, and 128 of them go through the Givens list
+#   entries: the entries of R2's first 32 columns are large
+@pytest.mark.parametrize("n1,n2", [(20, 32), (33, 32), (48, 64), (97, 64), (85, 128), (127, 128)])
+@pytest.mark.parametrize("what,r", [("columns", 1e-2), ("columns", 1e-3), ("columns", 1e-4), ("channels", 0.02), ("channels", 1e-3),
+                                    ("entries", 100.0), ("entries", 4000.0)])
+def test_any_number_of_rows_keeps_the_bits_of_fp32(oracle, n1, n2, what, r):
+    print(f"case precision {n1}x{n2} {what} {r}", flush=True)
+    g = np.random.default_rng(n1 + n2)
+    T, K = 33, n1 * n2
+    small = np.zeros(n2, bool)
+    R1, R2 = synth.random_orthogonal(n1, g), synth.random_orthogonal(n2, g)
+    X = 8.0 * g.standard_normal((T, n1, n2))
+    P = 0 if what == "columns" else 64
+    if what == "columns":
+        R2 = np.zeros((n2, n2))
+        for b in range(0, n2, 16):
+            R2[b:b + 16, b:b + 16] = synth.random_orthogonal(16, g)
+        small = (np.arange(n2) // 16) % 2 == 1
+        X[:, :, small] *= r
+    elif what == "channels":
+        X *= r / 8.0
+    else:
+        R2[:, :32] *= r
+    chans = g.permutation(K)[:2 * P].astype(np.int32)
+    cfg = synth.LayerConfig(f"bits_{n1}x{n2}", T, n1, n2, 16, P, "normal", 0, 1.0, 0.0, 20.0, 0.02, 1)
+    R1h, R2h = R1.astype(np.float16), R2.astype(np.float16)
+    L = synth.Layer(cfg, X.reshape(T, K).astype(np.float16), chans[0::2].copy(), chans[1::2].copy(),
+                    g.uniform(-3.1, 3.1, P).astype(np.float32), R1h, R2h, R1h.astype(np.float64), R2h.astype(np.float64))
+    _, _, xg = run_rotate_quantize(L)
+    xo = oracle.rotate(L.X, L.giv_i, L.giv_j, L.giv_theta, R1h, R2h).reshape(T, n1, n2)
+    d = xg.astype(np.float64).reshape(T, n1, n2) - xo
+    groups = [small, ~small] if what == "columns" else [np.arange(n2) < 32, np.arange(n2) >= 32]
+    for cols in groups:
+        if cols.any():
+            err = np.linalg.norm(d[:, :, cols]) / np.linalg.norm(xo[:, :, cols])
+            assert err <= 2.0 ** -24 * np.sqrt(n1 + n2), f"relative error {err:.2e}"
+
+
 @pytest.mark.parametrize("n1,n2", [(20, 32), (48, 64), (85, 128)])
 def test_rotated_outliers_beyond_fp16(oracle, n1, n2):
     """Channels at the largest fp16 value that rotate into one beyond it (up to 4 x 65504 over a chain of pairs),
