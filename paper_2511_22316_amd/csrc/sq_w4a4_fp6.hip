@@ -106,6 +106,17 @@ __device__ __forceinline__ void dma_4(const void *base, uint32_t off)
                  : "memory", "m0", "scc");
 }
 
+// fp16(x0 w0) and fp16(x1 w1) in one dword, each product rounded once, on its way to fp16, as the other GEMM kernels do
+// (their compiler finds this instruction; for two results in one dword it finds two products and a packed conversion,
+// which round twice): Y is the same bit for bit whichever kernel a call takes.
+__device__ __forceinline__ uint32_t scaled_pair(float x0, float w0, float x1, float w1)
+{
+    uint32_t d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(x0), "v"(w0));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(x1), "v"(w1));
+    return d;
+}
+
 // Output tile WM FM 32 tokens x 2 FN 32 channels; KG groups of WM x 2 waves share it and split every K tile.
 template <int WM, int FM, int FN, int KG>
 struct Fp6Shape {
@@ -455,8 +466,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
                         // whole numbers below 2^24 throughout: exact
                         const float a0 = fmaf(64.f, acc[i][j][e], sbn[e]) + sat[i];
                         const float a1 = fmaf(64.f, acc[i][j][e + 1], sbn[e + 1]) + sat[i];
-                        const v2h pair = {(_Float16)__float2half_rn(a0 * sxt[i] * swn[e]), (_Float16)__float2half_rn(a1 * sxt[i] * swn[e + 1])};
-                        run[(e / 4) & 1][(e / 2) & 1] = __builtin_bit_cast(uint32_t, pair);
+                        run[(e / 4) & 1][(e / 2) & 1] = scaled_pair(a0 * sxt[i], swn[e], a1 * sxt[i], swn[e + 1]);
                     }
                     // lower half-wave: both halves of the first run; upper half-wave: of the second
                     const v2u s0 = __builtin_amdgcn_permlane32_swap(run[0][0], run[1][0], false, false);

@@ -407,6 +407,25 @@ def test_gemm_six_bit_float_kernel(oracle, case, T, K, N):
         assert half_ulp_distance(Yg, Yo).max() <= 1
 
 
+@pytest.mark.parametrize("case,other", [(18, 16), (19, 4)])
+def test_gemm_six_bit_float_kernel_rounds_like_the_others(case, other):
+    """The same fp16 outputs, bit for bit, as from the int8 tile kernel."""
+    print(f"case gemm rounding {case} against {other}", flush=True)
+    import paper_2511_22316_amd as sq
+    T, K, N = 700, 1024, 1032
+    g = np.random.default_rng(case)
+    sx, sw = g.uniform(0.05, 4.0, T).astype(np.float32), g.uniform(1e-5, 5e-4, N).astype(np.float32)
+    Qx, Qw = synth.random_codes(T, K, 31), synth.random_codes(N, K, 32)
+    Y = []
+    for shape in (case, other):
+        sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, shape + 1)
+        try:
+            Y.append(run_gemm(Qx, sx, Qw, sw)[0])
+        finally:
+            sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, 0)
+    assert np.array_equal(Y[0].view(np.uint16), Y[1].view(np.uint16))
+
+
 def test_gemm_seeded_random_shapes_bit_exact(oracle):
     """Thirty shapes drawn from a seed (T up to 700, K a multiple of 32 up to 2304, N up to 3000, a
     third of them with at most 64 tokens): whatever kernel and launch shape the dispatcher picks,
