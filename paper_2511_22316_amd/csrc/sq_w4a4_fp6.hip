@@ -20,6 +20,7 @@
 // two groups of four waves of 64 x 128 that take half of every K tile each.  The conversion is done in registers, by
 // every wave for itself: one that is shared through LDS (24 bytes per 32 codes written once and read by all) moves 1.5
 // times the bytes out of LDS, writes them at a quarter of the read rate, and was 10 - 15 % slower.
+#include "sq_fp6_store.h"
 #include "sq_gemm_tile.h"
 #include "sq_w4a4_fp6.h"
 
@@ -155,7 +156,7 @@ template <int WM, int FM, int FN, int KG>
 __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp6_kernel(
     const uint8_t *__restrict__ Qx, const float *__restrict__ sx, int T, int Kb, const uint8_t *__restrict__ Qw,
     const float *__restrict__ sw, int N, __half *__restrict__ Y, int64_t ldy, int32_t *__restrict__ acc_dbg,
-    int tiles_m, int tiles_n, int vec_store)
+    int tiles_m, int tiles_n, int rows_aligned)
 {
     using G = Fp6Shape<WM, FM, FN, KG>;
     constexpr int WN = G::WN, BM = G::BM, BN = G::BN, NS = G::NS, NW = G::NW, BKB = G::BKB, STEPS = G::STEPS;
@@ -194,8 +195,8 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     auto origin = [&](int tile, int &row0, int &col0) {
         int bm, bn;
         tile_of_index(tile, tiles_m, tiles_n, bm, bn);
-        row0 = min(bm * BM, T - BM);
-        col0 = min(bn * BN, N - BN);
+        row0 = fp6_tile_origin(bm, BM, T);
+        col0 = fp6_tile_origin(bn, BN, N);
     };
     // first request of an output tile: where its rows lie; its dequantization steps go to LDS too (two sets alternate)
     auto open_tile = [&]() {
@@ -427,6 +428,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         }
         int row0, col0;
         origin(tile, row0, col0);
+        const bool vector_stores = fp6_vector_stores(rows_aligned != 0, col0);
         auto sum_of = [&](int r) { return KG == 2 ? sums[r] + sums[BM + BN + r] : sums[r]; };
         constexpr int FMO = KG == 2 ? 1 : FM;             // fragment rows this wave finishes
         float sxt[FMO], sat[FMO];
@@ -473,7 +475,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
                     const v2u s1 = __builtin_amdgcn_permlane32_swap(run[0][1], run[1][1], false, false);
                     w[h] = uint4{s0[0], s1[0], s0[1], s1[1]};
                 }
-                if (vec_store) {
+                if (vector_stores) {
                     *reinterpret_cast<uint4 *>(ydst[i] + nj) = w[0];
                     *reinterpret_cast<uint4 *>(ydst[i] + nj + 16) = w[1];
                 } else {
@@ -514,14 +516,14 @@ static sq_status launch(const uint8_t *Qx, const float *sx, int T, int K, const 
     auto kernel = w4a4_gemm_fp6_kernel<WM, FM, FN, KG>;
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return SQ_ERR_LAUNCH;
     const int tiles_m = (T + G::BM - 1) / G::BM, tiles_n = (N + G::BN - 1) / G::BN, tiles = tiles_m * tiles_n;
-    const int vec_store = (((uintptr_t)Y & 15) == 0 && (ldy % 8) == 0) ? 1 : 0;
+    const int rows_aligned = fp6_rows_aligned((uintptr_t)Y, ldy) ? 1 : 0;
     static_assert(G::NS * 256 <= 768, "the requests run at most one output tile ahead");
     // One workgroup per CU walks over its output tiles: the loads of the next one run behind the epilogue (T = 8192,
     // K = 8192, N = 28672: 1060 -> 1037 us).  (Two K groups exchange their sums through the ring: one
     // output tile each.)
     const bool walk = KG == 1 && tiles > 256;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(walk ? 256 : tiles)), dim3(G::NT), G::LDS_BYTES, st, Qx, sx, T, K / 2, Qw,
-                       sw, N, Y, ldy, acc_dbg, tiles_m, tiles_n, vec_store);
+                       sw, N, Y, ldy, acc_dbg, tiles_m, tiles_n, rows_aligned);
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 

@@ -418,3 +418,43 @@ def test_kron_factor_follows_alg1(lib, oracle):
     a = C.c_int32(0)
     assert lib.sq_kron_factor(0, C.byref(a), C.byref(a)) == 2
     assert lib.sq_kron_factor(8, None, C.byref(a)) == 1
+
+
+FP6_STORES = r"""
+#include "sq_fp6_store.h"
+#include <cstdio>
+#include <initializer_list>
+// every 16-byte store of every output tile of the 6-bit float GEMM kernel begins at a multiple of 16 bytes, the tiles
+// cover the matrix and stay inside it, and where the channels allow it they all take such stores
+int main()
+{
+    for (int size : {128, 256})
+        for (int n = 256; n <= 900; n += (n % 16 < 4) ? 1 : 3)
+            for (int64_t ldy : {(int64_t)n, (int64_t)(n + 7) / 8 * 8, (int64_t)n + 9, (int64_t)(n + 23) / 8 * 8})
+                for (uintptr_t y : {(uintptr_t)4096, (uintptr_t)4098, (uintptr_t)4104}) {
+                    int covered = 0;
+                    for (int tile = 0; tile < (n + size - 1) / size; ++tile) {
+                        const int col0 = sq::fp6_tile_origin(tile, size, n);
+                        if (col0 > covered || col0 < 0 || col0 + size > n) return std::printf("tile %d of n = %d\n", tile, n), 1;
+                        covered = col0 + size;
+                        const bool vector = sq::fp6_vector_stores(sq::fp6_rows_aligned(y, ldy), col0);
+                        if (!vector && y % 16 == 0 && ldy % 8 == 0 && n % 8 == 0) return std::printf("n = %d not taken\n", n), 1;
+                        for (int row = 0; vector && row < 3; ++row)
+                            for (int c = 0; c < size; c += 8)
+                                if ((y + 2 * (row * ldy + col0 + c)) % 16) return std::printf("n = %d ldy = %d\n", n, (int)ldy), 1;
+                    }
+                    if (covered != n) return std::printf("n = %d: covered %d\n", n, covered), 1;
+                }
+    return 0;
+}
+"""
+
+
+def test_six_bit_float_kernel_stores_are_aligned(tmp_path):
+    import subprocess
+    src, exe = tmp_path / "stores.cpp", tmp_path / "stores"
+    src.write_text(FP6_STORES)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2511_22316_amd", "csrc"), str(src), "-o",
+                    str(exe)], check=True)
+    run = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout

@@ -9,7 +9,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 from paper_2511_22316_amd import synth
-from parity_util import (Y_ROW_TOL, check_codes, check_rotation, codes_of, half_ulp_distance,
+from parity_util import (Y_ROW_TOL, check_codes, check_rotation, codes_of, dev, half_ulp_distance, host,
                          run_gemm, run_rotate_quantize)
 
 pytestmark = pytest.mark.gpu
@@ -405,6 +405,30 @@ def test_gemm_six_bit_float_kernel(oracle, case, T, K, N):
             sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, 0)
         assert np.array_equal(accg, acco)
         assert half_ulp_distance(Yg, Yo).max() <= 1
+
+
+@pytest.mark.parametrize("case,T,K,N", [(18, 130, 768, 257), (18, 128, 768, 260), (18, 140, 768, 522), (18, 129, 768, 512),
+                                        (19, 257, 768, 257), (19, 256, 768, 300), (19, 300, 768, 517), (19, 257, 768, 512)])
+def test_gemm_six_bit_float_kernel_padded_rows(oracle, case, T, K, N):
+    """Output rows longer than N, a multiple of eight: the last tile of a row begins at any channel, and the channels
+    behind the end keep what they held."""
+    print(f"case gemm six-bit padded rows {case} T={T} K={K} N={N}", flush=True)
+    import torch
+    import paper_2511_22316_amd as sq
+    g = np.random.default_rng(case + N)
+    sx, sw = g.uniform(0.05, 4.0, T).astype(np.float32), g.uniform(1e-6, 5e-5, N).astype(np.float32)
+    Qx, Qw = synth.random_codes(T, K, 41), synth.random_codes(N, K, 42)
+    Yo, _ = oracle.gemm(Qx, sx, Qw, sw)
+    room = torch.full((T + 1, (N + 7) // 8 * 8 + 8), -77.0, dtype=torch.float16, device="cuda")
+    sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, case + 1)
+    try:
+        sq.sq_w4a4_gemm(dev(Qx), dev(sx), dev(Qw), dev(sw), room[:T, :N])
+        torch.cuda.synchronize()
+    finally:
+        sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, 0)
+    got = host(room)
+    assert half_ulp_distance(np.ascontiguousarray(got[:T, :N]), Yo).max() <= 1
+    assert np.all(got[:T, N:] == -77.0) and np.all(got[T] == -77.0)
 
 
 @pytest.mark.parametrize("case,other", [(18, 16), (19, 4)])
