@@ -851,7 +851,7 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // 128x256 or 256x256 tiles: one workgroup per CU either way, so the time goes with the number
     // of rounds of 256 tiles.  On the 6-bit float instruction (cases 18 and 19) a 256x256 tile takes about 1.6 times as
     // long as a 128x256 one (K = 4096 / 8192 / 11008, all CUs busy: 42.3 / 74.6 / 98 against 28.0 / 46.8 / 60.2 us),
-    // on the int8 instruction (cases 16 and 4) 1.85 times.
+    // on the int8 instruction (cases 16, 17 and 4) 1.85 times.
     if (choice < 0) {
         const int64_t n_small = (int64_t)((Ti + 127) / 128) * ((N + 255) / 256);
         const int64_t n_large = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
@@ -864,9 +864,11 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         const bool small_pays = K >= 5120 || (K >= 2048 && n_small >= 192);
         if (prefer_large && K >= 1024 && sq::w4a4_fp6_takes(true, Ti, K, N)) choice = 19;
         else if (!prefer_large && small_pays && sq::w4a4_fp6_takes(false, Ti, K, N)) choice = 18;
-        // (case 16: the 128x256 tile with four loading waves, 32.0 -> 31.5 us at T = 2048, K = N = 4096 against case 1,
-        // the same tile with the loads in the multiplying waves)
-        else choice = (20 * rounds_small > 37 * rounds_large) ? 4 : 16;
+        // (Cases 16 and 17: the 128x256 tile with four loading waves; 16, eight multiplying waves of 64x64: 32.0 -> 31.5 us at
+        // T = 2048, K = N = 4096 against case 1, the same tile with the loads in the multiplying waves; 17, four of
+        // 64x128 with half the widening per MFMA: T = 2048, N = 4096, K = 65792 396 -> 376 us, K = 130816 791 -> 751
+        // against 16.  Its gain grows with the number of K tiles and turns positive at about 20 of them.)
+        else choice = (20 * rounds_small > 37 * rounds_large) ? 4 : (K >= 6144 ? 17 : 16);
     }
     switch (choice) {
         case 0: return sq::launch_main<2, 2, 2, 4, 128, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
@@ -878,6 +880,7 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         case 10: return sq::launch_main<2, 2, 1, 1, 128, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 11: return sq::launch_main<2, 2, 1, 2, 128, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 16: return sq::launch_main<2, 4, 2, 2, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        case 17: return sq::launch_main<2, 2, 2, 4, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 14: if (K % 512 == 0) return sq::launch_main<2, 2, 1, 1, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 15: if (K % 512 == 0) return sq::launch_main<2, 2, 1, 2, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 7: if (Ti <= 32) return sq::launch_skinny<1, 1, 16>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
