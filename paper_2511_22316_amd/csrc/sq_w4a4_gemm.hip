@@ -801,13 +801,20 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // memory round trip per K tile (us, generic / here): K = 3200, T = 1, N = 4096 20.0 / 8.9; T = 1000, N = 4096 29.2 / 19.0;
     // T = 8000, N = 27000 824 / 618; K = 10880, T = 100, N = 300 65.1 / 24.3.
     // 64x64 tiles while two of them per CU take the whole product (T = 300, N = 4096, K = 3200: 12.6 against 15.3 us with
-    // 128x128 tiles); 256x256 tiles once every CU has one and K is long (T = 4000, N = 4096: K = 3200 47.8 against 53.1
-    // us with 128x128 tiles, K = 10880 132 against 154; K = 640, N = 27000 111 against 94 us).
+    // 128x128 tiles); else 128x128 tiles, two per CU, or, with long K, 256x256 tiles, one per CU, whichever is done first.
+    // In units of a full round of 128x128 tiles, a last round with one tile per CU or less takes 0.6, and a round of
+    // 256x256 tiles 1.8, or 1.65 with very long K, where power counts more than rounds.  (128x128 / 256x256 tiles, us:
+    // T = 333, N = 33000, 774 or 258 of them: K = 3200 46.3 / 73.4, K = 10880 139 / 212; T = 333, N = 28672, 672 or 224:
+    // K = 3200 35.5 / 40.0; T = 512, N = 28672, 896 or 224: K = 3200 47.9 / 41.8; T = 2048, N = 20000, 2512 or 632:
+    // K = 2176 82.7 / 88.9, K = 10880 358 / 342; K = 640, T = 8000, N = 27000 94 / 111.)
     if ((K % 256) != 0) {
-        const int64_t n64 = (int64_t)((Ti + 63) / 64) * ((N + 63) / 64);
-        const int64_t n256 = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
-        if (n64 <= 512) return sq::launch_main<2, 2, 1, 1, 64, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
-        if (n256 >= 256 && K >= 2048) return sq::launch_main<4, 2, 2, 4, 64, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        auto tiles = [&](int side) { return (int64_t)((Ti + side - 1) / side) * ((N + side - 1) / side); };
+        if (tiles(64) <= 512) return sq::launch_main<2, 2, 1, 1, 64, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        const int64_t n128 = tiles(128), rest = n128 % 512;
+        const int64_t time_128 = 20 * (n128 / 512) + (rest == 0 ? 0 : rest <= 256 ? 12 : 20);
+        const int64_t time_256 = (tiles(256) + 255) / 256 * (K >= 8192 ? 33 : 36);
+        if (K >= 2048 && time_256 <= time_128)
+            return sq::launch_main<4, 2, 2, 4, 64, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         return sq::launch_main<2, 2, 2, 2, 64, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
     }
     // At most 64 tokens: one pass over the weights by the decode-shaped kernel; its launch shape

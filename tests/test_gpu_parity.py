@@ -363,7 +363,7 @@ def test_gemm_every_tile_launch_shape(oracle, case, T, K, N):
 
 # one K tile, fewer than the ring has stages, many; 64x64, 128x128 and 256x256 output tiles with ragged ends
 @pytest.mark.parametrize("T,K,N", [(1, 128, 1), (65, 128, 300), (33, 384, 700), (64, 640, 32768), (65, 384, 32700), (300, 896, 4097),
-                                   (1025, 640, 4200), (4100, 2176, 4000), (257, 2176, 65500)])
+                                   (1025, 640, 4200), (4100, 2176, 4000), (257, 2176, 65500), (385, 2176, 25001)])
 def test_gemm_odd_multiples_of_128(oracle, T, K, N):
     print(f"case gemm K an odd multiple of 128: T={T} K={K} N={N}", flush=True)
     g = np.random.default_rng(T + K + N)
