@@ -865,10 +865,16 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         const int64_t rounds_small = (n_small + 255) / 256, rounds_large = (n_large + 255) / 256;
         const bool prefer_large = 5 * rounds_small > 8 * rounds_large;
         // The gain of the 6-bit form is power, and its loop is the longer one in cycles: it pays once the K loop
-        // dominates and most of the CUs work (us, int8 against 6-bit: T = 1024, K = 768, N = 8192 11.6 / 12.3;
-        // K = 2048 18.6 / 18.3; K = 8192 51.5 / 48.4; 162 tiles of 128x256: K = 4096 24.6 / 25.1, K = 8192 42.9 / 41.9;
-        // 256x256 tiles, T = 3000, N = 11008: K = 768 43.2 / 41.6, K = 2048 80.0 / 68.2).
-        const bool small_pays = K >= 5120 || (K >= 2048 && n_small >= 192);
+        // dominates and most of the CUs work.  Its time over the better int8 shape's, 128x256 tiles, by their number:
+        //              129 - 176        192      200      224      256
+        //   K = 1024   1.07 - 1.10      1.08     1.07     1.06     1.03
+        //   K = 2048   1.02 - 1.04      1.02     1.01     0.99     0.97
+        //   K = 3072   0.99 - 1.00      0.99     0.97     0.95     0.94
+        //   K = 3584   0.98 - 0.99      0.98     0.96     0.95     0.93
+        //   K = 5120   0.95 - 0.97      0.95     0.93     0.92     0.91      (162 tiles: 30.1 / 29.1 us)
+        // and with 256x256 tiles, 132 - 256 of them: K = 768 0.94 - 0.99, K = 1024 0.90 - 0.97, K = 4096 0.80 - 0.84.
+        // Several rounds count by their average (K = 2048: 387 tiles 33.5 / 34.8 us, 648 tiles 50.3 / 50.5).
+        const bool small_pays = K >= 3584 || (K >= 2048 && n_small >= 216 * rounds_small);
         if (prefer_large && K >= 1024 && sq::w4a4_fp6_takes(true, Ti, K, N)) choice = 19;
         else if (!prefer_large && small_pays && sq::w4a4_fp6_takes(false, Ti, K, N)) choice = 18;
         // (Cases 16 and 17: the 128x256 tile with four loading waves; 16, eight multiplying waves of 64x64: 32.0 -> 31.5 us at
