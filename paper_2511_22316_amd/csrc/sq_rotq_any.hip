@@ -18,7 +18,6 @@
 //   10^-3                          1.4e-7 / 0.9e-7    1.8e-7 / 1.1e-7    1.1e-7 / 0.8e-7
 //   10^-4                          1.4e-7 / 0.9e-7    1.8e-7 / 1.1e-7    1.0e-7 / 0.8e-7
 //   10^-5                          1.4e-7 / 2.4e-7    1.8e-7 / 2.7e-7    1.0e-7 / 2.3e-7
-// Rotated values beyond the range of fp16 scale their row (rotate_quantize_mfma_body, ANY_N1).
 //
 // The operands are R1 and R2 as they are, also behind a prepared rotation (it holds copies of both): its
 // layout for these pairs stays what it was.
@@ -66,7 +65,7 @@ sq_status launch_ring(const AnyArgs &a, const RotqPlan &plan, hipStream_t st)
 {
     using S = RotqShape<N1P, N2, NSX, R1LDS>;
     const int qsteps = (plan.n_qslots + 15) / 16;
-    const int sides = S::side_tiles(qsteps, OCC), lds = S::lds_bytes(qsteps, sides) + S::ROW_SCALE_BYTES;
+    const int sides = S::side_tiles(qsteps, OCC), lds = S::lds_bytes(qsteps, sides);
     if (lds > kMaxDynamicLds) return SQ_ERR_SHAPE;
     const int groups = (a.T + S::TPP - 1) / S::TPP, by_lds = (160 * 1024) / lds;
     const int resident = 256 * (by_lds < OCC ? by_lds : OCC);
@@ -91,7 +90,7 @@ sq_status launch_qs(const AnyArgs &a, const RotqPlan &plan, hipStream_t st)
 {
     if constexpr (N1P == 96 && QS_MAX == 4) {
         using S2 = RotqShape<N1P, N2, 2, true>;
-        if (2 * (S2::lds_bytes((plan.n_qslots + 15) / 16, 1) + S2::ROW_SCALE_BYTES) <= 160 * 1024)
+        if (2 * S2::lds_bytes((plan.n_qslots + 15) / 16, 1) <= 160 * 1024)
             return launch_ring<N1P, N2, QS_MAX, 2, 2, true>(a, plan, st);
     }
     return launch_ring<N1P, N2, QS_MAX, 3, (N1P <= 64) ? 2 : 1, false>(a, plan, st);

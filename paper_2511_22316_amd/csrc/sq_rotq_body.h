@@ -94,9 +94,8 @@ struct RotqShape {
     static constexpr bool R1_SHARED = R1LDS_ || MB <= 2;
     static constexpr int R1F_BYTES = R1_SHARED ? MB * KSB * 1024 : 0;
     static constexpr int OFF_LO = OFF_R1F + R1F_BYTES;                // [TPP][side tiles][qsteps][LO_STEP]
-    // after the side tiles (runtime size): [TPP][128] float, [2][TPP][4] float
-    static constexpr int TAIL_BYTES = TPP * (kRotqMaxSlots * 4 + 32);
-    static constexpr int ROW_SCALE_BYTES = 2 * TPP * 4;               // behind those, where n1 is an argument
+    // after the side tiles (runtime size): [TPP][128] float, [2][TPP][4] float, [2][TPP] float
+    static constexpr int TAIL_BYTES = TPP * (kRotqMaxSlots * 4 + 32 + 8);
     // sides: side tiles per token slot, 2 (they alternate from token to token, one barrier per
     // token) or 1 (less LDS, a second barrier per token)
     static constexpr int lds_bytes(int qsteps, int sides)
@@ -133,7 +132,8 @@ struct RotqShape {
 // R1, R2 as they are.  Three things hold more bits there than in the other pairs' instantiations, because the kernel these
 // pairs had before held all of it as fp32: Z is split with both halves rounded to nearest, and always behind a scale that
 // puts its largest entry just below 2^15; the remainders of the Givens values enter stage A times 2^11 (kRepairScale).
-// A row whose rotated values leave the range of fp16 is scaled by a power of two.
+// A row with a Givens value beyond the range of fp16 (two channels near its end may rotate into one beyond it) is divided
+// by a power of two in its tile, and the results are multiplied by it (row_scale).
 template <int N1, int N2, int QS_MAX, int NSX_, bool R1LDS, bool PREPARED, bool F16OUT = false, bool CLIP = false,
           bool ANY_N1 = false>
 __device__ __forceinline__ void rotate_quantize_mfma_body(
@@ -182,7 +182,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
     const int off_gv = S::OFF_LO + TPP * sides * lo_bytes;
     const int side_mask = sides - 1;                         // 1: the two tiles alternate, 0: one tile
     const int off_red = off_gv + TPP * kRotqMaxSlots * 4;    // [2][TPP][4] floats
-    // ANY_N1: what the row in the tile of a token slot was divided by, a power of two (1 nearly always)
+    // what the row in the tile of a token slot was divided by, a power of two (1 nearly always)
     float *row_scale = reinterpret_cast<float *>(lds + off_red + 32 * TPP);        // [2][TPP]
 
     const int groups = (T + TPP - 1) / TPP;
@@ -263,37 +263,36 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
             }
         }
         __builtin_amdgcn_wave_barrier();
-        float down = 1.0f;
-        if constexpr (ANY_N1) {
-            // two channels near the largest fp16 value may rotate into one beyond it: the whole row is
-            // divided by a power of two then, which moves nothing but the subnormals of a row that large
-            float top = 0.f;
+        float v[2], top = 0.f;
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (gs_tile[u] >= 0) top = fmaxf(top, fabsf(gv[lane + 64 * u]));
-            float up = 1.0f;
-            if (__any(top > 65504.0f)) {
-                const int e = min((int)(__float_as_uint(wave_max(top)) >> 23) - 127 - 14, 24);
-                up = __uint_as_float((uint32_t)(127 + e) << 23);
-                down = __uint_as_float((uint32_t)(127 - e) << 23);
-                for (int c = lane; c < n1 * CPRX; c += 64) {
-                    v8h *chunk16 = reinterpret_cast<v8h *>(xt + 16 * c);
-                    v8h v = *chunk16;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = (_Float16)((float)v[k] * down);
-                    *chunk16 = v;
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-            if (lane == 0) row_scale[(side & 1) * TPP + tok_slot] = up;
+        for (int u = 0; u < 2; ++u) {
+            v[u] = gs_tile[u] >= 0 ? gv[lane + 64 * u] : 0.f;
+            top = fmaxf(top, fabsf(v[u]));
         }
+        float up = 1.0f;
+        if (__any(top > 65504.0f)) {
+            // beyond fp16: the whole row is divided by a power of two, which moves nothing but the subnormals of a
+            // row that large
+            const int e = min((int)(__float_as_uint(wave_max(top)) >> 23) - 127 - 14, 24);
+            up = __uint_as_float((uint32_t)(127 + e) << 23);
+            const float down = __uint_as_float((uint32_t)(127 - e) << 23);
+            for (int c = lane; c < n1 * CPRX; c += 64) {
+                v8h *chunk16 = reinterpret_cast<v8h *>(xt + 16 * c);
+                v8h w = *chunk16;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) w[k] = (_Float16)((float)w[k] * down);
+                *chunk16 = w;
+            }
+            __builtin_amdgcn_wave_barrier();
+            v[0] *= down, v[1] *= down;
+        }
+        if (lane == 0) row_scale[(side & 1) * TPP + tok_slot] = up;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             if (gs_tile[u] >= 0) {
-                const float v = ANY_N1 ? gv[lane + 64 * u] * down : gv[lane + 64 * u];
-                const __half hi = __float2half_rn(v);
+                const __half hi = __float2half_rn(v[u]);
                 *reinterpret_cast<__half *>(xt + gs_tile[u]) = hi;
-                *reinterpret_cast<__half *>(lo_t + gs_lo[u]) = __float2half_rn((v - __half2float(hi)) * kRepairScale);
+                *reinterpret_cast<__half *>(lo_t + gs_lo[u]) = __float2half_rn((v[u] - __half2float(hi)) * kRepairScale);
             }
     };
 
@@ -462,7 +461,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 *reinterpret_cast<uint4 *>(lds + S::OFF_X + tile * S::TILE_BYTES + (n1 * CPRX + r) * 16) = uint4{0, 0, 0, 0};
             }
         }
-        if (ANY_N1 && tid < 2 * TPP) row_scale[tid] = 1.0f;
+        if (tid < 2 * TPP) row_scale[tid] = 1.0f;
         for (int c = tid; c < TPP * sides * lo_bytes / 16; c += 256)
             *reinterpret_cast<uint4 *>(lds + S::OFF_LO + c * 16) = uint4{0, 0, 0, 0};
 
@@ -660,7 +659,8 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
                 for (int e = 0; e < 16; ++e) accz[mb][e] *= fz;
         }
-        if constexpr (ANY_N1) fz_inv *= row_scale[par * TPP + tok_slot] * z_unscale;
+        // (read ahead of B2: behind it the owner of the row after next may write this one's place)
+        const float z_scale = row_scale[par * TPP + tok_slot] * (ANY_N1 ? z_unscale : 1.0f);
 
         // ---- stage B: Y^T = Z^T R1, Z = hi + lo; the split of step ks+1 is issued between the
         // MFMAs of step ks -----------------------------------------------------------------
@@ -720,6 +720,8 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 for (int nb = 0; nb < MB; ++nb) rb[nb] = rb_n[nb];
             }
         }
+
+        fz_inv *= z_scale;                       // Y = accy * fz_inv
 
         // ---- per-token step: wave maximum now, token maximum after the barrier --------------
         float amax = 0.f;

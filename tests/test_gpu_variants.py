@@ -526,7 +526,9 @@ def test_any_number_of_rows_keeps_the_bits_of_fp32(oracle, n1, n2, what, r):
             assert err <= 2.0 ** -24 * np.sqrt(n1 + n2), f"relative error {err:.2e}"
 
 
-@pytest.mark.parametrize("n1,n2", [(20, 32), (48, 64), (85, 128)])
+@pytest.mark.parametrize("n1,n2", [(20, 32), (48, 64), (85, 128),
+                                   # the pairs with instantiations of their own
+                                   (16, 32), (32, 64), (64, 64), (80, 64), (64, 128), (128, 64), (86, 128), (112, 128)])
 def test_rotated_outliers_beyond_fp16(oracle, n1, n2):
     """Channels at the largest fp16 value that rotate into one beyond it (up to 4 x 65504 over a chain of pairs),
     in some rows and not in others: the fp32 rows, steps and codes are as accurate as anywhere."""
@@ -545,3 +547,29 @@ def test_rotated_outliers_beyond_fp16(oracle, n1, n2):
     Qo, so = oracle.quantize_rows(xo)
     check_rotation(xg, xo)
     check_codes(Qg, sg, Qo, so)
+    check_rotated_f16(run_rotate_fp16(Lb), oracle.rotate_f16(X, gi, gj, gt, L.R1, L.R2), xo)
+    Q3, s3, _ = run_variant(Lb, 3, 0.85)
+    check_variant_codes(Q3, s3, *oracle.quantize_rows_variant(xo, 3, 0.85), 3)
+
+
+def test_rotated_outliers_beyond_fp16_in_many_rows_and_in_one_launch(oracle):
+    """The same where a workgroup of the 64 x 64 kernel takes many rows (two LDS tiles, both parities of a row's scale),
+    and through the single-launch layer."""
+    import torch
+    from test_gpu_decode_layer import Layer
+    print("case outliers beyond fp16, many rows", flush=True)
+    cfg = synth.LayerConfig("beyond_many", 8200, 64, 64, 16, 3, "normal", 2, 50.0, 0.01, 20.0, 0.02, 77)
+    L = synth.layer(cfg)
+    X = L.X.copy()
+    hit = np.random.default_rng(7).random(X.shape[0]) < 0.3
+    X[hit, 5] = X[hit, 77] = X[hit, 200] = 65504.0
+    gi, gj = np.array([5, 200, 5], np.int32), np.array([77, 9, 200], np.int32)
+    Lb = synth.Layer(cfg, X, gi, gj, np.full(3, np.pi / 4, np.float32), L.R1, L.R2, L.R1_f64, L.R2_f64)
+    Qg, sg, xg = run_rotate_quantize(Lb)
+    xo = oracle.rotate(X, gi, gj, Lb.giv_theta, L.R1, L.R2)
+    Qo, so = oracle.quantize_rows(xo)
+    check_rotation(xg, xo)
+    check_codes(Qg, sg, Qo, so)
+    lay = Layer(Lb, 700, 32)
+    want = lay.two_calls(X[:32])
+    assert hit[:32].any() and bool(torch.isfinite(want).all()) and torch.equal(lay.one_launch(X[:32]), want)
