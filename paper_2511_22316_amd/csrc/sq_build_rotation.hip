@@ -237,13 +237,15 @@ __device__ __forceinline__ void chain_step(const double *vec, int n, int k, floa
 // and takes the steps without a barrier,
 // 0.73 us each.  T = 2048, K = 4096, P = 32: 91.5 -> 41.5 us against a reduction over all
 // channels by the whole workgroup in every step.
+// BY_ALL: that reduction instead, which is faster for few steps over few channels (steps_by_all).
+template <bool BY_ALL>
 __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
     const __half *__restrict__ X, int64_t ldx, int T, int K, int n1, int n2, int P, double inv_sqrt_n2,
     const float *__restrict__ rowmax, int32_t *__restrict__ giv_i, int32_t *__restrict__ giv_j,
     float *__restrict__ giv_theta, float *__restrict__ chain)
 {
     extern __shared__ uint32_t build_lds[];
-    uint32_t *slots_a = build_lds;
+    uint32_t *slots_a = build_lds, *slots_b = build_lds + 3 * kBuildWaves;
     double(*vec)[kMaxSide] = reinterpret_cast<double(*)[kMaxSide]>(build_lds + 6 * kBuildWaves);   // V1 | V2 H
     double *v2 = vec[2];
     double(*target)[kMaxSide] = reinterpret_cast<double(*)[kMaxSide]>(vec[3]);                     // U1 | U2
@@ -280,10 +282,10 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
         key[e] = in ? (__half_as_ushort(h) & 0x7FFFu) : 0xFFFFu;
         if (in) cvec[at(k0 + e)] = (double)__half2float(h);
     }
-    if (P > 0 && K <= kMaxCandidates) {
+    if (P > 0 && !BY_ALL && K <= kMaxCandidates) {
         if (tid < K) cand[tid] = (uint32_t)tid;
         if (tid == 0) *n_cand = (uint32_t)K;
-    } else if (P > 0) {
+    } else if (P > 0 && !BY_ALL) {
         const uint32_t wanted = 2 * (uint32_t)P;
 #pragma unroll
         for (int e = 0; e < kMost; ++e)
@@ -346,7 +348,35 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
 
     // ART (Sec. 4.2; several steps as in the "ART steps" study): largest against smallest
     // magnitude, angle of Lemma 1, after which both channels hold r / sqrt(2)
-    if (wave == 0 && P > 0) {
+    if constexpr (BY_ALL) {
+        for (int p = 0; p < P; ++p) {
+            // k ascends within a thread, so strict comparisons keep the lower channel among equals
+            uint32_t hi_h = 0, hi_l = 0, hi_at = 0xFFFFFFFFu, lo_h = 0xFFFFFFFFu, lo_l = 0xFFFFFFFFu, lo_at = 0xFFFFFFFFu;
+            for (int k = tid; k < K; k += kBuildThreads) {
+                uint32_t h, l;
+                magnitude_key(cvec[at(k)], h, l);
+                if (hi_at == 0xFFFFFFFFu || h > hi_h || (h == hi_h && l > hi_l)) hi_h = h, hi_l = l, hi_at = (uint32_t)k;
+            }
+            const int i = (int)block_arg<true>(hi_h, hi_l, hi_at, slots_a);
+            for (int k = tid; k < K; k += kBuildThreads) {
+                uint32_t h, l;
+                magnitude_key(cvec[at(k)], h, l);
+                if (k != i && (lo_at == 0xFFFFFFFFu || h < lo_h || (h == lo_h && l < lo_l)))
+                    lo_h = h, lo_l = l, lo_at = (uint32_t)k;
+            }
+            const int j = (int)block_arg<false>(lo_h, lo_l, lo_at, slots_b);
+            if (tid == 0) {
+                const double a = cvec[at(i)], b = cvec[at(j)];
+                const double e = sqrt(a * a + b * b) * 0.70710678118654752440;
+                giv_i[p] = i;
+                giv_j[p] = j;
+                pair_a[p] = a;
+                pair_b[p] = b;
+                cvec[at(i)] = cvec[at(j)] = e;
+            }
+            __syncthreads();
+        }
+    } else if (wave == 0 && P > 0) {
         // This lane's candidates by channel, their magnitudes as integers; no channel: zero among the largest, all
         // ones among the smallest.
         uint32_t idx[4];
@@ -532,6 +562,11 @@ __global__ __launch_bounds__(kMaxSide) void urt_columns_kernel(const float *__re
         if (r < n && c0 + c < n) R2[r * n + c0 + c] = __float2half_rn(s[c] * inv_sqrt_n2);
 }
 
+// A step over all channels by the whole workgroup takes 1.5 us at K = 512 and 2 us at 1024, the choice of the candidates 5 us
+// whatever P (whole call in us, candidates / all channels: K = 512, P = 1 24.1 / 20.3, P = 4 26.7 / 25.2, P = 6 28.6 / 28.5;
+// K = 1024, P = 1 25.4 / 21.6, P = 3 26.7 / 25.1, P = 4 27.7 / 28.0; K = 1536, P = 1 25.6 / 21.9, P = 2 26.5 / 26.4).
+bool steps_by_all(int32_t K, int32_t P) { return K > kMaxCandidates && 256 * P + K <= 1792; }
+
 bool build_shape_ok(int64_t T, int32_t K, int32_t n1, int32_t n2, int32_t P)
 {
     if (T < 1 || T > SQ_MAX_ROWS || K <= 0 || P < 0 || P > SQ_MAX_GIVENS) return false;
@@ -586,7 +621,7 @@ extern "C" sq_status sq_build_rotation(const void *X, int64_t T, int32_t K, int6
     const int64_t row_groups = (T + 3) / 4;
     hipLaunchKernelGGL(sq::row_absmax_kernel, dim3((unsigned)(row_groups < 4096 ? row_groups : 4096)), dim3(256), 0,
                        st, Xh, ldx, (int)T, K, w.rowmax);
-    auto art = sq::art_urt_kernel;
+    auto art = sq::steps_by_all(K, P) ? sq::art_urt_kernel<true> : sq::art_urt_kernel<false>;
     // 146.9 KiB at the largest K
     const size_t lds = sq::kBuildSmallBytes + (size_t)(K + n1) * sizeof(double) + sq::kSelectWords * sizeof(uint32_t);
     if (!sq::allow_large_lds(reinterpret_cast<const void *>(art))) return SQ_ERR_LAUNCH;

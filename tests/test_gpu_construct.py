@@ -124,12 +124,14 @@ def test_build_rotation_edge_cases(oracle):
     assert np.allclose(np.abs(g["R2"].astype(np.float64)), 1.0 / np.sqrt(cfg.n2), rtol=1e-3)
 
 
-@pytest.mark.parametrize("n1,n2,P", [(8, 32, 64), (16, 32, 64), (9, 32, 1), (48, 64, 40), (128, 128, 64), (65, 8, 7)])
+@pytest.mark.parametrize("n1,n2,P", [(8, 32, 64), (16, 32, 64), (9, 32, 1), (48, 64, 40), (128, 128, 64), (65, 8, 7),
+                                     # the longest lists that the whole workgroup takes, and the shortest it doesn't
+                                     (9, 32, 5), (9, 32, 6), (16, 32, 5), (32, 32, 3), (33, 32, 2), (33, 32, 3), (48, 32, 1), (48, 32, 2)])
 @pytest.mark.parametrize("values", [[0.0], [1.0], [0.0, 3.0], [1.0, -1.0, 0.5, 60000.0], [6e-8, 1.2e-7, 0.0, 2.0, -2.25]])
 def test_art_channels_among_equal_magnitudes(oracle, n1, n2, P, values):
     """A calibration row of a few distinct magnitudes: nearly every choice is among equals, and the channels that can
     be chosen at all are cut out of runs of equals (the lowest channels win); just below and above the 256 channels
-    up to which every one is a candidate."""
+    up to which every one is a candidate, and on either side of the rule for short lists."""
     print(f"case ART ties {n1}x{n2} P={P} values={values}", flush=True)
     X = np.random.default_rng(n1 + P).choice(np.array(values, np.float16), size=(1, n1 * n2))
     g = run_build(X, n1, n2, P)
