@@ -51,7 +51,7 @@ __host__ int64_t build_workspace_floats(int64_t T, int n1, int n2)
     return t_pad + 8 * kMaxSide + 2 * (int64_t)n1 * n1 + 3 * (int64_t)n2 * n2;
 }
 
-__host__ BuildWorkspace carve_workspace(void *workspace, int64_t T, int n1, int n2)
+__host__ BuildWorkspace carve_workspace(void *workspace, int64_t T)
 {
     BuildWorkspace w;
     float *p = static_cast<float *>(workspace);
@@ -234,9 +234,8 @@ __device__ __forceinline__ void chain_step(const double *vec, int n, int k, floa
 // before it, so what it picks is one of those or among the first 2 p + 1 in order of the calibration row as it was:
 // the 2 P largest and the 2 P smallest channels are all that can ever be chosen.  A radix selection on the
 // 15-bit magnitudes (two histograms of 256 bins, ties by channel) finds them, and one wave then holds them in registers
-// and takes the steps without a barrier,
-// 0.73 us each.  T = 2048, K = 4096, P = 32: 91.5 -> 41.5 us against a reduction over all
-// channels by the whole workgroup in every step.
+// and takes the steps without a barrier, 0.73 us each.  T = 2048, K = 4096, P = 32: 91.5 -> 41.5 us against a
+// reduction over all channels by the whole workgroup in every step.
 // BY_ALL: that reduction instead, which is faster for few steps over few channels (steps_by_all).
 template <bool BY_ALL>
 __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
@@ -614,7 +613,7 @@ extern "C" sq_status sq_build_rotation(const void *X, int64_t T, int32_t K, int6
         return SQ_ERR_ALIGN;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const sq::BuildWorkspace w = sq::carve_workspace(workspace, T, n1, n2);
+    const sq::BuildWorkspace w = sq::carve_workspace(workspace, T);
     const double inv_sqrt_n2 = 1.0 / sqrt((double)n2);
     const __half *Xh = static_cast<const __half *>(X);
 
@@ -622,7 +621,7 @@ extern "C" sq_status sq_build_rotation(const void *X, int64_t T, int32_t K, int6
     hipLaunchKernelGGL(sq::row_absmax_kernel, dim3((unsigned)(row_groups < 4096 ? row_groups : 4096)), dim3(256), 0,
                        st, Xh, ldx, (int)T, K, w.rowmax);
     auto art = sq::steps_by_all(K, P) ? sq::art_urt_kernel<true> : sq::art_urt_kernel<false>;
-    // 146.9 KiB at the largest K
+    // 143.5 KiB at the largest K
     const size_t lds = sq::kBuildSmallBytes + (size_t)(K + n1) * sizeof(double) + sq::kSelectWords * sizeof(uint32_t);
     if (!sq::allow_large_lds(reinterpret_cast<const void *>(art))) return SQ_ERR_LAUNCH;
     hipLaunchKernelGGL(art, dim3(1), dim3(sq::kBuildThreads), lds, st, Xh, ldx, (int)T, K, n1, n2, P, inv_sqrt_n2,
