@@ -382,7 +382,7 @@ def test_gemm_odd_multiples_of_128(oracle, T, K, N):
     # 256 x 256 tiles: the same, and more tiles than CUs (a workgroup walks over several)
     (19, 256, 768, 256), (19, 257, 1280, 257), (19, 300, 1024, 520), (19, 513, 2048, 300), (19, 2100, 768, 8300),
     (19, 4100, 1024, 4500),
-    # the longest K: sums of the offset codes up to 225 K, just below 2^24
+    # the longest K: a code goes in as code + 8, so the sum of products of sevens is 225 K, just below 2^24
     (18, 128, 65536, 256), (19, 256, 65536, 256)])
 def test_gemm_six_bit_float_kernel(oracle, case, T, K, N):
     """The tile kernel on the 6-bit float instruction, forced through the debug option: int32 accumulators bit-exact
@@ -393,9 +393,13 @@ def test_gemm_six_bit_float_kernel(oracle, case, T, K, N):
     sx = g.uniform(0.05, 4.0, T).astype(np.float32)
     sw = g.uniform(1e-6, 5e-5, N).astype(np.float32)
     inputs = [(synth.random_codes(T, K, 500 + T), synth.random_codes(N, K, 600 + N))]
-    if T * K * N < 1 << 33:      # all (-8)(-8) and all (-8) * 7: the ends of the range
-        low, high = np.full((T, K // 2), 0x88, np.uint8), np.full((N, K // 2), 0x77, np.uint8)
-        inputs += [(low, np.full((N, K // 2), 0x88, np.uint8)), (low, high)]
+    if T * K * N < 1 << 33:
+        # The ends of the range.  -8 goes in as 0: against it the accumulator stays zero and the row sums are all there is;
+        # 7 goes in as 15: the largest sum there is, and with sixes among the sevens one whose low bits count.
+        full = lambda rows, byte: np.full((rows, K // 2), byte, np.uint8)     # noqa: E731
+        near = lambda rows: (0x66 + g.integers(0, 2, (rows, K // 2)) + 16 * g.integers(0, 2, (rows, K // 2))).astype(np.uint8)    # noqa: E731
+        inputs += [(full(T, 0x88), full(N, 0x88)), (full(T, 0x88), full(N, 0x77)), (full(T, 0x77), full(N, 0x77)),
+                   (near(T), near(N))]
     for Qx, Qw in inputs:
         Yo, acco = oracle.gemm(Qx, sx, Qw, sw)
         sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, case + 1)
