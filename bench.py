@@ -21,7 +21,7 @@ the same launches was tried for this and replays 1-5 us per node slower than the
 them; the held stream is used only where needed because the clocks sag during the hold.)
 
 Prints ONE JSON line: layer time (us), the per-kernel rates, the roofline of the dominant kernel
-(the GEMM: int8 MFMA) and of the rotate+quantize kernel (HBM), and the CPU oracle timed on this
+(the GEMM: 6-bit float MFMA, or the weight stream) and of the rotate+quantize kernel (HBM), and the CPU oracle timed on this
 box's host cores beside them (all cores and one thread; the headline layer and large_prefill).
 """
 from __future__ import annotations
@@ -42,6 +42,7 @@ import numpy as np
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E
 INT8_MFMA_PEAK_TOPS = 5000.0    # MI355X dense int8 matrix peak
+FP6_MFMA_PEAK_TOPS = 10000.0    # MI355X dense 6-bit float matrix peak
 RING_BYTES = 640 << 20          # > 2x the 256 MB Infinity Cache
 MIN_TIMED_STEPS = 100           # per figure, whatever --steps says
 MIN_BLOCKS = 3
@@ -50,14 +51,14 @@ MIN_BLOCKS = 3
 # summaries profiles/w4a4_gemm_<workload>.md and profiles/rotate_quantize_<workload>.md (FETCH_SIZE
 # and WRITE_SIZE, each scaled by what the counter reads for a plain 256 MiB copy: x2.000, x1.000).
 PROFILED_TRAFFIC = {
-    "attn_proj": {"gemm": {"fetch": 33825466, "write": 16777216},
-                  "rotate_quantize": {"fetch": 17075532, "write": 4227072}},
-    "mlp_down": {"gemm": {"fetch": 90541107, "write": 16777216},
-                 "rotate_quantize": {"fetch": 45743076, "write": 11337728}},
-    "decode": {"gemm": {"fetch": 118156413, "write": 458752},
-               "rotate_quantize": {"fetch": 659389, "write": 33024}},
-    "large_prefill": {"gemm": {"fetch": 1414240495, "write": 469762048},
-                      "rotate_quantize": {"fetch": 134742838, "write": 33816576}},
+    "attn_proj": {"gemm": {"fetch": 34077390, "write": 16810368},
+                  "rotate_quantize": {"fetch": 17090465, "write": 4227072}},
+    "mlp_down": {"gemm": {"fetch": 96835291, "write": 16804928},
+                 "rotate_quantize": {"fetch": 45757211, "write": 11337728}},
+    "decode": {"gemm": {"fetch": 118147247, "write": 458752},
+               "rotate_quantize": {"fetch": 690089, "write": 33024}},
+    "large_prefill": {"gemm": {"fetch": 1419501906, "write": 632612096},
+                      "rotate_quantize": {"fetch": 134755113, "write": 33816576}},
 }
 
 
@@ -299,7 +300,9 @@ def measure_layer(cfg, torch, sq, synth, steps, warmup):
         "massive_channels": [int(c) for c in synth.massive_channels(cfg)],
     }
     out["rotate_quant_frac_of_hbm_peak"] = out["rotate_quant_GBps"] / HBM_PEAK_GBPS
-    out["gemm_frac_of_int8_peak"] = out["gemm_int_TOPS"] / INT8_MFMA_PEAK_TOPS
+    # the layers of many tokens are multiplied by the 6-bit float instruction, the decode-shaped ones by the int8 one
+    matrix, peak = ("int8", INT8_MFMA_PEAK_TOPS) if T <= 64 else ("fp6", FP6_MFMA_PEAK_TOPS)
+    out[f"gemm_frac_of_{matrix}_peak"] = out["gemm_int_TOPS"] / peak
     out["gemm_weight_stream_frac_of_hbm_peak"] = out["gemm_weight_stream_GBps"] / HBM_PEAK_GBPS
     del B
     torch.cuda.empty_cache()
@@ -523,8 +526,8 @@ def main() -> int:
                          "traffic": traffic("gemm"), "traffic_detail": prof.get("gemm"),
                          "traffic_source": source("w4a4_gemm")}
     else:
-        gemm_roofline = {"kernel": "w4a4_gemm_kernel", "bound": "mfma", "achieved": gemm_tops,
-                         "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s", "frac": gemm_tops / INT8_MFMA_PEAK_TOPS,
+        gemm_roofline = {"kernel": "w4a4_gemm_fp6_kernel", "bound": "mfma", "achieved": gemm_tops,
+                         "peak": FP6_MFMA_PEAK_TOPS, "unit": "TOP/s", "frac": gemm_tops / FP6_MFMA_PEAK_TOPS,
                          "ops_per_launch": gemm_ops(cfg.T, cfg.K, cfg.N), "launch_us": head["gemm_us"],
                          "timing": timing_note + head["gemm_timing"], "traffic": traffic("gemm"), "traffic_detail": prof.get("gemm"),
                          "traffic_source": source("w4a4_gemm")}

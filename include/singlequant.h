@@ -69,8 +69,14 @@ typedef enum {
  *      n1 x n2 view of x;  R1, R2 are passed un-transposed.
  *   3. Quantizer of Sec. 3.2 with a per-token step:  s = max_k |x'_k| / 7
  *      (s = 1 for an all-zero row), code_k = clamp(floor(x'_k / s + 1/2), -8, 7).
- * Arithmetic is fp32 or better; x' is never written to memory unless
- * xrot_dbg is given.
+ * Products are exact and sums fp32.  On the matrix cores the Givens results and
+ * X_mat R2 pass as pairs of fp16 halves: x' is within about 2e-7 of exact
+ * arithmetic, relative to its norm (the plain kernel's fp32: 1e-7 to 3e-7).
+ * The pairs n1 x n2 with a kernel of their own keep 21 bits and end at
+ * 2^-25 absolute, so that rows of 0.001 with 64 pairs come out within 9e-6, and
+ * columns of R2 whose results are 1000 times smaller than their neighbours'
+ * within 4e-6 of themselves.  x' is never written to memory unless xrot_dbg is
+ * given.
  *
  *   X          device, fp16 [T, ldx]; rows 16-byte aligned (ldx % 8 == 0)
  *   T, K, ldx  tokens, channels (= n1*n2, even), leading dimension >= K
@@ -191,9 +197,9 @@ sq_status sq_w4a4_gemm_decode(const uint8_t *Qx, const float *sx, int64_t T, int
  * its result is kept in fp16.
  *
  * sq_rotate_fp16   steps 1 and 2 of sq_rotate_quantize (Givens list, then the
- *   Kronecker rotation of Eq. 18) with fp32-or-better arithmetic, each entry of
- *   the rotated row then rounded once to fp16 (nearest even; beyond the fp16
- *   range the result is infinite).  No quantizer.
+ *   Kronecker rotation of Eq. 18) in the same arithmetic, each entry of the
+ *   rotated row then rounded once to fp16 (nearest even; beyond the fp16 range
+ *   the result is infinite).  No quantizer.
  *     X, T, K, ldx, giv_*, P, R1, n1, R2, n2   as sq_rotate_quantize
  *     Xrot   device out, fp16 [T, ldo], 16-byte aligned, ldo >= K, ldo % 8 == 0
  *
