@@ -383,9 +383,12 @@ static sq_status rotate_quantize_any(const void *X, int64_t T, int32_t K, int64_
                                    &status, prepared))
             return status;
         // Every other pair the matrix cores can take, at any token count.  Plain-FMA kernel / this one, us in a stream of
-        // calls: 48 x 64, T = 1001 45.3 / 11.6; 36 x 64, T = 2048 59.4 / 12.1; 97 x 64, T = 16 43.0 / 16.4; 85 x 128,
-        // T = 2048 855 / 39; 8 x 32 .. 33 x 32 at T <= 500 10.1 - 11.9 / 10.4 - 11.5 (both below the host's time).
-        if (sq::rotq_any_covers(n1, n2))
+        // launches, P = 32: 48 x 64, T = 1001 40.6 / 9.2; 36 x 64, T = 2048 52.7 / 11.9; 97 x 64, T = 16 41.1 / 17.1; 85 x 128,
+        // T = 2048 842 / 40.9; 33 x 32, T = 500 10.9 / 6.7.  The plain kernel stays where short rows are done before this
+        // one's prologue: 8 x 32, T = 64, no pairs, fp16 output 3.96 / 4.45, P = 8 5.05 / 5.23; beside that line 8 x 32, P = 32
+        // 6.7 / 5.4, T = 2048 6.6 / 6.0; 9 x 32 0 - 6 % apart up to T = 500, 10 x 32 3 % at most, either way.
+        const bool short_rows = K <= 288 && P <= 8 && T <= 512;
+        if (!short_rows && sq::rotq_any_covers(n1, n2))
             return sq::rotq_any_launch(static_cast<const __half *>(X), ldx, (int)T, n1, n2, plan,
                                        static_cast<const __half *>(R1), static_cast<const __half *>(R2), Q, scales,
                                        xrot_dbg, static_cast<__half *>(xout), ldo, st);

@@ -453,7 +453,7 @@ def test_decode_path_captured_in_a_graph_replays_correctly(oracle):
 
 
 # rows at the edges of the 32-row blocks, odd ones among them, and token counts around a pass of the workgroup
-@pytest.mark.parametrize("n1,n2,T,P", [(8, 32, 1, 4), (9, 32, 37, 3), (31, 32, 4100, 64), (33, 32, 5, 16), (127, 32, 9, 64),
+@pytest.mark.parametrize("n1,n2,T,P", [(8, 32, 1, 4), (9, 32, 37, 3), (8, 32, 513, 4), (9, 32, 5, 9), (10, 32, 7, 8), (31, 32, 4100, 64), (33, 32, 5, 16), (127, 32, 9, 64),
                                        (13, 64, 3, 64), (48, 64, 1001, 16), (65, 64, 2, 0), (96, 64, 33, 64), (97, 64, 19, 8),
                                        (126, 64, 600, 32), (11, 128, 40, 64), (63, 128, 7, 64), (85, 128, 530, 16),
                                        (96, 128, 16, 64), (111, 128, 300, 0), (127, 128, 3, 64)])
