@@ -5,7 +5,7 @@
 // its LDS reads: one per two fp32 FMAs.  Here the rows of a token are padded to the 32-row blocks of the
 // matrix instruction, as they are there, and only their number is an argument; padding rows are zeros in LDS
 // that nothing is ever loaded over.  R1 has rows of n1 halves, so its chunks start at any even byte.
-// 48 x 64 at T = 1001: 45.9 us there, 10.4 us here (layer with N = 9216: 73.4 -> 37.9 us).
+// 48 x 64 at T = 1001: 45.9 us there, 10.7 us here (layer with N = 9216: 78.4 -> 38.5 us).
 //
 // The plain-FMA kernel holds everything as fp32; the split Z and the Givens values carry scales here that keep the error
 // below that kernel's (rotate_quantize_mfma_body, ANY_N1; they cost 2 - 4 % of the kernel).  Error against 64 bits, relative

@@ -12,14 +12,16 @@
 // taken beside it.  What the encoding buys over the codes times 16 as int8 is power: with the codes of Gaussian rows a
 // register-only loop on all CUs sustains 7.6 POP/s against 4.3 POP/s, both at the power limit of the chip.
 //
-// What bounds the kernel (T = 8192, K = 8192, N = 28672: 1010 us against 1330 us on the int8 instruction; T = 2048,
-// K = N = 4096 28.0 against 30.6 us; K = 11008 60.2 against 67.7 us): the issue slots of a wave, one instruction per 4.9
-// cycles.  Widening a nibble operand takes 14 instructions per fragment and step, so a wave's tile is as large as the
-// registers allow.  256 x 256 tile: four waves of 128 x 128, one per SIMD (7 instructions of conversion per matrix
-// instruction; eight waves of 64 x 128 take 11.5 and were 8 % slower).  128 x 256 tile, for fewer tokens or channels:
-// two groups of four waves of 64 x 128 that take half of every K tile each.  The conversion is done in registers, by
-// every wave for itself: one that is shared through LDS (24 bytes per 32 codes written once and read by all) moves 1.5
-// times the bytes out of LDS, writes them at a quarter of the read rate, and was 10 - 15 % slower.
+// What bounds the kernel (int8 instruction / here, same launches in turn: T = 8192, K = 8192, N = 28672 1359 / 1018 us; T = 2048,
+// N = 4096, K = 4096 33.7 / 31.9 us, K = 11008 72.9 / 66.3 us) is its instruction stream: matrix cores 53 % busy with
+// 256 x 256 tiles, 68 % of a wave's life executing, 13 % waiting for an issue slot, 19 % in waits, one instruction per 6.0
+// cycles; with 128 x 256 tiles one per 4.7 - 5.0 cycles of a SIMD (two waves).  Widening a nibble operand takes 14
+// instructions per fragment and step, so a wave's tile is as large as the registers allow.  256 x 256 tile: four waves
+// of 128 x 128, one per SIMD (7 instructions of conversion per matrix instruction; eight waves of 64 x 128 take 11.5
+// and were 8 % slower).  128 x 256 tile, for fewer tokens or channels: two groups of four waves of 64 x 128 that take
+// half of every K tile each.  The conversion is done in registers, by every wave for itself: one that is shared
+// through LDS (24 bytes per 32 codes written once and read by all) moves 1.5 times the bytes out of LDS, writes them
+// at a quarter of the read rate, and was 10 - 15 % slower.
 #include "sq_fp6_store.h"
 #include "sq_gemm_tile.h"
 #include "sq_w4a4_fp6.h"
