@@ -26,6 +26,12 @@ __device__ __forceinline__ void wait_loads_le()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// the same value of every lane, in a scalar register
+__device__ __forceinline__ float wave_uniform(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+
 // swizzle of a tile row with CPR 16-byte chunks: 8 consecutive rows land on 8 different
 // 16-byte bank groups for the column-of-rows access pattern of MFMA operand reads
 template <int CPR>
@@ -94,7 +100,7 @@ struct RotqShape {
     static constexpr bool R1_SHARED = R1LDS_ || MB <= 2;
     static constexpr int R1F_BYTES = R1_SHARED ? MB * KSB * 1024 : 0;
     static constexpr int OFF_LO = OFF_R1F + R1F_BYTES;                // [TPP][side tiles][qsteps][LO_STEP]
-    // after the side tiles (runtime size): [TPP][128] float, [2][TPP][4] float, [2][TPP] float
+    // after the side tiles (runtime size): [TPP][128] float, [2][TPP][4] float, [2][TPP] int
     static constexpr int TAIL_BYTES = TPP * (kRotqMaxSlots * 4 + 32 + 8);
     // sides: side tiles per token slot, 2 (they alternate from token to token, one barrier per
     // token) or 1 (less LDS, a second barrier per token)
@@ -133,7 +139,7 @@ struct RotqShape {
 // pairs had before held all of it as fp32: Z is split with both halves rounded to nearest, and always behind a scale that
 // puts its largest entry just below 2^15; the remainders of the Givens values enter stage A times 2^11 (kRepairScale).
 // A row with a Givens value beyond the range of fp16 (two channels near its end may rotate into one beyond it) is divided
-// by a power of two in its tile, and the results are multiplied by it (row_scale).
+// by a power of two in its tile, and the results are multiplied by it (row_exponent).
 template <int N1, int N2, int QS_MAX, int NSX_, bool R1LDS, bool PREPARED, bool F16OUT = false, bool CLIP = false,
           bool ANY_N1 = false>
 __device__ __forceinline__ void rotate_quantize_mfma_body(
@@ -147,9 +153,9 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
     // ANY_N1: a remainder v - fp16(v) is at most 2^-11 of the value, 16 at the largest fp16 value: times 2^11 it still fits,
     // and what fp16 cuts off a remainder is 2^-36 at most, not 2^-25.  To match, stage A multiplies the row itself with
     // R2 times 2^11 (its entries are at most 1; a wave that meets one of 16 or more takes R2 as it is, and the rows
-    // that the remainders meet times 2^-11), and Z comes out divided by z_unscale.
+    // that the remainders meet times 2^-11), and Z comes out times 2^z_exponent.
     constexpr float kRepairScale = ANY_N1 ? 2048.0f : 1.0f;
-    float z_unscale = 1.0f;
+    int z_exponent = 0;
     constexpr int N1P = S::N1P, MB = S::MB, NCB = S::NCB, TPP = S::TPP, KSA = S::KSA, KSB = S::KSB;
     constexpr int CPRX = S::CPRX, LPT = S::LPT, NSX = S::NSX;
     static_assert(!ANY_N1 || (!PREPARED && N1 % 32 == 0), "rows padded to the MFMA block, R1 and R2 as they are");
@@ -182,8 +188,8 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
     const int off_gv = S::OFF_LO + TPP * sides * lo_bytes;
     const int side_mask = sides - 1;                         // 1: the two tiles alternate, 0: one tile
     const int off_red = off_gv + TPP * kRotqMaxSlots * 4;    // [2][TPP][4] floats
-    // what the row in the tile of a token slot was divided by, a power of two (1 nearly always)
-    float *row_scale = reinterpret_cast<float *>(lds + off_red + 32 * TPP);        // [2][TPP]
+    // exponent of the power of two that the row in the tile of a token slot was divided by (0 nearly always)
+    int *row_exponent = reinterpret_cast<int *>(lds + off_red + 32 * TPP);         // [2][TPP]
 
     const int groups = (T + TPP - 1) / TPP;
     // does this wave's token exist in group grp (the last group may be partial)?
@@ -269,24 +275,21 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
             v[u] = gs_tile[u] >= 0 ? gv[lane + 64 * u] : 0.f;
             top = fmaxf(top, fabsf(v[u]));
         }
-        float up = 1.0f;
+        int e = 0;
         if (__any(top > 65504.0f)) {
             // beyond fp16: the whole row is divided by a power of two, which moves nothing but the subnormals of a
             // row that large
-            const int e = min((int)(__float_as_uint(wave_max(top)) >> 23) - 127 - 14, 24);
-            up = __uint_as_float((uint32_t)(127 + e) << 23);
+            e = min((int)(__float_as_uint(wave_max(top)) >> 23) - 127 - 14, 24);
             const float down = __uint_as_float((uint32_t)(127 - e) << 23);
-            for (int c = lane; c < n1 * CPRX; c += 64) {
-                v8h *chunk16 = reinterpret_cast<v8h *>(xt + 16 * c);
-                v8h w = *chunk16;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) w[k] = (_Float16)((float)w[k] * down);
-                *chunk16 = w;
+            const v2h down2 = {(_Float16)down, (_Float16)down};
+            for (int c = lane; c < n1 * (N2 / 2); c += 64) {
+                v2h *pair = reinterpret_cast<v2h *>(xt + 4 * c);
+                *pair = *pair * down2;
             }
             __builtin_amdgcn_wave_barrier();
             v[0] *= down, v[1] *= down;
         }
-        if (lane == 0) row_scale[(side & 1) * TPP + tok_slot] = up;
+        if (lane == 0) row_exponent[(side & 1) * TPP + tok_slot] = e;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             if (gs_tile[u] >= 0) {
@@ -461,7 +464,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
                 *reinterpret_cast<uint4 *>(lds + S::OFF_X + tile * S::TILE_BYTES + (n1 * CPRX + r) * 16) = uint4{0, 0, 0, 0};
             }
         }
-        if (tid < 2 * TPP) row_scale[tid] = 1.0f;
+        if (tid < 2 * TPP) row_exponent[tid] = 0;
         for (int c = tid; c < TPP * sides * lo_bytes / 16; c += 256)
             *reinterpret_cast<uint4 *>(lds + S::OFF_LO + c * 16) = uint4{0, 0, 0, 0};
 
@@ -524,7 +527,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 #pragma unroll
             for (int e = 0; e < 8; ++e) large |= top[e] >= 0x4C00;       // 16.0
             if (!__any(large)) {
-                z_unscale = 1.0f / kRepairScale;
+                z_exponent = 11;
 #pragma unroll
                 for (int ks = 0; ks < KSA; ++ks) r2f[ks] *= (_Float16)kRepairScale;
             }
@@ -639,6 +642,8 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
 
         // ---- power-of-two prescale of this wave's columns so that hi/lo fit fp16 -------------
         // Stage B contracts over rows p within a column, so a per-wave factor commutes with it.
+        // (the exponent is read ahead of B2: behind it the owner of the row after next may write this one's place)
+        int exponent = row_exponent[par * TPP + tok_slot];
         float zmax = 0.f;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) zmax = max_abs16(accz[mb], zmax);
@@ -648,19 +653,18 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
         // smaller keep their bits.
         constexpr float kUnscaledFrom = ANY_N1 ? 16384.0f : 1.0f, kUnscaledTo = ANY_N1 ? 32768.0f : 16384.0f;
         constexpr int kTopExponent = ANY_N1 ? 14 : 13;
-        float fz_inv = 1.0f;
+        exponent = __builtin_amdgcn_readfirstlane(exponent) - (ANY_N1 ? z_exponent : 0);
         if (!(zmax >= kUnscaledFrom && zmax < kUnscaledTo) && zmax > 0.f) {
             const int ez = (int)((__float_as_uint(zmax) >> 23) & 0xFF) - 127;
             const int sh = max(-100, min(100, kTopExponent - ez));
             const float fz = __uint_as_float((uint32_t)(127 + sh) << 23);
-            fz_inv = __uint_as_float((uint32_t)(127 - sh) << 23);
+            exponent -= sh;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) accz[mb][e] *= fz;
         }
-        // (read ahead of B2: behind it the owner of the row after next may write this one's place)
-        const float z_scale = row_scale[par * TPP + tok_slot] * (ANY_N1 ? z_unscale : 1.0f);
+        const float fz_inv = __uint_as_float((uint32_t)(127 + exponent) << 23);       // Y = accy * fz_inv
 
         // ---- stage B: Y^T = Z^T R1, Z = hi + lo; the split of step ks+1 is issued between the
         // MFMAs of step ks -----------------------------------------------------------------
@@ -721,8 +725,6 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
             }
         }
 
-        fz_inv *= z_scale;                       // Y = accy * fz_inv
-
         // ---- per-token step: wave maximum now, token maximum after the barrier --------------
         float amax = 0.f;
         float *red = reinterpret_cast<float *>(lds + off_red) + (par * TPP + tok_slot) * 4;
@@ -752,6 +754,7 @@ __device__ __forceinline__ void rotate_quantize_mfma_body(
             for (int w = 1; w < NCB; ++w) amax = fmaxf(amax, red[w]);
             const float step = (amax == 0.f) ? 1.0f : amax / plan.q_div;      // q_div = 7: max|Y| / 7
             inv = fz_inv / step;               // codes = Y / step with Y = accy * fz_inv
+            if constexpr (CLIP) inv = wave_uniform(inv);     // (the four-row-block kernels spill fewer registers)
             if (live && cb == 0 && lane == 0) scales[t] = step;
         }
         if (!F16OUT && xrot != nullptr && live) {

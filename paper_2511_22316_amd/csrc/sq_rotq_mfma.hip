@@ -119,6 +119,18 @@ static sq_status launch_rotq_mfma_qs(const __half *X, int64_t ldx, int T, const 
         if (!force_reg && 2 * S2::lds_bytes((plan.n_qslots + 15) / 16, 1) <= 160 * 1024)
             return launch_rotq_mfma_ring<N1, N2, QS_MAX, 2, 2, true>(X, ldx, T, plan, R1, R2, Q, scales, xrot, st, prepared, xout, ldo);
     }
+    if constexpr (MB == 4) {
+        // One workgroup per CU either way.  From a row-major R1 the register form spills at the 512 registers there are, more or
+        // fewer with every change to the loop; the shared copy does not (fp16 output / clipped codes at P = 32, T = 2048,
+        // registers and LDS: 128 x 64 30.6 and 26.5 / 24.1 and 22.0 us, 112 x 128 51.3 and 45.1 / 46.9 and 42.4, 128 x 128
+        // 56.6 and 44.6 / 42.2 and 40.1).  Prepared fragments need fewer registers at the start and stay in them (128 x 64,
+        // P = 32, T = 16 7.9 and 7.6, T = 2048 20.2 and 20.4, T = 4096 35.2 and 36.9).  Lists on more than 96 columns leave no
+        // room for the copy beside rows of 128 x 128.
+        using S3 = RotqShape<N1, N2, 3, true>;
+        const bool force_reg = debug_option(SQ_DEBUG_ROTQ_R1_IN_REGISTERS) != 0;
+        if (prepared != 1 && !force_reg && S3::lds_bytes((plan.n_qslots + 15) / 16, 1) <= kMaxDynamicLds)
+            return launch_rotq_mfma_ring<N1, N2, QS_MAX, 3, 1, true>(X, ldx, T, plan, R1, R2, Q, scales, xrot, st, prepared, xout, ldo);
+    }
     return launch_rotq_mfma_ring<N1, N2, QS_MAX, 3, (MB <= 2) ? 2 : 1>(X, ldx, T, plan, R1, R2, Q, scales, xrot, st, prepared, xout, ldo);
 }
 

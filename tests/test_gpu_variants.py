@@ -573,3 +573,26 @@ def test_rotated_outliers_beyond_fp16_in_many_rows_and_in_one_launch(oracle):
     lay = Layer(Lb, 700, 32)
     want = lay.two_calls(X[:32])
     assert hit[:32].any() and bool(torch.isfinite(want).all()) and torch.equal(lay.one_launch(X[:32]), want)
+
+
+@pytest.mark.parametrize("n1,n2", [(108, 128), (112, 128), (128, 128), (128, 64)])
+@pytest.mark.parametrize("P", [0, 12, 64])
+def test_four_row_blocks_with_r1_in_lds_and_in_registers(oracle, n1, n2, P):
+    """R1, R2 as they are: the fragments of R1 lie in LDS or, with a list on nearly all columns, in registers, and behind
+    a prepared rotation in registers; the rows are the same bit for bit (run_rotate_quantize) and the oracle's."""
+    print(f"case four row blocks {n1}x{n2} P={P}", flush=True)
+    cfg = synth.LayerConfig(f"blocks_{n1}x{n2}", 530, n1, n2, 16, P, "normal", 2, 300.0, 0.01, 20.0, 0.02, 60 + n1)
+    L = synth.layer(cfg)
+    g = np.random.default_rng(n1 + P)
+    chans = np.unique([g.integers(0, n1) * n2 + c % n2 for c in range(2 * P)])
+    chans = g.permutation(chans)[: len(chans) // 2 * 2].astype(np.int32)
+    L = synth.Layer(cfg, L.X, chans[0::2].copy(), chans[1::2].copy(), g.uniform(-3.1, 3.1, len(chans) // 2).astype(np.float32),
+                    L.R1, L.R2, L.R1_f64, L.R2_f64)
+    rows = np.array([0, 1, 2, 255, 256, 529])
+    xo = oracle.rotate(L.X[rows], L.giv_i, L.giv_j, L.giv_theta, L.R1, L.R2)
+    Qg, sg, xg = run_rotate_quantize(L)
+    check_rotation(xg[rows], xo)
+    check_codes(Qg[rows], sg[rows], *oracle.quantize_rows(xo))
+    check_rotated_f16(run_rotate_fp16(L)[rows], oracle.rotate_f16(L.X[rows], L.giv_i, L.giv_j, L.giv_theta, L.R1, L.R2), xo)
+    Q3, s3, _ = run_variant(L, 4, 0.9)
+    check_variant_codes(Q3[rows], s3[rows], *oracle.quantize_rows_variant(xo, 4, 0.9), 4)
