@@ -11,7 +11,8 @@
 // B needs for its contraction over p, so Z never leaves the registers.  R2 and R1 are held in
 // registers as MFMA operands for the life of the workgroup, which walks over many tokens (for
 // three 32-row blocks the fragments of R1, which every wave needs alike, are kept once in LDS
-// instead, so that the registers allow a second workgroup on the CU).
+// instead, so that the registers allow a second workgroup on the CU; for four with a row-major R1
+// too, where the registers would not hold them without spills).
 //
 // Token rows stream from HBM straight into a ring of LDS tiles (global_load_lds): three tiles, two
 // rows ahead of the one being multiplied, with two workgroups per CU; or two tiles where that
