@@ -12,7 +12,7 @@ inline bool w4a4_fp6_takes(bool large, int T, int K, int N)
     return K % 256 == 0 && K >= 768 && K <= 65536 && T >= (large ? 256 : 128) && N >= 256;
 }
 
-// launch shapes of the kernel: 256 x 256 or 128 x 256 output tiles, eight waves
+// launch shapes of the kernel: 256 x 256 or 128 x 256 output tiles, four waves
 sq_status launch_w4a4_fp6(bool large, const uint8_t *Qx, const float *sx, int T, int K, const uint8_t *Qw,
                           const float *sw, int N, __half *Y, int64_t ldy, int32_t *acc_dbg, hipStream_t st);
 

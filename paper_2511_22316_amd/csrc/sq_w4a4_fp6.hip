@@ -12,16 +12,19 @@
 // taken beside it.  What the encoding buys over the codes times 16 as int8 is power: with the codes of Gaussian rows a
 // register-only loop on all CUs sustains 7.6 POP/s against 4.3 POP/s, both at the power limit of the chip.
 //
-// What bounds the kernel (int8 instruction / here, same launches in turn: T = 8192, K = 8192, N = 28672 1359 / 1018 us; T = 2048,
-// N = 4096, K = 4096 33.7 / 31.9 us, K = 11008 72.9 / 66.3 us) is its instruction stream: matrix cores 53 % busy with
-// 256 x 256 tiles, 68 % of a wave's life executing, 13 % waiting for an issue slot, 19 % in waits, one instruction per 6.0
-// cycles; with 128 x 256 tiles one per 4.7 - 5.0 cycles of a SIMD (two waves).  Widening a nibble operand takes 14
-// instructions per fragment and step, so a wave's tile is as large as the registers allow.  256 x 256 tile: four waves
-// of 128 x 128, one per SIMD (7 instructions of conversion per matrix instruction; eight waves of 64 x 128 take 11.5
-// and were 8 % slower).  128 x 256 tile, for fewer tokens or channels: two groups of four waves of 64 x 128 that take
-// half of every K tile each.  The conversion is done in registers, by every wave for itself: one that is shared
-// through LDS (24 bytes per 32 codes written once and read by all) moves 1.5 times the bytes out of LDS, writes them
-// at a quarter of the read rate, and was 10 - 15 % slower.
+// What bounds the kernel is its instruction stream, at the power limit.  Widening a nibble operand takes 14 instructions per
+// fragment and step of 64 codes, and a wave issues one instruction in four cycles (4.5 for the eight-byte forms used here),
+// so a wave's tile is as large as the registers allow: 128 x 128 (7 instructions of conversion per matrix instruction), one
+// wave per SIMD.  Built up in registers, per matrix instruction and SIMD: alone 17.3 ns (7.7 POP/s), with the conversion
+// 23.1, with the reads from LDS 26.5, with the barriers 27.1; this loop takes 32, the rest being the row sums (1) and the
+// global -> LDS requests (4; half of them left out: 3 - 5 % of the kernel).
+//   256 x 256 tile: four waves, a persistent walk over the output tiles.
+//   128 x 256 tile, for fewer tokens or channels: two K groups of two waves that take half of every K tile each.  (Two groups
+// of four waves of 64 x 128, two waves per SIMD, 10.5 instructions of conversion: a K tile of 256 codes takes 1.30 us, here
+// 1.05.  T = 2048, N = 4096, K = 4096 27.5 -> 25.3 us, K = 11008 59.9 -> 53.2; T = 333, K = 5120, N = 13824 28.5 -> 25.9.)
+// The conversion is done in registers, by every wave for itself: one that is shared through LDS (24 bytes per 32 codes
+// written once and read by all) moves 1.5 times the bytes out of LDS, writes them at a quarter of the read rate, and was
+// 10 - 15 % slower.  T = 8192, K = 8192, N = 28672: int8 instruction 1359 us, here 980.
 #include "sq_fp6_store.h"
 #include "sq_gemm_tile.h"
 #include "sq_w4a4_fp6.h"
@@ -162,14 +165,12 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
 {
     using G = Fp6Shape<WM, FM, FN, KG>;
     constexpr int WN = G::WN, BM = G::BM, BN = G::BN, NS = G::NS, NW = G::NW, BKB = G::BKB, STEPS = G::STEPS;
-    constexpr int NM = FM * FN, NF = FM + FN, FRAG_BYTES = 32 * BKB;
+    constexpr int NM = FM * FN, NF = FM + FN, FMO = FM / KG, FRAG_BYTES = 32 * BKB;
     constexpr int A_LOADS = BM / 8 / NW, B_LOADS = BN / 8 / NW, LOADS = A_LOADS + B_LOADS;
     constexpr int NSUM_A = FM / WN, NSUM = NSUM_A + FN / WM;          // fragments a wave sums
-    // Row sums: by the matrix cores where issue slots are short (one wave per SIMD: 7 % of the kernel), else eight codes
-    // per instruction on the vector ALU (the 16 accumulators more do not fit beside two waves per SIMD).
-    constexpr bool SUM_MFMA = KG == 1;
     static_assert(FM % WN == 0 && FN % WM == 0, "the waves that share a row block share its sums");
-    static_assert(KG == 1 || (KG == 2 && FM == 2), "each of two K groups finishes one row of fragments");
+    static_assert(KG == 1 || (KG == 2 && FM % 2 == 0), "each of two K groups finishes half of the rows of fragments");
+    static_assert(NW == 4, "one wave per SIMD: issue slots are short, registers are not");
     extern __shared__ uint4 smem[];
     char *lds = reinterpret_cast<char *>(smem);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)smem;
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     const uint32_t dma_off = (uint32_t)(lane >> 3) * Kb + ((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7)) * 16;
     static_assert(NW % 2 == 0, "the swizzle is the same for all loads of a wave");
     // (one workgroup of four waves per CU issues too few instructions to spend scalar ones on addresses: offsets kept)
-    constexpr int KEPT = KG == 1 ? (A_LOADS > B_LOADS ? A_LOADS : B_LOADS) : 1;
+    constexpr int KEPT = A_LOADS > B_LOADS ? A_LOADS : B_LOADS;
     uint32_t load_off[KEPT];
 #pragma unroll
     for (int g = 0; g < KEPT; ++g) load_off[g] = dma_off + (uint32_t)(g * 8 * NW) * Kb;
@@ -216,24 +217,18 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     auto issue_one = [&](int idx) {
         const uint8_t *base = idx < A_LOADS ? a_next : b_next;
         const int g = idx < A_LOADS ? idx : idx - A_LOADS;
-        if constexpr (KEPT > 1) dma_16<NW * 1024>(base, load_off[g % KEPT]);
-        else dma_16<NW * 1024>(base + (int64_t)(g * 8 * NW) * Kb, load_off[0]);
+        dma_16<NW * 1024>(base, load_off[g]);
     };
     auto start_requests = [&](int stage) { dma_begin(lds_base + (uint32_t)stage * G::STAGE + wave * 1024); };
     auto end_requests = [&]() {
         a_next += BKB;
         b_next += BKB;
     };
-    // Past the last output tile of this workgroup its last one is requested again, into dead stages: the count of
-    // outstanding loads stays constant.
+    // A walk over output tiles: past the last one of this workgroup that one is requested again, into dead stages, so
+    // that the count of outstanding loads stays constant.
     auto next_tile = [&]() {
-        if constexpr (KG == 2) {
-            a_next -= ktiles * BKB;
-            b_next -= ktiles * BKB;
-        } else {
-            if (req_tile + (int)gridDim.x < tiles) req_tile += gridDim.x;
-            open_tile();
-        }
+        if (req_tile + (int)gridDim.x < tiles) req_tile += gridDim.x;
+        open_tile();
     };
 
     // Fragment c (0 .. FM - 1: tokens, then the weights) of this wave is row block c ^ wn of its tokens, block
@@ -242,18 +237,18 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     // Byte offset in LDS: the lane's part (row, and chunk fhalf of the first step of this K group; a later step flips
     // bits of the chunk number above that one, which the swizzle passes through) plus a wave-uniform part.
     const int lane_off = lds_chunk_slot<BKB>(frow, 2 * kg * STEPS + fhalf) * 16;
+    auto token_block = [&](int c) { return c ^ wn ^ (kg * FMO); };
     auto part = [&](int c) {
-        return c < FM ? (wm * FM + (c ^ wn)) * FRAG_BYTES : G::A_BYTES + (wn * FN + ((c - FM) ^ wm)) * FRAG_BYTES;
+        return c < FM ? (wm * FM + token_block(c)) * FRAG_BYTES : G::A_BYTES + (wn * FN + ((c - FM) ^ wm)) * FRAG_BYTES;
     };
     const FieldMasks masks = field_masks();
 
     v16f acc[FM][FN];
-    constexpr int RB = KG == 1 ? 4 : NF;  // chunks on their way from LDS
+    constexpr int RB = 4;                // chunks on their way from LDS
     static_assert(NF % RB == 0, "a chunk keeps its place from step to step");
     uint4 raw[RB];
     v6i frag[2][NF];
-    int sum[NSUM], sum_out[NSUM];        // sums of the codes (this lane's half of the row)
-    v4f sum_acc[NSUM];                   // or, SUM_MFMA, of the codes + 8, divided by 8
+    v4f sum_acc[NSUM];                   // sums of the codes + 8, divided by 8
     const v6i sum_sel = sum_selector(lane);
     auto read_chunk = [&](int stage_byte, int s, int c) {
         raw[c % RB] = *reinterpret_cast<const uint4 *>(lds + ((lane_off ^ (32 * s)) + (stage_byte + part(c))));
@@ -266,8 +261,6 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         int d0, d1, d2;
         to_fp6(w0, w1, masks, d0, d1, d2);
         frag[set][c][3 * h] = d0, frag[set][c][3 * h + 1] = d1, frag[set][c][3 * h + 2] = d2;
-        const int u = sum_slot(c);
-        if (!SUM_MFMA && u >= 0) sum[u] = __builtin_amdgcn_sdot8((int)w1, 0x11111111, __builtin_amdgcn_sdot8((int)w0, 0x11111111, sum[u], false), false);
     };
     auto clear = [&]() {
 #pragma unroll
@@ -283,57 +276,61 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     // One step of 64 codes, written in the order it should issue: every MFMA on frag[C] is followed by its share of
     // the conversion of raw (the next step, at N_BYTE, N_STEP) into frag[1 - C], and the place of a converted chunk is
     // refilled RB chunks ahead, in that step or the one behind it (A_BYTE, A_STEP).  LOAD0 .. LOAD1: the loads of a K
-    // tile this step issues, from MFMA M0 on.  TURN: the turn between two K tiles, ahead of the first read of the next.
-#define SQ_FP6_STEP(C, N_BYTE, N_STEP, A_BYTE, A_STEP, M0, LOAD0, LOAD1, TURN)                                      \
+    // tile this step issues, from MFMA M0 on.  TURN: the turn between two K tiles, ahead of the first read of the next (the
+    // K tiles that may still be on their way), or -1.  CONVERT, AHEAD: whether there is a next step, and one behind it.
+    // (The row sums' instruction waits for the matrix core behind an MFMA: 256 x 256 tiles 0 - 1.5 % faster with it at the
+    // end of a slot, 128 x 256 tiles 1 % slower.)
+#define SQ_FP6_STEP(C, N_BYTE, N_STEP, A_BYTE, A_STEP, M0, LOAD0, LOAD1, TURN, CONVERT, AHEAD)                      \
     do {                                                                                                            \
         _Pragma("unroll") for (int m = 0; m < NM; ++m) {                                                            \
             const int j = m / FM, i = m % FM;                                                                       \
-            if ((TURN) && m == (M0)) SQ_FP6_TURN();                                                                 \
+            if ((TURN) >= 0 && m == (M0)) SQ_FP6_TURN(TURN);                                                        \
             acc[i][j] = mfma_fp6(frag[C][FM + j], frag[C][i], acc[i][j]);                                           \
-            if (SUM_MFMA && m % (NM / NF) == 1 % (NM / NF)) {                                                       \
+            if (KG == 2 && m % (NM / NF) == 1 % (NM / NF)) {                                                        \
                 const int c = m / (NM / NF), u = sum_slot(c);                                                       \
                 if (u >= 0) mfma_fp6_16(frag[C][c], sum_sel, sum_acc[u]);                                           \
             }                                                                                                       \
-            _Pragma("unroll") for (int h = m * 2 * NF / NM; h < (m + 1) * 2 * NF / NM; ++h) {                       \
+            _Pragma("unroll") for (int h = m * 2 * NF / NM; (CONVERT) && h < (m + 1) * 2 * NF / NM; ++h) {          \
                 convert_half(1 - (C), h >> 1, h & 1);                                                               \
                 if (h & 1) {                                                                                        \
                     const int t = (h >> 1) + RB;                                                                    \
                     if (t < NF) read_chunk(N_BYTE, N_STEP, t);                                                      \
-                    else read_chunk(A_BYTE, A_STEP, t - NF);                                                        \
+                    else if (AHEAD) read_chunk(A_BYTE, A_STEP, t - NF);                                             \
                 }                                                                                                   \
             }                                                                                                       \
             _Pragma("unroll") for (int q = (LOAD0); q < (LOAD1); ++q)                                               \
                 if (m == (M0) + (q - (LOAD0)) * (NM - (M0)) / ((LOAD1) > (LOAD0) ? (LOAD1) - (LOAD0) : 1)) issue_one(q);   \
+            if (KG == 1) __builtin_amdgcn_sched_barrier(0);                                                         \
+            if (KG == 1 && m % (NM / NF) == 1 % (NM / NF)) {                                                        \
+                const int c = m / (NM / NF), u = sum_slot(c);                                                       \
+                if (u >= 0) mfma_fp6_16(frag[C][c], sum_sel, sum_acc[u]);                                           \
+            }                                                                                                       \
             __builtin_amdgcn_sched_barrier(0);                                                                      \
         }                                                                                                           \
     } while (0)
-    // Between K tiles.  Loads complete in order: the next K tile has landed once only the NS - 2 behind it are
+    // Between K tiles.  Loads complete in order: the next K tile has landed once only the LATER behind it are
     // outstanding.  All reads of this one have been issued and are drained here: its stage takes the one NS ahead.
-#define SQ_FP6_TURN()                                                                                               \
+#define SQ_FP6_TURN(LATER)                                                                                          \
     do {                                                                                                            \
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * LOADS) : "memory");             \
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((LATER) * LOADS) : "memory");              \
         start_requests(cur);                                                                                        \
     } while (0)
-    // One K tile.  The conversion runs ahead of the MFMAs: the last step converts the first step of the next K tile, so
-    // behind the last K tile (LAST) sums taken beside it are put aside first.
-#define SQ_FP6_TILE(LAST)                                                                                           \
+    // One K tile.  The conversion runs ahead of the MFMAs: the last step converts the first step of the next K tile,
+    // and stops behind the last one of the workgroup (LAST, two K groups).
+    // LATER: K tiles requested beyond the next one; REQUEST: this K tile's turn requests another one.
+#define SQ_FP6_TILE(LAST, LATER, REQUEST)                                                                           \
     do {                                                                                                            \
         const int next = cur + 1 == NS ? 0 : cur + 1;                                                               \
         const int cb = cur * G::STAGE, nb = next * G::STAGE;                                                        \
+        constexpr int TURN_AT = 2 * (NF - RB) + 1, FIRST = STEPS == 4 ? LOADS / 4 : LOADS / 6;                      \
+        constexpr bool END = KG == 2 && (LAST);                                                                     \
         if constexpr (STEPS == 4) {                                                                                 \
-            constexpr int TURN_AT = 2 * (NF - RB) + 1;                                                              \
-            SQ_FP6_STEP(0, cb, 1 % STEPS, cb, 2 % STEPS, 0, 0, 0, false);                                           \
-            SQ_FP6_STEP(1, cb, 2 % STEPS, cb, 3 % STEPS, 0, 0, 0, false);                                           \
-            SQ_FP6_STEP(0, cb, 3 % STEPS, nb, 0, TURN_AT, 0, LOADS / 4, true);                                      \
-            SQ_FP6_STEP(1, nb, 0, nb, 1, 0, LOADS / 4, LOADS, false);                                               \
-        } else {                                                                                                    \
-            SQ_FP6_STEP(0, cb, 1, nb, 0, 0, 0, LOADS / 2, true);                                                    \
-            if (LAST && !SUM_MFMA) {                                                                                \
-                _Pragma("unroll") for (int c = 0; c < NSUM; ++c) sum_out[c] = sum[c], sum[c] = 0;                   \
-            }                                                                                                       \
-            SQ_FP6_STEP(1, nb, 0, nb, 1, 0, LOADS / 2, LOADS, false);                                               \
+            SQ_FP6_STEP(0, cb, 1 % STEPS, cb, 2 % STEPS, 0, 0, 0, -1, true, true);                                  \
+            SQ_FP6_STEP(1, cb, 2 % STEPS, cb, 3 % STEPS, 0, 0, 0, -1, true, true);                                  \
         }                                                                                                           \
-        end_requests();                                                                                             \
+        SQ_FP6_STEP(0, cb, STEPS - 1, nb, 0, TURN_AT, 0, (REQUEST) ? FIRST : 0, END ? -1 : (LATER), true, !END);    \
+        SQ_FP6_STEP(1, nb, 0, nb, 1, 0, (REQUEST) ? FIRST : 0, (REQUEST) ? LOADS : 0, -1, !END, true);              \
+        if (REQUEST) end_requests();                                                                                \
         cur = next;                                                                                                 \
     } while (0)
 
@@ -345,8 +342,6 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         for (int q = 0; q < LOADS; ++q) issue_one(q);
         end_requests();
     }
-#pragma unroll
-    for (int c = 0; c < NSUM; ++c) sum[c] = 0;
     wait_vmcnt<(NS - 1) * LOADS>();
     block_barrier();
 #pragma unroll
@@ -362,11 +357,18 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     int cur = 0, parity = 0;     // ring stage of the K tile being multiplied; set of dequantization steps
     for (int tile = blockIdx.x;;) {
         clear();
-        for (int kt = NS; kt < ktiles; ++kt) SQ_FP6_TILE(false);
-        next_tile();
+        for (int kt = NS; kt < ktiles; ++kt) SQ_FP6_TILE(false, NS - 2, true);
+        if constexpr (KG == 1) {
+            next_tile();
 #pragma unroll
-        for (int u = 1; u < NS; ++u) SQ_FP6_TILE(false);
-        SQ_FP6_TILE(true);
+            for (int u = 1; u < NS; ++u) SQ_FP6_TILE(false, NS - 2, true);
+            SQ_FP6_TILE(true, NS - 2, true);
+        } else {                  // one output tile: nothing is requested behind it
+            static_assert(KG == 1 || NS == 3, "two K tiles are left");
+            SQ_FP6_TILE(false, 1, false);
+            SQ_FP6_TILE(false, 0, false);
+            SQ_FP6_TILE(true, 0, false);
+        }
 
         // ---- epilogue.  The row sums meet in LDS, then every lane stores runs of eight channels of its token row
         // straight from registers.  The weights are the first MFMA operand: the 32 x 32 accumulator has the token in
@@ -376,130 +378,145 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         int el = lane;
         asm volatile("" : "+v"(el));
         const int frow = el & 31, fhalf = el >> 5;
-        int *sums = reinterpret_cast<int *>(lds + G::SUM_BYTE);
+        float *sums = reinterpret_cast<float *>(lds + G::SUM_BYTE);
         const float *steps = reinterpret_cast<const float *>(lds + G::SCALE_BYTE) + parity * (BM + BN);
         typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-        if constexpr (SUM_MFMA) {                 // the results of the last matrix instructions: seven passes at most
+        // the results of the last matrix instructions: seven passes at most
 #pragma unroll
-            for (int u = 0; u < NSUM; ++u) asm volatile("s_nop 15" : "+v"(sum_acc[u]));
-        }
+        for (int u = 0; u < NSUM; ++u) asm volatile("s_nop 15" : "+v"(sum_acc[u]));
+        // In LDS a row's share of the correction, a whole number: -8 sum b of a channel (its codes are 8 less than the fields)
+        // and -8 sum a - 64 K of a token.
 #pragma unroll
         for (int c = 0; c < NF; ++c) {
             const int u = sum_slot(c);
             if (u < 0) continue;
-            const int row = c < FM ? (wm * FM + (c ^ wn)) * 32 : BM + (wn * FN + ((c - FM) ^ wm)) * 32;
-            if constexpr (SUM_MFMA) {
-                // accumulator of the 16 x 16 instruction: column l % 16, rows 4 (l / 16) + register; columns 0 and 1
-                // hold the sums of rows 0 .. 15 and 16 .. 31 of the block
-                if ((el & 15) < 2)
-                    *reinterpret_cast<int4 *>(sums + row + 16 * (el & 15) + 4 * (el >> 4)) =
-                        int4{(int)(8.f * sum_acc[u][0]) - 16 * Kb, (int)(8.f * sum_acc[u][1]) - 16 * Kb,
-                             (int)(8.f * sum_acc[u][2]) - 16 * Kb, (int)(8.f * sum_acc[u][3]) - 16 * Kb};
-            } else {
-                const v2u both = __builtin_amdgcn_permlane32_swap(sum_out[u], sum_out[u], false, false);
-                if (fhalf == 0) sums[kg * (BM + BN) + row + frow] = (int)(both[0] + both[1]);
+            const int row = c < FM ? (wm * FM + token_block(c)) * 32 : BM + (wn * FN + ((c - FM) ^ wm)) * 32;
+            const float codes8 = c < FM ? 0.f : (float)(128 / KG * Kb);      // 64 times the codes of this K group
+            // accumulator of the 16 x 16 instruction: column l % 16, rows 4 (l / 16) + register; columns 0 and 1
+            // hold the sums of rows 0 .. 15 and 16 .. 31 of the block
+            if ((el & 15) < 2)
+                *reinterpret_cast<float4 *>(sums + kg * (BM + BN) + row + 16 * (el & 15) + 4 * (el >> 4)) =
+                    float4{fmaf(-64.f, sum_acc[u][0], codes8), fmaf(-64.f, sum_acc[u][1], codes8),
+                           fmaf(-64.f, sum_acc[u][2], codes8), fmaf(-64.f, sum_acc[u][3], codes8)};
+        }
+        block_barrier();
+        // The correction is c + t for channel c and token t: one matrix instruction of rank four per fragment adds it, in place of
+        // two additions per entry.  A number below 2^23 is 4096 hi + lo, both whole and exact in fp16; the sums stay
+        // multiples of 1/64 below 2^18, exact in fp32 in any order.
+        auto halves = [&](int row) {
+            const float x = KG == 2 ? sums[row] + sums[BM + BN + row] : sums[row], hi = rintf(x * (1.f / 4096.f));
+            const uint32_t d = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(hi, fmaf(-4096.f, hi, x)));
+            return fhalf == 0 ? d : 0u;
+        };
+        const uint32_t ones = fhalf == 0 ? 0x24005400u : 0u;         // 4096 / 64 and 1 / 64
+        uint32_t token_halves[FMO];
+#pragma unroll
+        for (int i = 0; i < FMO; ++i) token_halves[i] = halves((wm * FM + token_block(i)) * 32 + frow);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const v4i channels = {(int)halves(BM + (wn * FN + (j ^ wm)) * 32 + frow), (int)ones, 0, 0};
+#pragma unroll
+            for (int i = 0; i < FMO; ++i) {
+                const v4i tokens = {(int)ones, (int)token_halves[i], 0, 0};
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, channels), __builtin_bit_cast(v8h, tokens),
+                                                                   acc[i][j], 0, 0, 0);
             }
         }
+        // A wave finishes its first FMO fragment rows, with the other K group's share of the sums (its last ones), which
+        // comes through the ring (dead: one output tile per workgroup).
+        float4 *part = reinterpret_cast<float4 *>(lds) + (wave % (WM * WN)) * (FMO * FN * 4 * kWave) + el;
+        constexpr int HALF = WM * WN * FMO * FN * 4 * kWave;
         if constexpr (KG == 2) {
-            // each group of waves adds the other's share of the fragment row it finishes (i = kg); the ring is dead
-            // (one output tile per workgroup)
-            wait_vmcnt<0>();
-            block_barrier();
-            float4 *part = reinterpret_cast<float4 *>(lds) + (wave % (WM * WN)) * (FN * 4 * kWave) + el;
-            constexpr int HALF = WM * WN * FN * 4 * kWave;
-            const int mine = kg * HALF, other = (1 - kg) * HALF;
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v16f &x = kg == 0 ? acc[1][j] : acc[0][j];
-                    part[mine + (j * 4 + q) * kWave] = float4{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
-                }
+                for (int i = 0; i < FMO; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const v16f &x = acc[FMO + i][j];
+                        part[kg * HALF + ((j * FMO + i) * 4 + q) * kWave] = float4{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
+                    }
             block_barrier();
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 p = part[other + (j * 4 + q) * kWave];
-                    const float d[4] = {p.x, p.y, p.z, p.w};
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[0][j][4 * q + r] = (kg == 0 ? acc[0][j][4 * q + r] : acc[1][j][4 * q + r]) + d[r];
-                }
-        } else {
-            block_barrier();
+            part += (1 - kg) * HALF;
         }
         int row0, col0;
         origin(tile, row0, col0);
         const bool vector_stores = fp6_vector_stores(rows_aligned != 0, col0);
-        auto sum_of = [&](int r) { return KG == 2 ? sums[r] + sums[BM + BN + r] : sums[r]; };
-        constexpr int FMO = KG == 2 ? 1 : FM;             // fragment rows this wave finishes
-        float sxt[FMO], sat[FMO];
+        float sxt[FMO];
         __half *ydst[FMO];
 #pragma unroll
         for (int i = 0; i < FMO; ++i) {
-            const int tl = (wm * FM + ((KG == 2 ? kg : i) ^ wn)) * 32 + frow;
-            sxt[i] = steps[tl];
-            sat[i] = (float)(-8 * sum_of(tl) - 128 * Kb);                     // - 64 K
-            ydst[i] = Y + (int64_t)(row0 + tl) * ldy + col0 + wn * (FN * 32) + 8 * fhalf;
+            const int tl = (wm * FM + token_block(i)) * 32 + frow;
+            sxt[i] = 64.f * steps[tl];
+            ydst[i] = Y + (int64_t)(row0 + tl) * ldy + col0 + wn * (FN * 32) + 8 * fhalf + (vector_stores && (el & 16) ? 16 - 16 * ldy : 0);
         }
+        // PLAIN: 16-byte stores and no accumulators asked for: no branch, so that the reads from LDS run ahead
+        auto finish = [&](auto plain) {
+            constexpr bool PLAIN = decltype(plain)::value;
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            const int nj = (j ^ wm) * 32;                 // first channel of the fragment within this wave's
-            float swn[16], sbn[16];
+            for (int j = 0; j < FN; ++j) {
+                const int nj = (j ^ wm) * 32;                 // first channel of the fragment within this wave's
+                float swn[16];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n4 = BM + wn * (FN * 32) + nj + 8 * q + 4 * fhalf;
-                const float4 s4 = *reinterpret_cast<const float4 *>(steps + n4);
-                int4 c4 = *reinterpret_cast<const int4 *>(sums + n4);
-                if constexpr (KG == 2) {
-                    const int4 d4 = *reinterpret_cast<const int4 *>(sums + BM + BN + n4);
-                    c4.x += d4.x, c4.y += d4.y, c4.z += d4.z, c4.w += d4.w;
+                for (int q = 0; q < 4; ++q) {
+                    const int n4 = BM + wn * (FN * 32) + nj + 8 * q + 4 * fhalf;
+                    const float4 s4 = *reinterpret_cast<const float4 *>(steps + n4);
+                    swn[4 * q] = s4.x, swn[4 * q + 1] = s4.y, swn[4 * q + 2] = s4.z, swn[4 * q + 3] = s4.w;
                 }
-                swn[4 * q] = s4.x, swn[4 * q + 1] = s4.y, swn[4 * q + 2] = s4.z, swn[4 * q + 3] = s4.w;
-                sbn[4 * q] = (float)(-8 * c4.x), sbn[4 * q + 1] = (float)(-8 * c4.y);
-                sbn[4 * q + 2] = (float)(-8 * c4.z), sbn[4 * q + 3] = (float)(-8 * c4.w);
-            }
-#pragma unroll
-            for (int i = 0; i < FMO; ++i) {
-                uint4 w[2];                               // channels nj + 16 h + 8 fhalf ..
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    uint32_t run[2][2];
-#pragma unroll
-                    for (int e = 8 * h; e < 8 * h + 8; e += 2) {
-                        // whole numbers below 2^24 throughout: exact
-                        const float a0 = fmaf(64.f, acc[i][j][e], sbn[e]) + sat[i];
-                        const float a1 = fmaf(64.f, acc[i][j][e + 1], sbn[e + 1]) + sat[i];
-                        run[(e / 4) & 1][(e / 2) & 1] = scaled_pair(a0 * sxt[i], swn[e], a1 * sxt[i], swn[e + 1]);
-                    }
-                    // lower half-wave: both halves of the first run; upper half-wave: of the second
-                    const v2u s0 = __builtin_amdgcn_permlane32_swap(run[0][0], run[1][0], false, false);
-                    const v2u s1 = __builtin_amdgcn_permlane32_swap(run[0][1], run[1][1], false, false);
-                    w[h] = uint4{s0[0], s1[0], s0[1], s1[1]};
-                }
-                if (vector_stores) {
-                    *reinterpret_cast<uint4 *>(ydst[i] + nj) = w[0];
-                    *reinterpret_cast<uint4 *>(ydst[i] + nj + 16) = w[1];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {           // register-only: no addressable copy of the chunks
-                        const uint32_t d[8] = {w[0].x, w[0].y, w[0].z, w[0].w, w[1].x, w[1].y, w[1].z, w[1].w};
-                        reinterpret_cast<uint16_t *>(ydst[i] + nj + 8 * (e / 8))[e] = (uint16_t)(d[e >> 1] >> (16 * (e & 1)));
-                    }
-                }
-            }
-            if (acc_dbg != nullptr) {
 #pragma unroll
                 for (int i = 0; i < FMO; ++i) {
-                    const int t = row0 + (wm * FM + ((KG == 2 ? kg : i) ^ wn)) * 32 + frow;
+                    v16f x = acc[i][j];
+                    if constexpr (KG == 2) {
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int n = col0 + wn * (FN * 32) + nj + 8 * (e / 4) + 4 * fhalf + (e % 4);
-                        acc_dbg[(int64_t)t * N + n] = (int)(fmaf(64.f, acc[i][j][e], sbn[e]) + sat[i]);
+                        for (int q = 0; q < 4; ++q) {
+                            const float4 p = part[((j * FMO + i) * 4 + q) * kWave];
+                            x[4 * q] += p.x, x[4 * q + 1] += p.y, x[4 * q + 2] += p.z, x[4 * q + 3] += p.w;
+                        }
+                    }
+                    uint4 w[2];                               // channels nj + 16 h + 8 fhalf ..
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        uint32_t run[2][2];
+#pragma unroll
+                        for (int e = 8 * h; e < 8 * h + 8; e += 2) {
+                            run[(e / 4) & 1][(e / 2) & 1] = scaled_pair(x[e] * sxt[i], swn[e], x[e + 1] * sxt[i], swn[e + 1]);
+                        }
+                        // lower half-wave: both halves of the first run; upper half-wave: of the second
+                        const v2u s0 = __builtin_amdgcn_permlane32_swap(run[0][0], run[1][0], false, false);
+                        const v2u s1 = __builtin_amdgcn_permlane32_swap(run[0][1], run[1][1], false, false);
+                        w[h] = uint4{s0[0], s1[0], s0[1], s1[1]};
+                    }
+                    if (PLAIN || vector_stores) {
+                        // sixteen rows of 64 bytes a store: rows l % 16, then the other sixteen (ydst is the lane's place)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            uint32_t &x0 = reinterpret_cast<uint32_t *>(&w[0])[r], &x1 = reinterpret_cast<uint32_t *>(&w[1])[r];
+                            const v2u sw16 = __builtin_amdgcn_permlane16_swap(x0, x1, false, false);
+                            x0 = sw16[0], x1 = sw16[1];
+                        }
+                        *reinterpret_cast<uint4 *>(ydst[i] + nj) = w[0];
+                        *reinterpret_cast<uint4 *>(ydst[i] + 16 * ldy + nj) = w[1];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {           // register-only: no addressable copy of the chunks
+                            const uint32_t d[8] = {w[0].x, w[0].y, w[0].z, w[0].w, w[1].x, w[1].y, w[1].z, w[1].w};
+                            reinterpret_cast<uint16_t *>(ydst[i] + nj + 8 * (e / 8))[e] = (uint16_t)(d[e >> 1] >> (16 * (e & 1)));
+                        }
+                    }
+                    if (!PLAIN && acc_dbg != nullptr) {
+                        const int t = row0 + (wm * FM + token_block(i)) * 32 + frow;
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int n = col0 + wn * (FN * 32) + nj + 8 * (e / 4) + 4 * fhalf + (e % 4);
+                            acc_dbg[(int64_t)t * N + n] = (int)(64.f * x[e]);
+                        }
                     }
                 }
             }
-        }
+        };
+        if constexpr (KG == 1) finish(std::false_type{});
+        else if (vector_stores && acc_dbg == nullptr) finish(std::true_type{});
+        else finish(std::false_type{});
         if (KG == 2 || tile + (int)gridDim.x >= tiles) break;
         tile += gridDim.x;
         parity ^= 1;
@@ -534,7 +551,7 @@ sq_status launch_w4a4_fp6(bool large, const uint8_t *Qx, const float *sx, int T,
 {
     if (!w4a4_fp6_takes(large, T, K, N)) return SQ_ERR_SHAPE;
     return large ? launch<2, 4, 4, 1>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st)
-                 : launch<2, 2, 4, 2>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
+                 : launch<1, 4, 4, 2>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
 }
 
 }  // namespace sq

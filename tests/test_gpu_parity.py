@@ -454,6 +454,31 @@ def test_gemm_six_bit_float_kernel_rounds_like_the_others(case, other):
     assert np.array_equal(Y[0].view(np.uint16), Y[1].view(np.uint16))
 
 
+@pytest.mark.parametrize("case,T,K,N,pad", [(18, 128, 768, 256, 0), (18, 200, 1280, 520, 0), (18, 129, 1024, 264, 8), (18, 128, 65536, 256, 0),
+                                            (19, 256, 768, 256, 0), (19, 300, 1024, 520, 0), (19, 4100, 768, 4504, 8)])
+def test_gemm_six_bit_float_kernel_without_accumulators(case, T, K, N, pad):
+    """The epilogue has a form without branches for calls that do not ask for the accumulators: the same fp16 outputs, bit
+    for bit, on sums of every size the corrections can take (random codes; all codes 7 against random ones; all -8)."""
+    print(f"case gemm six-bit plain epilogue {case} T={T} K={K} N={N}", flush=True)
+    import torch
+    import paper_2511_22316_amd as sq
+    g = np.random.default_rng(case + T)
+    sx, sw = dev(g.uniform(0.05, 4.0, T).astype(np.float32)), dev(g.uniform(1e-6, 5e-5, N).astype(np.float32))
+    random = [synth.random_codes(T, K, 51), synth.random_codes(N, K, 52)]
+    full = lambda rows, byte: np.full((rows, K // 2), byte, np.uint8)     # noqa: E731
+    for Qx, Qw in [random, [full(T, 0x77), random[1]], [random[0], full(N, 0x88)], [full(T, 0x88), full(N, 0x88)]]:
+        Y = [torch.full((T, N + pad), -77.0, dtype=torch.float16, device="cuda") for _ in range(2)]
+        acc = torch.empty((T, N), dtype=torch.int32, device="cuda")
+        sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, case + 1)
+        try:
+            sq.sq_w4a4_gemm(dev(Qx), sx, dev(Qw), sw, Y[0][:, :N], acc)
+            sq.sq_w4a4_gemm(dev(Qx), sx, dev(Qw), sw, Y[1][:, :N])
+            torch.cuda.synchronize()
+        finally:
+            sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, 0)
+        assert np.array_equal(host(Y[0]).view(np.uint16), host(Y[1]).view(np.uint16))
+
+
 def test_gemm_seeded_random_shapes_bit_exact(oracle):
     """Thirty shapes drawn from a seed (T up to 700, K a multiple of 32 up to 2304, N up to 3000, a
     third of them with at most 64 tokens): whatever kernel and launch shape the dispatcher picks,
