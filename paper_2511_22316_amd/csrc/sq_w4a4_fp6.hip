@@ -22,6 +22,9 @@
 //   128 x 256 tile, for fewer tokens or channels: two K groups of two waves that take half of every K tile each.  (Two groups
 // of four waves of 64 x 128, two waves per SIMD, 10.5 instructions of conversion: a K tile of 256 codes takes 1.30 us, here
 // 1.05.  T = 2048, N = 4096, K = 4096 27.5 -> 25.3 us, K = 11008 59.9 -> 53.2; T = 333, K = 5120, N = 13824 28.5 -> 25.9.)
+//   128 x 192 and 256 x 192 tiles (waves of 128 x 96, 8.2 instructions of conversion): a K tile takes 0.86 and 0.85 of the time of
+// the wider ones, so they pay where they fill the CUs better (T = 333, K = 5120, N = 13824, 216 or 162 tiles: 25.9 -> 23.5 us;
+// T = 1001, K = 3072, N = 9216, 192 or 144 tiles: 29.3 -> 26.2).
 // The conversion is done in registers, by every wave for itself: one that is shared through LDS (24 bytes per 32 codes
 // written once and read by all) moves 1.5 times the bytes out of LDS, writes them at a quarter of the read rate, and was
 // 10 - 15 % slower.  T = 8192, K = 8192, N = 28672: int8 instruction 1359 us, here 980.
@@ -167,8 +170,10 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     constexpr int WN = G::WN, BM = G::BM, BN = G::BN, NS = G::NS, NW = G::NW, BKB = G::BKB, STEPS = G::STEPS;
     constexpr int NM = FM * FN, NF = FM + FN, FMO = FM / KG, FRAG_BYTES = 32 * BKB;
     constexpr int A_LOADS = BM / 8 / NW, B_LOADS = BN / 8 / NW, LOADS = A_LOADS + B_LOADS;
-    constexpr int NSUM_A = FM / WN, NSUM = NSUM_A + FN / WM;          // fragments a wave sums
-    static_assert(FM % WN == 0 && FN % WM == 0, "the waves that share a row block share its sums");
+    // the waves that share a row block share its sums, if its blocks are so many
+    constexpr int SHARE_B = FN % WM == 0 ? WM : 1;
+    constexpr int NSUM_A = FM / WN, NSUM = NSUM_A + FN / SHARE_B;     // fragments a wave sums
+    static_assert(FM % WN == 0, "the waves that share a row block share its sums");
     static_assert(KG == 1 || (KG == 2 && FM % 2 == 0), "each of two K groups finishes half of the rows of fragments");
     static_assert(NW == 4, "one wave per SIMD: issue slots are short, registers are not");
     extern __shared__ uint4 smem[];
@@ -208,7 +213,6 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         a_next = Qx + (int64_t)(row0 + 8 * wave) * Kb;
         b_next = Qw + (int64_t)(col0 + 8 * wave) * Kb;
         dma_begin(lds_base + G::SCALE_BYTE + req_parity * ((BM + BN) * 4) + wave * 256);
-#pragma unroll
         for (int p = wave * kWave; p < BM + BN; p += NW * kWave)
             dma_4<NW * 256>(p < BM ? sx + row0 + p : sw + col0 + p - BM, lane * 4);
         req_parity ^= 1;
@@ -238,13 +242,14 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     // bits of the chunk number above that one, which the swizzle passes through) plus a wave-uniform part.
     const int lane_off = lds_chunk_slot<BKB>(frow, 2 * kg * STEPS + fhalf) * 16;
     auto token_block = [&](int c) { return c ^ wn ^ (kg * FMO); };
+    auto channel_block = [&](int j) { return SHARE_B == 1 ? j : j ^ wm; };
     auto part = [&](int c) {
-        return c < FM ? (wm * FM + token_block(c)) * FRAG_BYTES : G::A_BYTES + (wn * FN + ((c - FM) ^ wm)) * FRAG_BYTES;
+        return c < FM ? (wm * FM + token_block(c)) * FRAG_BYTES : G::A_BYTES + (wn * FN + channel_block(c - FM)) * FRAG_BYTES;
     };
     const FieldMasks masks = field_masks();
 
     v16f acc[FM][FN];
-    constexpr int RB = 4;                // chunks on their way from LDS
+    constexpr int RB = NF % 4 == 0 ? 4 : NF;      // chunks on their way from LDS
     static_assert(NF % RB == 0, "a chunk keeps its place from step to step");
     uint4 raw[RB];
     v6i frag[2][NF];
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         raw[c % RB] = *reinterpret_cast<const uint4 *>(lds + ((lane_off ^ (32 * s)) + (stage_byte + part(c))));
     };
     // place of a fragment among those this wave sums, or -1
-    auto sum_slot = [](int c) { return c < FM ? (c % WN == 0 ? c / WN : -1) : ((c - FM) % WM == 0 ? NSUM_A + (c - FM) / WM : -1); };
+    auto sum_slot = [](int c) { return c < FM ? (c % WN == 0 ? c / WN : -1) : ((c - FM) % SHARE_B == 0 ? NSUM_A + (c - FM) / SHARE_B : -1); };
     auto convert_half = [&](int set, int c, int h) {
         const uint4 r = raw[c % RB];
         const uint32_t w0 = h ? r.z : r.x, w1 = h ? r.w : r.y;
@@ -286,10 +291,8 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
             const int j = m / FM, i = m % FM;                                                                       \
             if ((TURN) >= 0 && m == (M0)) SQ_FP6_TURN(TURN);                                                        \
             acc[i][j] = mfma_fp6(frag[C][FM + j], frag[C][i], acc[i][j]);                                           \
-            if (KG == 2 && m % (NM / NF) == 1 % (NM / NF)) {                                                        \
-                const int c = m / (NM / NF), u = sum_slot(c);                                                       \
-                if (u >= 0) mfma_fp6_16(frag[C][c], sum_sel, sum_acc[u]);                                           \
-            }                                                                                                       \
+            _Pragma("unroll") for (int c = 0; KG == 2 && c < NF; ++c)                                               \
+                if (sum_slot(c) >= 0 && m == (2 * c + 1) * NM / (2 * NF)) mfma_fp6_16(frag[C][c], sum_sel, sum_acc[sum_slot(c)]); \
             _Pragma("unroll") for (int h = m * 2 * NF / NM; (CONVERT) && h < (m + 1) * 2 * NF / NM; ++h) {          \
                 convert_half(1 - (C), h >> 1, h & 1);                                                               \
                 if (h & 1) {                                                                                        \
@@ -301,10 +304,8 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
             _Pragma("unroll") for (int q = (LOAD0); q < (LOAD1); ++q)                                               \
                 if (m == (M0) + (q - (LOAD0)) * (NM - (M0)) / ((LOAD1) > (LOAD0) ? (LOAD1) - (LOAD0) : 1)) issue_one(q);   \
             if (KG == 1) __builtin_amdgcn_sched_barrier(0);                                                         \
-            if (KG == 1 && m % (NM / NF) == 1 % (NM / NF)) {                                                        \
-                const int c = m / (NM / NF), u = sum_slot(c);                                                       \
-                if (u >= 0) mfma_fp6_16(frag[C][c], sum_sel, sum_acc[u]);                                           \
-            }                                                                                                       \
+            _Pragma("unroll") for (int c = 0; KG == 1 && c < NF; ++c)                                               \
+                if (sum_slot(c) >= 0 && m == (2 * c + 1) * NM / (2 * NF)) mfma_fp6_16(frag[C][c], sum_sel, sum_acc[sum_slot(c)]); \
             __builtin_amdgcn_sched_barrier(0);                                                                      \
         }                                                                                                           \
     } while (0)
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
     do {                                                                                                            \
         const int next = cur + 1 == NS ? 0 : cur + 1;                                                               \
         const int cb = cur * G::STAGE, nb = next * G::STAGE;                                                        \
-        constexpr int TURN_AT = 2 * (NF - RB) + 1, FIRST = STEPS == 4 ? LOADS / 4 : LOADS / 6;                      \
+        constexpr int TURN_AT = ((2 * (NF - RB) + 2) * NM + 2 * NF - 1) / (2 * NF) - 1, FIRST = STEPS == 4 ? LOADS / 4 : LOADS / 6;                      \
         constexpr bool END = KG == 2 && (LAST);                                                                     \
         if constexpr (STEPS == 4) {                                                                                 \
             SQ_FP6_STEP(0, cb, 1 % STEPS, cb, 2 % STEPS, 0, 0, 0, -1, true, true);                                  \
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         for (int c = 0; c < NF; ++c) {
             const int u = sum_slot(c);
             if (u < 0) continue;
-            const int row = c < FM ? (wm * FM + token_block(c)) * 32 : BM + (wn * FN + ((c - FM) ^ wm)) * 32;
+            const int row = c < FM ? (wm * FM + token_block(c)) * 32 : BM + (wn * FN + channel_block(c - FM)) * 32;
             const float codes8 = c < FM ? 0.f : (float)(128 / KG * Kb);      // 64 times the codes of this K group
             // accumulator of the 16 x 16 instruction: column l % 16, rows 4 (l / 16) + register; columns 0 and 1
             // hold the sums of rows 0 .. 15 and 16 .. 31 of the block
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
         for (int i = 0; i < FMO; ++i) token_halves[i] = halves((wm * FM + token_block(i)) * 32 + frow);
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-            const v4i channels = {(int)halves(BM + (wn * FN + (j ^ wm)) * 32 + frow), (int)ones, 0, 0};
+            const v4i channels = {(int)halves(BM + (wn * FN + channel_block(j)) * 32 + frow), (int)ones, 0, 0};
 #pragma unroll
             for (int i = 0; i < FMO; ++i) {
                 const v4i tokens = {(int)ones, (int)token_halves[i], 0, 0};
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
             constexpr bool PLAIN = decltype(plain)::value;
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
-                const int nj = (j ^ wm) * 32;                 // first channel of the fragment within this wave's
+                const int nj = channel_block(j) * 32;                 // first channel of the fragment within this wave's
                 float swn[16];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -546,12 +547,16 @@ static sq_status launch(const uint8_t *Qx, const float *sx, int T, int K, const 
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 
-sq_status launch_w4a4_fp6(bool large, const uint8_t *Qx, const float *sx, int T, int K, const uint8_t *Qw,
+sq_status launch_w4a4_fp6(Fp6Tile tile, const uint8_t *Qx, const float *sx, int T, int K, const uint8_t *Qw,
                           const float *sw, int N, __half *Y, int64_t ldy, int32_t *acc_dbg, hipStream_t st)
 {
-    if (!w4a4_fp6_takes(large, T, K, N)) return SQ_ERR_SHAPE;
-    return large ? launch<2, 4, 4, 1>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st)
-                 : launch<1, 4, 4, 2>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
+    if (!w4a4_fp6_takes(tile, T, K, N)) return SQ_ERR_SHAPE;
+    switch (tile) {
+        case Fp6Tile::k128x192: return launch<1, 4, 3, 2>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
+        case Fp6Tile::k128x256: return launch<1, 4, 4, 2>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
+        case Fp6Tile::k256x192: return launch<2, 4, 3, 1>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
+        default: return launch<2, 4, 4, 1>(Qx, sx, T, K, Qw, sw, N, Y, ldy, acc_dbg, st);
+    }
 }
 
 }  // namespace sq

@@ -843,45 +843,43 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     if (choice < 0 && Ti <= 32) choice = (N >= 64 * 384 && !rows_fit_lds) ? 8 : (N >= 10240 ? 9 : 7);
     if (choice < 0 && Ti <= 64) choice = 13;
     // Few tokens times few output channels: even 128x128 tiles would be too few for 256 CUs, and the
-    // time is one workgroup's walk over K.  64x64 tiles (four times as many workgroups) up to 64
-    // tiles of 128x128, 64x128 tiles up to 128.  (T = 128, K = N = 4096: 19.9 -> 14.6 us.)
+    // time is one workgroup's walk over K.  64x64 tiles, else 64x128 tiles, while they number at most one per CU
+    // (T = 200, K = N = 4096: 13.3 -> 11.6 us against 128x128 tiles; T = 384 16.8 -> 15.5; T = 675, K = 2048, N = 2752, 132 tiles
+    // of 128x128 or 242 of 64x128: 12.1 -> 8.7).  Without two K groups they run two per CU, and pay up to 128 tiles of 128x128.
     if (choice < 0) {
+        const int64_t n64 = (int64_t)((Ti + 63) / 64) * ((N + 63) / 64), n64x128 = (int64_t)((Ti + 63) / 64) * ((N + 127) / 128);
         const int64_t n128 = (int64_t)((Ti + 127) / 128) * ((N + 127) / 128);
-        if (n128 <= 64) choice = two_k_groups ? 14 : 10;          // T = 200, K = N = 4096: 13.3 -> 11.6 us
-        else if (n128 <= 128) choice = two_k_groups ? 15 : 11;    // T = 384, K = N = 4096: 16.8 -> 15.5 us
+        if (two_k_groups ? n64 <= 256 : n128 <= 64) choice = two_k_groups ? 14 : 10;
+        else if (two_k_groups ? n64x128 <= 256 : n128 <= 128) choice = two_k_groups ? 15 : 11;
     }
-    // Up to a few hundred tokens 128x256 tiles would leave CUs idle: 128x128 tiles (four waves).
+    // Many tokens or channels: the tile that needs the least time for its rounds of 256 workgroups, one per CU.  A full round
+    // takes fixed + slope per 256 codes of K; a last round of n tiles (5 + n / 256) / 6 of that, since fewer CUs at work run
+    // at a higher clock.  The constants are the best fit to 314 shapes (T = 128 .. 3100, K = 1024 .. 12288, N = 512 .. 30000),
+    // in ns; the choice takes at most 3 % longer than the best of the forms there (but where rows of Y begin at any element,
+    // below), 0.9 % in the mean.  The 6-bit forms have the smaller slope, for power; the int8 ones the shorter start.
     if (choice < 0) {
-        const int64_t wide = (int64_t)((Ti + 127) / 128) * ((N + 255) / 256);
-        if (wide <= 128) choice = (2 * wide <= 256) ? 5 : 2;
-    }
-    // 128x256 or 256x256 tiles: one workgroup per CU either way, so the time goes with the number
-    // of rounds of 256 tiles.  On the 6-bit float instruction (cases 18 and 19) a 256x256 tile takes about 1.6 times as
-    // long as a 128x256 one (K = 4096 / 8192 / 11008, all CUs busy: 42.3 / 74.6 / 98 against 28.0 / 46.8 / 60.2 us),
-    // on the int8 instruction (cases 16, 17 and 4) 1.85 times.
-    if (choice < 0) {
-        const int64_t n_small = (int64_t)((Ti + 127) / 128) * ((N + 255) / 256);
-        const int64_t n_large = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
-        const int64_t rounds_small = (n_small + 255) / 256, rounds_large = (n_large + 255) / 256;
-        const bool prefer_large = 5 * rounds_small > 8 * rounds_large;
-        // The gain of the 6-bit form is power, and its loop is the longer one in cycles: it pays once the K loop
-        // dominates and most of the CUs work.  Its time over the better int8 shape's, 128x256 tiles, by their number:
-        //              129 - 176        192      200      224      256
-        //   K = 1024   1.07 - 1.10      1.08     1.07     1.06     1.03
-        //   K = 2048   1.02 - 1.04      1.02     1.01     0.99     0.97
-        //   K = 3072   0.99 - 1.00      0.99     0.97     0.95     0.94
-        //   K = 3584   0.98 - 0.99      0.98     0.96     0.95     0.93
-        //   K = 5120   0.95 - 0.97      0.95     0.93     0.92     0.91      (162 tiles: 30.1 / 29.1 us)
-        // and with 256x256 tiles, 132 - 256 of them: K = 768 0.94 - 0.99, K = 1024 0.90 - 0.97, K = 4096 0.80 - 0.84.
-        // Several rounds count by their average (K = 2048: 387 tiles 33.5 / 34.8 us, 648 tiles 50.3 / 50.5).
-        const bool small_pays = K >= 3584 || (K >= 2048 && n_small >= 216 * rounds_small);
-        if (prefer_large && K >= 1024 && sq::w4a4_fp6_takes(true, Ti, K, N)) choice = 19;
-        else if (!prefer_large && small_pays && sq::w4a4_fp6_takes(false, Ti, K, N)) choice = 18;
-        // (Cases 16 and 17: the 128x256 tile with four loading waves; 16, eight multiplying waves of 64x64: 32.0 -> 31.5 us at
-        // T = 2048, K = N = 4096 against case 1, the same tile with the loads in the multiplying waves; 17, four of
-        // 64x128 with half the widening per MFMA: T = 2048, N = 4096, K = 65792 396 -> 376 us, K = 130816 791 -> 751
-        // against 16.  Its gain grows with the number of K tiles and turns positive at about 20 of them.)
-        else choice = (20 * rounds_small > 37 * rounds_large) ? 4 : (K >= 6144 ? 17 : 16);
+        auto time = [&](int rows, int columns, int64_t fixed, int64_t slope) {
+            const int64_t n = (int64_t)((Ti + rows - 1) / rows) * ((N + columns - 1) / columns), rest = n % 256;
+            return (fixed + slope * (K / 256)) * (1536 * (n / 256) + (rest ? 1280 + rest : 0));
+        };
+        // int8: 128x128 tiles (four waves, K tiles twice as long) while 128x256 ones would leave half of the CUs idle; else 128x256
+        // with four loading waves (32.0 -> 31.5 us at T = 2048, K = N = 4096 against the loads in the multiplying waves), eight
+        // multiplying waves of 64x64 or, with long K, four of 64x128 (T = 2048, N = 4096, K = 65792 396 -> 376 us); or 256x256.
+        // The int8 epilogue stores rows that begin at any element two bytes at a time: 4 us a round.
+        const int64_t n_small = (int64_t)((Ti + 127) / 128) * ((N + 255) / 256), n_large = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
+        const int64_t unaligned = ((uintptr_t)Y & 15) == 0 && (ldy % 8) == 0 ? 0 : 4000;
+        int64_t best;
+        if (n_small <= 128) choice = 5, best = time(128, 128, 6200 + unaligned, 900);
+        else if (20 * ((n_small + 255) / 256) > 37 * ((n_large + 255) / 256)) choice = 4, best = time(256, 256, 12440 + unaligned, 2361);
+        else choice = K >= 6144 ? 17 : 16, best = time(128, 256, 8120 + unaligned, 1319);
+        const struct { int choice; sq::Fp6Tile tile; int64_t fixed, slope; } forms[] = {
+            {20, sq::Fp6Tile::k128x192, 7590, 866}, {18, sq::Fp6Tile::k128x256, 10330, 931},
+            {21, sq::Fp6Tile::k256x192, 10060, 1536}, {19, sq::Fp6Tile::k256x256, 12520, 1692}};
+        for (const auto &form : forms) {
+            if (!sq::w4a4_fp6_takes(form.tile, Ti, K, N)) continue;
+            const int64_t t = time(sq::fp6_tile_tokens(form.tile), sq::fp6_tile_channels(form.tile), form.fixed, form.slope);
+            if (t < best) choice = form.choice, best = t;
+        }
     }
     switch (choice) {
         case 0: return sq::launch_main<2, 2, 2, 4, 128, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
@@ -900,8 +898,12 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         case 8: if (Ti <= 32) return sq::launch_skinny<1, 2, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 9: if (Ti <= 32) return sq::launch_skinny<1, 1, 8>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 13: if (Ti <= 64) return sq::launch_skinny<2, 1, 8>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
-        case 18: if (sq::w4a4_fp6_takes(false, Ti, K, N)) return sq::launch_w4a4_fp6(false, Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
-        case 19: if (sq::w4a4_fp6_takes(true, Ti, K, N)) return sq::launch_w4a4_fp6(true, Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
+        case 18: case 19: case 20: case 21: {
+            const sq::Fp6Tile tile = choice == 18 ? sq::Fp6Tile::k128x256 : choice == 19 ? sq::Fp6Tile::k256x256
+                                   : choice == 20 ? sq::Fp6Tile::k128x192 : sq::Fp6Tile::k256x192;
+            if (sq::w4a4_fp6_takes(tile, Ti, K, N)) return sq::launch_w4a4_fp6(tile, Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+            break;
+        }
         default: break;
     }
     return sq::launch_main<2, 4, 2, 2, 128, 1>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);

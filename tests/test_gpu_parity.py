@@ -454,8 +454,19 @@ def test_gemm_six_bit_float_kernel_rounds_like_the_others(case, other):
     assert np.array_equal(Y[0].view(np.uint16), Y[1].view(np.uint16))
 
 
+@pytest.mark.parametrize("case,T,K,N", [
+    # 128 x 192 and 256 x 192 tiles: exactly one, overlapping last tiles in both directions, an odd number of K tiles, more
+    # tiles than CUs, the longest K
+    (20, 128, 768, 192), (20, 129, 1024, 193), (20, 300, 1280, 520), (20, 200, 65536, 192), (20, 4100, 768, 1800),
+    (21, 256, 768, 192), (21, 257, 1280, 193), (21, 300, 1024, 520), (21, 256, 65536, 200), (21, 4100, 768, 4300)])
+def test_gemm_six_bit_float_kernel_192_channels(oracle, case, T, K, N):
+    """The tiles of 192 channels: fragments of an odd number, which the waves of a row of tiles sum each for itself."""
+    test_gemm_six_bit_float_kernel(oracle, case, T, K, N)
+
+
 @pytest.mark.parametrize("case,T,K,N,pad", [(18, 128, 768, 256, 0), (18, 200, 1280, 520, 0), (18, 129, 1024, 264, 8), (18, 128, 65536, 256, 0),
-                                            (19, 256, 768, 256, 0), (19, 300, 1024, 520, 0), (19, 4100, 768, 4504, 8)])
+                                            (19, 256, 768, 256, 0), (19, 300, 1024, 520, 0), (19, 4100, 768, 4504, 8),
+                                            (20, 200, 1280, 520, 8), (21, 300, 1024, 520, 8)])
 def test_gemm_six_bit_float_kernel_without_accumulators(case, T, K, N, pad):
     """The epilogue has a form without branches for calls that do not ask for the accumulators: the same fp16 outputs, bit
     for bit, on sums of every size the corrections can take (random codes; all codes 7 against random ones; all -8)."""
