@@ -34,8 +34,11 @@ constexpr int kBuildSmallBytes = 6 * kBuildWaves * 4 + 5 * kMaxSide * 8 + 2 * SQ
 // ART candidates: the 2 P largest and the 2 P smallest channels of the calibration row
 constexpr int kMaxCandidates = 4 * SQ_MAX_GIVENS;
 static_assert(kMaxCandidates == 4 * kWave, "one wave holds them, four per lane");
-// two histograms of 256 bins, the candidates' channels, one count per wave, results of the two searches, a counter
-constexpr int kSelectWords = 2 * 256 + kMaxCandidates + kBuildWaves + 4 + 2;
+// two histograms of 256 bins, the candidates, one count per wave, results of the two searches, a counter, the channels of
+// the P largest and the P smallest in order
+constexpr int kSelectWords = 2 * 256 + kMaxCandidates + kBuildWaves + 4 + 2 + 2 * SQ_MAX_GIVENS;
+constexpr uint32_t kChannelMask = 0x3FFF;      // a candidate: its 15-bit magnitude above its channel
+static_assert(SQ_MAX_K <= kChannelMask + 1 && SQ_MAX_GIVENS <= kWave, "limits");
 static_assert(kBuildSmallBytes % 8 == 0, "the fp64 vectors behind the slots are 8-byte aligned");
 
 // workspace, in floats
@@ -198,6 +201,62 @@ __device__ __forceinline__ int bin_reaching(const uint32_t *hist, uint32_t targe
     return DOWN ? 255 - bin : bin;
 }
 
+// r / sqrt(2) of Lemma 1
+__device__ __forceinline__ double equalised(double a, double b)
+{
+    return sqrt(fma(a, a, b * b)) * 0.70710678118654752440;
+}
+
+// The same for a in the range of fp16 and of what the steps make of it (a >= 2^-25, b <= a), where a square root needs neither
+// its scaling nor its special cases: a Newton step for 1 / sqrt beside one for sqrt, then two for sqrt alone.  The same
+// bits as the square root of the function above, whose steps these are.
+__device__ __forceinline__ double equalised_in_range(double a, double b)
+{
+    const double x = fma(a, a, b * b), r = __builtin_amdgcn_rsq(x);
+    double root = x * r, half = 0.5 * r;
+    const double d = fma(-half, root, 0.5);
+    root = fma(root, d, root), half = fma(half, d, half);
+    root = fma(fma(-root, root, x), half, root);
+    root = fma(fma(-root, root, x), half, root);
+    return root * 0.70710678118654752440;
+}
+
+// lane l takes the value of lane l - 1 (lane 0: zero)
+__device__ __forceinline__ uint32_t wave_up(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);      // wave_shr:1
+}
+
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+
+// The wave's list of the largest channels, in order: value (as the two halves of a double, magnitudes) descending, among
+// equals the channel ascending (above its sign bit).  What is pushed past lane 63 is never asked for again: a step takes one,
+// and there are 64 steps.
+struct Largest {
+    static constexpr uint32_t kNone = 0xFFFFFFFFu;
+    uint32_t hi = 0, lo = 0, channel = kNone;
+
+    __device__ __forceinline__ double value() const { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); }
+    __device__ __forceinline__ void drop_first(int r, int lane)
+    {
+        hi = __shfl(hi, lane + r), lo = __shfl(lo, lane + r), channel = __shfl(channel, lane + r);
+        if (lane + r >= kWave) hi = 0, lo = 0, channel = kNone;
+    }
+    // the value e for channels c1 < c2
+    __device__ __forceinline__ void insert(uint32_t eh, uint32_t el, uint32_t c1, uint32_t c2, int lane)
+    {
+        const double e = __longlong_as_double((long long)(((uint64_t)eh << 32) | el)), mine = value();
+        const uint64_t above = __ballot(mine > e), same = __ballot(mine == e);
+        const int at1 = __popcll(above | (same & __ballot(channel < c1))), at2 = __popcll(above | (same & __ballot(channel < c2))) + 1;
+        const uint32_t hi1 = wave_up(hi), lo1 = wave_up(lo), ch1 = wave_up(channel);
+        const uint32_t hi2 = wave_up(hi1), lo2 = wave_up(lo1), ch2 = wave_up(ch1);
+        const bool first = lane == at1, second = lane == at2, one = lane > at1, two = lane > at2;
+        hi = first || second ? eh : two ? hi2 : one ? hi1 : hi;
+        lo = first || second ? el : two ? lo2 : one ? lo1 : lo;
+        channel = first ? c1 : second ? c2 : two ? ch2 : one ? ch1 : channel;
+    }
+};
+
 __device__ __forceinline__ void magnitude_key(double v, uint32_t &hi, uint32_t &lo)
 {
     const uint64_t bits = (uint64_t)__double_as_longlong(fabs(v));
@@ -207,23 +266,41 @@ __device__ __forceinline__ void magnitude_key(double v, uint32_t &hi, uint32_t &
 
 // Step k of the Givens chain that takes `vec` (n entries) to ||vec|| e_1: entry k is zeroed by a
 // rotation in the plane (k - 1, k), k = n - 1 down to 1.  When step k acts, entry k holds the norm
-// of the original entries k .. n-1, so with S_k the sum of their squares
+// of the original entries k .. n-1, so with S_k the sum of their squares (tail[k])
 //   cos_k = v_{k-1} / sqrt(S_{k-1}),   sin_k = sqrt(S_k / S_{k-1})     (cos = 1, sin = 0 if S_{k-1} = 0;
 //   sin_{n-1} = v_{n-1} / sqrt(S_{n-2}), because the last entry enters with its sign)
 // and the steps can be computed independently of one another.  Stored at cs[k], cs[kMaxSide + k].
-__device__ __forceinline__ void chain_step(const double *vec, int n, int k, float *cs)
+__device__ __forceinline__ void chain_step(const double *vec, const double *tails, int n, int k, float *cs)
 {
-    double tail = 0.0;
-    // (every thread reads every entry, eight at a time, rather than each its own number of them one after another)
-#pragma unroll 8
-    for (int m = n - 1; m >= 1; --m) {
-        const double o = vec[m];
-        tail += m >= k ? o * o : 0.0;
-    }
-    const double x = vec[k - 1], all = tail + x * x;
+    const double x = vec[k - 1], tail = tails[k], all = tail + x * x;
     cs[k] = (all == 0.0) ? 1.f : (float)(x / sqrt(all));
     // the first step (k = n-1) meets the last entry itself, sign included; later ones meet a norm
     cs[kMaxSide + k] = (all == 0.0) ? 0.f : (float)(k == n - 1 ? vec[k] / sqrt(all) : sqrt(tail / all));
+}
+
+// tails[k] = sum of the squares of the entries k .. n-1, k = n-1 .. 1, by one wave (four entries a lane); returns the sum of all
+__device__ __forceinline__ double sum_tails(const double *vec, int n, double *tails)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    static_assert(kMaxSide == 4 * kWave, "four entries a lane");
+    double own[4], sum = 0.0;
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+        const double o = 4 * lane + u < n ? vec[4 * lane + u] : 0.0;
+        own[u] = sum += o * o;
+    }
+    double from = sum;                                             // of this lane's entries and all behind them
+#pragma unroll
+    for (int d = 1; d < kWave; d *= 2) {
+        const double o = __shfl_down(from, d);
+        if (lane + d < kWave) from += o;
+    }
+    double next = __shfl_down(from, 1);
+    if (lane == kWave - 1) next = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (4 * lane + u >= 1 && 4 * lane + u < n) tails[4 * lane + u] = own[u] + next;
+    return __shfl(from, 0);
 }
 
 // One workgroup.  All of its LDS is dynamic (kBuildSmallBytes + 8 (K + n1) + 4 kSelectWords bytes): the reduction slots,
@@ -233,9 +310,12 @@ __device__ __forceinline__ void chain_step(const double *vec, int n, int k, floa
 // What bounds it is the chain of P dependent ART steps.  Step p (from 0) has at most 2 p channels rewritten by the steps
 // before it, so what it picks is one of those or among the first 2 p + 1 in order of the calibration row as it was:
 // the 2 P largest and the 2 P smallest channels are all that can ever be chosen.  A radix selection on the
-// 15-bit magnitudes (two histograms of 256 bins, ties by channel) finds them, and one wave then holds them in registers
-// and takes the steps without a barrier, 0.73 us each.  T = 2048, K = 4096, P = 32: 91.5 -> 41.5 us against a
-// reduction over all channels by the whole workgroup in every step.
+// 15-bit magnitudes (two histograms of 256 bins, ties by channel) finds them, 5.6 us; where the two sets are disjoint, counting
+// puts the P outermost of either in order (1.5 us), and one wave takes the steps from those two ends, several at once
+// (T = 2048, K = 4096, P = 32: 0.18 us a step).  What that does not cover (generated values among the smallest, a row nearly all
+// of one magnitude, at most 256 channels) one wave does with the candidates in registers and two reductions a step, 0.73 us each.
+// The whole kernel at that size: 91.5 us with a reduction over all channels by the whole workgroup in every step, 41.5 with
+// the reductions of one wave, 22 now.
 // BY_ALL: that reduction instead, which is faster for few steps over few channels (steps_by_all).
 template <bool BY_ALL>
 __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
@@ -255,6 +335,8 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
     uint32_t *wave_ties = cand + kMaxCandidates;                   // [kBuildWaves]
     uint32_t *found = wave_ties + kBuildWaves;                     // bin and count before it, from above and from below
     uint32_t *n_cand = found + 4;
+    uint32_t *in_order = n_cand + 2;                               // [2][SQ_MAX_GIVENS]
+    double *pair_norm = reinterpret_cast<double *>(slots_a);       // [2]: the slots are free by then
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int n2_log = 31 - __clz(n2);                             // n2 is a power of two
     auto at = [n2_log](int k) { return k + (k >> n2_log); };
@@ -281,6 +363,7 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
         key[e] = in ? (__half_as_ushort(h) & 0x7FFFu) : 0xFFFFu;
         if (in) cvec[at(k0 + e)] = (double)__half2float(h);
     }
+    bool ordered = false;                                          // in_order holds the ends of two disjoint sets
     if (P > 0 && !BY_ALL && K <= kMaxCandidates) {
         if (tid < K) cand[tid] = (uint32_t)tid;
         if (tid == 0) *n_cand = (uint32_t)K;
@@ -340,7 +423,26 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
             bool take = key[e] > key_hi || key[e] < key_lo;
             if (key[e] == key_hi) take |= rank_hi++ < ties_hi;
             if (key[e] == key_lo) take |= rank_lo++ < ties_lo;
-            if (take) cand[atomicAdd(n_cand, 1u)] = (uint32_t)(k0 + e);
+            if (take) cand[atomicAdd(n_cand, 1u)] = (key[e] << 14) | (uint32_t)(k0 + e);
+        }
+        __syncthreads();
+        // Four threads count how many candidates come before theirs, from above and from below (lower channels first).
+        ordered = key_hi > key_lo;
+        if (ordered) {
+            const uint32_t self = (tid >> 2) < 4 * P ? cand[tid >> 2] : 0u;
+            uint32_t larger = 0, smaller = 0;                      // 16 bits each would do
+#pragma unroll 8
+            for (int m = 0; m < P; ++m) {
+                const uint32_t o = cand[4 * m + (tid & 3)];
+                larger += (o ^ kChannelMask) > (self ^ kChannelMask);
+                smaller += o < self;
+            }
+            larger += __shfl_xor(larger, 1), smaller += __shfl_xor(smaller, 1);
+            larger += __shfl_xor(larger, 2), smaller += __shfl_xor(smaller, 2);
+            if ((tid & 3) == 0 && (tid >> 2) < 4 * P) {
+                if (larger < (uint32_t)P) in_order[larger] = self & kChannelMask;
+                if (smaller < (uint32_t)P) in_order[SQ_MAX_GIVENS + smaller] = self & kChannelMask;
+            }
         }
     }
     __syncthreads();
@@ -366,7 +468,7 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
             const int j = (int)block_arg<false>(lo_h, lo_l, lo_at, slots_b);
             if (tid == 0) {
                 const double a = cvec[at(i)], b = cvec[at(j)];
-                const double e = sqrt(a * a + b * b) * 0.70710678118654752440;
+                const double e = equalised(a, b);
                 giv_i[p] = i;
                 giv_j[p] = j;
                 pair_a[p] = a;
@@ -376,12 +478,60 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
             __syncthreads();
         }
     } else if (wave == 0 && P > 0) {
+        auto value = [](uint32_t hi, uint32_t lo) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); };
+        // While the smallest untouched channels are below everything generated, a step takes the next one of those, which lie in
+        // lane order, and the first of the list of the largest, where what it makes is put in its place by counting: no
+        // reduction on the chain.  What a step makes of a >= 4 b is below 0.73 a, so all channels of the list above 0.73 of the
+        // first one are taken, in order, before anything the steps between make: those steps are done at once, a lane each.
+        // (Magnitudes of fp16 values have no lower half.)
+        int p0 = 0;
+        if (ordered) {
+            Largest largest;
+            uint32_t low_hi = 0, low_ch = 0;                       // channel above its sign bit
+            if (lane < P) {
+                const uint32_t t = in_order[lane], l = in_order[SQ_MAX_GIVENS + lane];
+                const uint32_t th = (uint32_t)__double2hiint(cvec[at((int)t)]), lh = (uint32_t)__double2hiint(cvec[at((int)l)]);
+                largest.hi = th & 0x7FFFFFFFu, largest.channel = t << 1 | th >> 31;
+                low_hi = lh & 0x7FFFFFFFu, low_ch = l << 1 | lh >> 31;
+            }
+            uint32_t least = 0x7FFFFFFFu;                          // upper half of the smallest value made
+            while (p0 < P) {
+                const uint32_t bh = __shfl(low_hi, lane + p0), cj = __shfl(low_ch, lane + p0), ci = largest.channel;
+                const double a = largest.value(), b = value(bh, 0), first = value(lane_of(largest.hi, 0), lane_of(largest.lo, 0));
+                if (first == 0.0) break;
+                int r = __popcll(__ballot(lane < P - p0 && a > 0.73 * first && 4.0 * b <= first && bh < least));
+                if (r == 0) {
+                    if (lane_of(bh, 0) >= least) break;
+                    r = 1;
+                }
+                const double e = equalised_in_range(a, b);
+                const uint32_t eh = (uint32_t)__double2hiint(e), el = (uint32_t)__double2loint(e), i = ci >> 1, j = cj >> 1;
+                if (lane < r) {
+                    giv_i[p0 + lane] = (int)i;
+                    giv_j[p0 + lane] = (int)j;
+                    pair_a[p0 + lane] = (ci & 1) ? -a : a;
+                    pair_b[p0 + lane] = (cj & 1) ? -b : b;
+                    cvec[at((int)i)] = cvec[at((int)j)] = e;
+                }
+                largest.drop_first(r, lane);
+                for (int q = 0; q < r; ++q) {
+                    const uint32_t qh = lane_of(eh, q), qi = lane_of(i, q) << 1, qj = lane_of(j, q) << 1;
+                    largest.insert(qh, lane_of(el, q), min(qi, qj), max(qi, qj), lane);
+                    least = min(least, qh);
+                }
+                p0 += r;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        // The other steps, if any (generated values among the smallest, few channels, nearly all of one magnitude).
         // This lane's candidates by channel, their magnitudes as integers; no channel: zero among the largest, all
         // ones among the smallest.
         uint32_t idx[4];
         uint64_t large[4], small[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) idx[u] = (uint32_t)(lane + 64 * u) < *n_cand ? cand[lane + 64 * u] : 0xFFFFFFFFu;
+        for (int u = 0; u < 4; ++u) idx[u] = (uint32_t)(lane + 64 * u) < *n_cand ? cand[lane + 64 * u] & kChannelMask : 0xFFFFFFFFu;
         auto order = [&](int x, int y) {
             const uint32_t lower = min(idx[x], idx[y]), upper = max(idx[x], idx[y]);
             idx[x] = lower, idx[y] = upper;
@@ -402,8 +552,7 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
                 if (small[u] < best && idx[u] != skip) best = small[u], who = idx[u];
             return wave_arg_short<false>((uint32_t)(best >> 32), (uint32_t)best, who, hi, lo);
         };
-        auto value = [](uint32_t hi, uint32_t lo) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); };
-        for (int p = 0; p < P; ++p) {
+        for (int p = p0; p < P; ++p) {
             uint64_t best = large[0];
             uint32_t who = idx[0], ah, al, bh, bl;
 #pragma unroll
@@ -413,7 +562,7 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
             uint32_t j = smallest_but(0xFFFFFFFFu, bh, bl);
             if (j == i) j = smallest_but(i, bh, bl);   // every magnitude the same
             const double a = value(ah, al), b = value(bh, bl);
-            const double e = sqrt(a * a + b * b) * 0.70710678118654752440;
+            const double e = equalised(a, b);
             if (lane == 0) {                           // beside the chain: the LDS traffic of a wave is in order
                 giv_i[p] = (int)i;
                 giv_j[p] = (int)j;
@@ -454,32 +603,39 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
     }
     __syncthreads();
 
-    // uniform targets (Sec. 4.2 URT): template q_k = (2k - n - 1)/n by rank (ties: lower index
-    // first), scaled to the norm of the vector; ||q||^2 = (n^2 - 1)/(3n)
-    {
-        const int side = tid >= 512, k = tid - 512 * side, n = side ? n2 : n1;
-        if (k < n) {
-            const double *v = vec[side];
-            const double mine = v[k];
-            int rank = 0;
-            double norm2 = 0.0;
+    // Uniform targets (Sec. 4.2 URT): template q_k = (2k - n - 1)/n by rank (ties: lower index
+    // first), scaled to the norm of the vector; ||q||^2 = (n^2 - 1)/(3n).  Half of the workgroup per side, two threads an
+    // entry; the sums of squares by a wave that has few or no entries to rank.  The tails lie where the calibration vector was.
+    const int half = tid / 512, in_half = tid % 512, n_half = half ? n2 : n1;
+    double *tail_v = cvec + (half ? 2 * n1 - 2 : 0) - 1, *tail_u = tail_v + n_half - 1;      // entries 1 .. n - 1
+    const double *v_half = vec[half];
+    int rank = 0;
+    if (in_half / 2 < n_half) {
+        const int k = in_half / 2;
+        const double mine = v_half[k];
 #pragma unroll 8
-            for (int m = 0; m < n; ++m) {
-                const double o = v[m];
-                rank += (o < mine) || (o == mine && m < k);
-                norm2 += o * o;
-            }
-            const double qnorm2 = ((double)n * n - 1.0) / (3.0 * n);
-            target[side][k] = sqrt(norm2 / qnorm2) * (2.0 * (rank + 1) - n - 1.0) / n;
+        for (int m = in_half & 1; m < n_half; m += 2) {
+            const double o = v_half[m];
+            rank += (o < mine) || (o == mine && m < k);
         }
     }
+    rank += __shfl_xor(rank, 1);
+    if (in_half >= 448) {
+        const double norm2 = sum_tails(v_half, n_half, tail_v);
+        if (lane == 0) pair_norm[half] = sqrt(norm2 / (((double)n_half * n_half - 1.0) / (3.0 * n_half)));
+    }
+    __syncthreads();
+    if (in_half / 2 < n_half && (in_half & 1) == 0)
+        target[half][in_half / 2] = pair_norm[half] * (2.0 * (rank + 1) - n_half - 1.0) / n_half;
+    __syncthreads();
+    if (in_half < kWave) sum_tails(target[half], n_half, tail_u);
     __syncthreads();
 
-    // the four chains: thread (which, k) computes step k of chain `which`
+    // the four chains: a thread computes step k of the chain of V or of U
     {
-        const int which = tid / kMaxSide, k = tid % kMaxSide, side = which >> 1, is_target = which & 1;
-        const int n = side ? n2 : n1;
-        if (k >= 1 && k < n) chain_step(is_target ? target[side] : vec[side], n, k, chain + which * 2 * kMaxSide);
+        const int is_target = in_half / kMaxSide, k = in_half % kMaxSide;
+        if (k >= 1 && k < n_half)
+            chain_step(is_target ? target[half] : v_half, is_target ? tail_u : tail_v, n_half, k, chain + (2 * half + is_target) * 2 * kMaxSide);
     }
 
     // the angles of Lemma 1, one thread per ART step
@@ -493,8 +649,8 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
 // register and multiplies every entry, as it appears, with eight entries of R'_map out of LDS: neither map is ever
 // stored.  Side 1 leaves as fp16 R1.  Side 2 goes through the normalised Sylvester Hadamard matrix first,
 // H[a][m] = (-1)^popcount(a & m) / sqrt n, as a fast transform over the rows (R2 = H R^U_2).
-// A few KB and a chain of n dependent steps: one launch and 11 us where the three launches (maps, product, Hadamard
-// factor) took 6.3 + 4.7 + 6.0 us at 64 x 64.
+// A few KB and a chain of n dependent steps: one launch and 8.4 us (11.2 with a barrier for every stage of the transform) where
+// the three launches (maps, product, Hadamard factor) took 6.3 + 4.7 + 6.0 us at 64 x 64.
 constexpr int kUrtCols = 8;
 
 __global__ __launch_bounds__(kMaxSide) void urt_columns_kernel(const float *__restrict__ chain, int n1, int n2,
@@ -548,7 +704,15 @@ __global__ __launch_bounds__(kMaxSide) void urt_columns_kernel(const float *__re
             if (r < n && c0 + c < n) R1[r * n + c0 + c] = __float2half_rn(s[c]);
         return;
     }
-    for (int h = 1; h < n; h *= 2) {                             // n is a power of two
+    // n is a power of two: six stages between the lanes of a wave, what is left through LDS
+    for (int h = 1; h < n && h < kWave; h *= 2) {
+#pragma unroll
+        for (int c = 0; c < kUrtCols; ++c) {
+            const float o = __shfl_xor(s[c], h);
+            s[c] = (r & h) ? o - s[c] : s[c] + o;
+        }
+    }
+    for (int h = kWave; h < n; h *= 2) {
 #pragma unroll
         for (int c = 0; c < kUrtCols; ++c) ru[r][c] = s[c];
         __syncthreads();
@@ -561,10 +725,14 @@ __global__ __launch_bounds__(kMaxSide) void urt_columns_kernel(const float *__re
         if (r < n && c0 + c < n) R2[r * n + c0 + c] = __float2half_rn(s[c] * inv_sqrt_n2);
 }
 
-// A step over all channels by the whole workgroup takes 1.5 us at K = 512 and 2 us at 1024, the choice of the candidates 5 us
-// whatever P (whole call in us, candidates / all channels: K = 512, P = 1 24.1 / 20.3, P = 4 26.7 / 25.2, P = 6 28.6 / 28.5;
-// K = 1024, P = 1 25.4 / 21.6, P = 3 26.7 / 25.1, P = 4 27.7 / 28.0; K = 1536, P = 1 25.6 / 21.9, P = 2 26.5 / 26.4).
-bool steps_by_all(int32_t K, int32_t P) { return K > kMaxCandidates && 256 * P + K <= 1792; }
+// A step over all channels by the whole workgroup takes 1.5 us at K = 512 and 6 us at 16384; the choice of the candidates and
+// their order take 7 us whatever P, and hardly more with every step (whole call in us, in order / all channels: K = 384, P = 4
+// 22.1 / 20.8; K = 1024, P = 4 22.5 / 22.4, P = 5 22.6 / 24.1; K = 2048, P = 3 25.5 / 24.4, P = 4 25.9 / 26.4; K = 8192, P = 2
+// 36.6 / 36.4, P = 3 37.0 / 40.2; K = 16384, P = 1 45.3 / 42.8, P = 2 45.6 / 48.7).
+bool steps_by_all(int32_t K, int32_t P)
+{
+    return K > kMaxCandidates && (P <= 1 || (P <= 2 && K <= 8192) || (P <= 3 && K <= 2048) || (P <= 4 && K <= 1024));
+}
 
 bool build_shape_ok(int64_t T, int32_t K, int32_t n1, int32_t n2, int32_t P)
 {

@@ -142,6 +142,34 @@ def test_art_channels_among_equal_magnitudes(oracle, n1, n2, P, values):
     assert np.max(np.abs(g["giv_theta"].astype(np.float64) - gt)) <= 2e-6
 
 
+@pytest.mark.parametrize("n1,n2,P", [(9, 32, 64), (33, 16, 5), (64, 64, 32), (128, 128, 64)])
+@pytest.mark.parametrize("kind", ["clamped", "geometric", "narrow", "two_scales"])
+def test_art_steps_taken_several_at_once(oracle, n1, n2, P, kind):
+    """Steps are taken together while nothing they make can come between the channels they take, and one by one by other means
+    once generated values are among the smallest: runs of equal outliers, magnitudes all along the boundary of what is taken
+    together, magnitudes too close for any two steps, and a row whose small half is used up in the middle of the list."""
+    print(f"case ART runs {n1}x{n2} P={P} {kind}", flush=True)
+    rng = np.random.default_rng(n1 + P)
+    K = n1 * n2
+    x = rng.standard_normal(K)
+    if kind == "clamped":
+        x[rng.permutation(K)[:12]] = rng.choice([-65504.0, 65504.0], 12)
+    elif kind == "geometric":
+        x = np.where(rng.random(K) < 0.5, -1.0, 1.0) * rng.permutation(6e4 * 0.985 ** np.arange(K))
+    elif kind == "narrow":
+        x = rng.uniform(1.0, 1.2, K)
+    else:
+        x = np.where(np.arange(K) < P // 2, rng.uniform(1e-3, 2e-3, K), rng.uniform(30.0, 31.0, K))
+        x[-8:] = 3000.0
+    X = x.astype(np.float16)[None]
+    g = run_build(X, n1, n2, P)
+    gi, gj, gt, _, margin, departures = oc.art_select(X[0], P, follow=(g["giv_i"], g["giv_j"]), band=ART_BAND)
+    if margin > ART_BAND:
+        assert departures == 0
+    assert np.array_equal(g["giv_i"], gi) and np.array_equal(g["giv_j"], gj)
+    assert np.max(np.abs(g["giv_theta"].astype(np.float64) - gt)) <= 2e-6
+
+
 def test_build_rotation_full_size_and_its_use_on_the_hot_path(oracle):
     """Full attn_proj calibration batch; then the constructed list and factors drive the online
     kernel, checked against the oracle's rotation with the same list and factors."""
