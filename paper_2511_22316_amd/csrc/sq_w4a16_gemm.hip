@@ -576,6 +576,11 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
     // what fits in LDS), then the first D slices of codes; loads complete in order, so the rows
     // can be written to LDS while the codes are still on their way.  All requests are
     // unconditional (clamped), which keeps the compiler's count of outstanding loads exact.
+    // The walk over K begins with another round in neighbouring workgroups, which sit on different XCDs: rows of codes lie a
+    // power of two apart for the usual K, and with every wave of the chip at the same place of its row the requests of a
+    // moment meet in a few memory channels (T = 8, N = 28672: K = 8192 31.6 -> 27.7 us; K = 4096 19.5 -> 19.1, K = 11264, K = 14336 the
+    // same within 1 %; by slices instead of whole rounds, or by wave: slower again).
+    const int turn = (int)blockIdx.x % (slices / D) * D;
     const int chunks_per_row = K / 8, chunks = T * chunks_per_row;
     {
         uint4 xv[kXldsChunks];
@@ -586,7 +591,7 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
         }
         const uint8_t *row0 = row_of(0);             // a wave without blocks requests (and drops) a valid row
 #pragma unroll
-        for (int i = 0; i < D; ++i) issue(rb[i], row0, i);
+        for (int i = 0; i < D; ++i) issue(rb[i], row0, turn + i);
 #pragma unroll
         for (int u = 0; u < kXldsChunks; ++u) {
             const int j = tid + NT * u;
@@ -638,7 +643,7 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
         }
     };
     v8h ta[2][8];                                      // token chunks of this slice and of the next
-    read_tokens(ta[0], 0);
+    read_tokens(ta[0], turn);
     for (int bi = 0; bi < my_blocks; ++bi) {
         const int n = 16 * (first + bi * step) + l16;
         const float step_n = sw[min(n, N - 1)];
@@ -646,21 +651,23 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
         const uint8_t *row_after = row_of(bi + 1 < my_blocks ? bi + 1 : bi);
         acc0 = v4f{0.f, 0.f, 0.f, 0.f};
         acc1 = v4f{0.f, 0.f, 0.f, 0.f};
-        for (int S0 = 0; S0 < slices; S0 += D) {
-            const bool wrap = S0 + D >= slices;            // the round D slices ahead opens the next block
+        int S0 = turn;
+        for (int done = 0; done < slices; done += D) {
+            const bool wrap = done + D >= slices;          // the round D slices ahead opens the next block
             const uint8_t *row_n = wrap ? row_after : row;
-            const int S_n = wrap ? (bi + 1 < my_blocks ? 0 : S0) : S0 + D;
+            const int after = S0 + D == slices ? 0 : S0 + D;       // behind the last round of a block: its first one, `turn`, again
+            const int S_n = wrap && bi + 1 == my_blocks ? S0 : after;
 #pragma unroll
             for (int i = 0; i < D; ++i) {
-                // the slice after this one: behind the last slice of a block comes slice 0 again
-                // (the token rows are the same for every block)
-                read_tokens(ta[(i + 1) & 1], (i + 1 == D && wrap) ? 0 : S0 + i + 1);
+                // the slice after this one (the token rows are the same for every block)
+                read_tokens(ta[(i + 1) & 1], i + 1 == D ? after : S0 + i + 1);
                 multiply(rb[i], ta[i & 1]);
                 issue(rb[i], row_n, S_n + i);
                 // keep the requests here, one slice behind another: collected at the end of the
                 // round (where the scheduler puts them) they would all be waited for at once
                 __builtin_amdgcn_sched_barrier(0);
             }
+            S0 = after;
         }
         // 16 x 16 accumulator layout: lane holds channel l16, register r holds token 4 q + r
 #pragma unroll
