@@ -6,8 +6,8 @@
 //   * blocks 0 .. groups-1 run the rotate + quantize body on token group `block`, publish codes
 //     and steps in the caller's workspace (release: their XCD's L2 is written back) and count
 //     themselves done;
-//   * every block then takes the output channels [block BN, (block + 1) BN): the weights of its
-//     first K slice are requested, it waits until all groups are done, reads the codes and runs
+//   * every block (on the narrower layers with long K, every one but those) takes 32 or 64 output channels: the weights
+//     of its first K slices are requested, it waits until all groups are done, reads the codes and runs
 //     the decode-shaped GEMM loop (K split over the four waves, partial sums added through LDS);
 //   * the last block clears the counters for the next launch once every block is past its wait.
 // The waits are bounded: a block that has polled for about a second skips its channels and raises
@@ -40,18 +40,28 @@ __device__ __forceinline__ void widen_codes(const uint4 w, v4i &first, v4i &seco
     second = v4i{(int)((w.z << 4) & m), (int)(w.z & m), (int)((w.w << 4) & m), (int)(w.w & m)};
 }
 
-// counters in the workspace: [0] token groups done, [1] workgroups past their wait, [3] error word
+// counters in the workspace: [0] token groups done, [1] workgroups with channels past their wait, [3] error word
 // (a wait gave up)
 template <int N1, int N2, int QS_MAX, int FN>
 __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
     const __half *__restrict__ X, int64_t ldx, int T, RotqPlan plan, const __half *__restrict__ F1,
     const __half *__restrict__ F2, uint8_t *Qx, float *sx, int *__restrict__ ctr,
     const uint8_t *__restrict__ Qw, const float *__restrict__ sw, int N, __half *__restrict__ Y, int64_t ldy,
-    int lds_main, int spin_limit, int sides)
+    int lds_main, int spin_limit, int sides, int apart)
 {
     using S = RotqShape<N1, N2, 3, false>;
     constexpr int Kb = N1 * N2 / 2, NW = 4, BN = 32 * FN, SLICE = 128;
     static_assert(Kb % SLICE == 0, "whole slices of 256 codes");
+    constexpr int slices = Kb / SLICE, PER_WAVE = (slices + NW - 1) / NW;
+    // One block of channels per wave: a ring of up to four slices, whose weights are all requested ahead of the wait and whose
+    // codes all at once behind it, so that a layer of K = 4096 has one memory latency behind its rotation instead of three; and from
+    // four slices a wave on the rotating blocks own no channels, since they would be the last to begin (T = 1, N = 4096: K = 4096
+    // 10.9 -> 9.9 us by the ring, 9.1 by both; K = 8192 13.9 -> 12.5 -> 11.9; T = 32, K = 4096 14.4 -> 13.2 -> 12.0.  K = 2048 8.8 ->
+    // 8.2 by the ring, no further by the other; beyond 256 blocks there the weights ahead of the wait hold the rotation up,
+    // 12.4 -> 12.7 us at N = 14336, so only those of the first slice leave).  With two blocks of channels per wave, where the
+    // weights ahead would be tens of MB, both lose (T = 1, K = 2048, N = 28672 15.2 -> 17.4 us).
+    constexpr bool RING = FN == 1 && PER_WAVE > 1;
+    static_assert(!RING || slices % NW == 0, "every wave has as many slices");
     extern __shared__ uint4 smem_u4[];
     int *note = reinterpret_cast<int *>(reinterpret_cast<char *>(smem_u4) + lds_main);   // [0] gave up
     const int tid = threadIdx.x;
@@ -66,11 +76,12 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
         // release writes this XCD's L2 back before the count can be seen.
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_add(&ctr[0], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (apart) return;
     }
 
     // ---- decode-shaped GEMM on channels [col0, col0 + BN) ----------------------------------------
     const int lane = tid & (kWave - 1), wave = tid / kWave, l32 = lane & 31, g = lane >> 5;
-    const int col0 = block * BN;
+    const int col0 = (apart ? block - groups : block) * BN;
     // The codes and steps were written by other workgroups of this launch, on other XCDs.  They
     // are read with agent-scope coherent loads (the sc1 form, which is what a relaxed agent-scope
     // atomic load compiles to, here 16 bytes wide through a buffer descriptor): such a load
@@ -88,8 +99,8 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0;
 
-    uint4 ra[2][4], rb[2][FN][4];
-    constexpr int slices = Kb / SLICE;
+    constexpr int SETS = RING && PER_WAVE >= 4 ? 4 : 2;
+    uint4 ra[SETS][4], rb[SETS][FN][4];
 #define SQ_DECODE_FETCH_B(BUF, SL)                                                                   \
     do {                                                                                             \
         _Pragma("unroll") for (int j = 0; j < FN; ++j)                                               \
@@ -116,12 +127,17 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
         }                                                                                            \
     } while (0)
 
-    // Wave w takes slices w, w+NW, ...; the weights of its first slice leave before the wait.  A block
+    // Wave w takes slices w, w+NW, ...; the weights of its first ones leave before the wait.  A block
     // that does not rotate holds them back for about 1.5 us, so that the first loads of the rotating
     // blocks (token rows, list, fragments) do not queue behind 14 MB of weights.
     int sl = wave;
     if (block >= groups) __builtin_amdgcn_s_sleep(60);
-    if (sl < slices) SQ_DECODE_FETCH_B(0, sl);
+    const bool ahead = PER_WAVE >= 4 || gridDim.x <= 256;
+    if constexpr (RING) {
+#pragma unroll
+        for (int u = 0; u < SETS; ++u)
+            if (u == 0 || ahead) SQ_DECODE_FETCH_B(u, wave + u * NW);
+    } else if (sl < slices) SQ_DECODE_FETCH_B(0, sl);
 
     if (tid == 0) {
         int spins = 0, gave_up = 0;
@@ -138,11 +154,30 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
     __syncthreads();
     const bool gave_up = note[0] != 0;
 
-    if (!gave_up && sl < slices) SQ_DECODE_FETCH_A(0, sl);
+    if constexpr (RING) {
+        if (!gave_up) {
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) {
+                if (u > 0 && !ahead) SQ_DECODE_FETCH_B(u, wave + u * NW);
+                SQ_DECODE_FETCH_A(u, wave + u * NW);
+            }
+        }
+    } else if (!gave_up && sl < slices) SQ_DECODE_FETCH_A(0, sl);
     // This block no longer looks at the count.  No value comes back and the add is queued behind the
     // loads just issued, so nothing waits for it; the loads behind it are not needed for a while.
     if (tid == 0) __hip_atomic_fetch_add(&ctr[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!gave_up) {
+        if constexpr (RING) {
+#pragma unroll
+            for (int u = 0; u < PER_WAVE; ++u) {
+                SQ_DECODE_MULTIPLY(u % SETS);
+                if (u + SETS < PER_WAVE) {
+                    SQ_DECODE_FETCH_B(u % SETS, wave + (u + SETS) * NW);
+                    SQ_DECODE_FETCH_A(u % SETS, wave + (u + SETS) * NW);
+                }
+            }
+            sl = slices;
+        }
         while (sl < slices) {
             if (sl + NW < slices) {
                 SQ_DECODE_FETCH_B(1, sl + NW);
@@ -189,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
     // like the other one).
     if (block == (int)gridDim.x - 1 && tid == 0) {
         int spins = 0;
-        while (__hip_atomic_load(&ctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)gridDim.x) {
+        while (__hip_atomic_load(&ctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)gridDim.x - (apart ? groups : 0)) {
             if (++spins > spin_limit) {
                 __hip_atomic_store(&ctr[3], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
@@ -224,8 +259,11 @@ sq_status launch_decode_layer(const __half *X, int64_t ldx, int T, const RotqPla
     // be reached)
     const int option = debug_option(SQ_DEBUG_DECODE_SPIN_LIMIT);
     const int spin_limit = option > 0 ? option : (1 << 20);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), lds, st, X, ldx, T, plan, F1, F2, Qx, sx, ctr, Qw, sw,
-                       N, Y, ldy, lds_main, spin_limit, sides);
+    // rotating blocks without channels (see the kernel); with one of them beside many others it is better to keep them
+    // (T = 1, K = 4096: N = 10240 13.5 us with channels, 13.1 without; N = 14336 14.7 / 15.8, N = 16000 15.7 / 16.1)
+    const int apart = FN == 1 && N1 * N2 >= 4096 && (groups > 1 || tiles <= 352);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(apart ? groups + tiles : tiles)), dim3(256), lds, st, X, ldx, T, plan, F1, F2, Qx, sx, ctr, Qw, sw,
+                       N, Y, ldy, lds_main, spin_limit, sides, apart);
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 

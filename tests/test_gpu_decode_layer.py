@@ -90,6 +90,26 @@ def test_decode_layer_other_shapes(n1, n2, T, N):
     assert torch.equal(lay.one_launch(L.X), lay.two_calls(L.X))
 
 
+@pytest.mark.parametrize("n1,n2,T,N", [
+    # two slices a wave: at most and more than 256 blocks
+    (32, 64, 2, 8192), (32, 64, 1, 8193), (32, 64, 32, 15000),
+    # four: rotating blocks without channels, and one with them beside more than 352 others
+    (64, 64, 1, 33), (64, 64, 32, 4097), (64, 64, 2, 11264), (64, 64, 2, 11265), (64, 64, 3, 11265), (64, 64, 1, 16383),
+    # eight
+    (64, 128, 1, 32), (64, 128, 31, 2050), (64, 128, 1, 14336), (64, 128, 2, 16383)])
+def test_decode_layer_slices_ahead_of_the_wait(n1, n2, T, N):
+    """One block of channels a wave: the forms that hold several slices, with and without rotating blocks that own channels,
+    on both sides of the rules; twice in a row on one workspace."""
+    print(f"case decode layer slices ahead {n1}x{n2} T={T} N={N}", flush=True)
+    import torch
+    cfg = synth.LayerConfig(f"a_{n1}x{n2}", T, n1, n2, N, 6, "normal", 2, 300.0, 0.01, 20.0, 0.02, 77 + n1 + n2)
+    L = synth.layer(cfg)
+    lay = Layer(L, N, T)
+    for _ in range(2):
+        assert torch.equal(lay.one_launch(L.X), lay.two_calls(L.X))
+        assert list(lay.counters()) == [0, 0, 0, 0]
+
+
 def test_decode_layer_wide_list_and_repeated_calls():
     """A list that touches all 128 columns (the instantiation with eight repair steps), and call
     after call on the same workspace without clearing it in between."""
