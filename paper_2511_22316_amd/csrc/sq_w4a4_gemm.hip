@@ -85,8 +85,8 @@ __device__ __forceinline__ void store_tile(const v16i (&acc)[FM][FN], int row_ba
 // every launch shape: deeper rings measured no faster, for large tiles or small).  The epilogue
 // stages the fp16 tile in LDS and writes it out in full 16-byte, row-contiguous stores.
 // ------------------------------------------------------------------------------------------
-// KG = 2: two groups of WM x WN waves share the block tile and split K in halves (group g walks
-// bytes [g Kb/2, (g+1) Kb/2) of every row); the second group's accumulators are added to the
+// KG = 2: two groups of WM x WN waves share the block tile and split K in halves (with an odd number
+// of K tiles both walk the middle one, the second group with zeros for its tokens' codes); the second group's accumulators are added to the
 // first's through LDS before the epilogue.  For tiles so small that the time is the walk over K.
 // LW > 0: LW more waves that do nothing but move the tiles (global -> LDS, the waits for them) while
 // the WM x WN others never issue a memory instruction inside the loop.  A global -> LDS load holds
@@ -125,12 +125,17 @@ __global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a4_gemm_ke
     const bool loader = LW > 0 && tid / kWave >= NW;
     const int kg = LW > 0 ? 0 : (tid / kWave) / NW, wave = (tid / kWave) % NW;
     const int wm = wave / WN, wn = wave % WN;
-    if constexpr (KG == 2) {                 // this group's half of K
-        Kb /= 2;
-        Qx += kg * Kb;
-        Qw += kg * Kb;
+    const int row_bytes = Kb;                // distance between rows in memory
+    bool repeats = false;
+    if constexpr (KG == 2) {
+        // This group's half of K.  With an odd number of tiles the second group begins with the last one of the first, and
+        // takes its tokens' codes for zeros there (below).
+        const int all = Kb / BKB, mine = (all + 1) / 2;
+        repeats = kg == 1 && (all & 1);
+        Qx += kg * (all - mine) * BKB;
+        Qw += kg * (all - mine) * BKB;
+        Kb = mine * BKB;
     }
-    const int row_bytes = KG * Kb;           // distance between rows in memory
     int bm, bn;
     tile_of_workgroup(tiles_m, tiles_n, bm, bn);
     const int row0 = bm * BM, col0 = bn * BN;
@@ -293,6 +298,14 @@ __global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a4_gemm_ke
         }
         block_barrier();                   // tile 0 has landed (the loading waves waited for it)
     } else {
+        if constexpr (KG == 2) {
+            if (repeats) {
+                wait_vmcnt<0>();           // this wave's part of the tokens' tile has landed: zeros in its place
+                uint4 *own = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(smem) + group_byte + wave_u * 1024) + lane;
+#pragma unroll
+                for (int g = 0; g < A_LOADS; ++g) own[g * NL * 64] = uint4{0, 0, 0, 0};
+            }
+        }
         wait_tile_and_barrier<LOADS, NS>(ktiles - 1);
         issue_tile(NS - 1, NS - 1, ktiles);
     }
@@ -675,7 +688,7 @@ static sq_status launch_main(const uint8_t *Qx, const float *sx, int T, int K, c
     constexpr size_t lds = (ring > out_tile ? ring : out_tile) + (size_t)(BM + BN) * 4;
     static_assert(lds <= (size_t)kMaxDynamicLds, "ring does not fit in LDS");
     auto kernel = w4a4_gemm_kernel<WM, WN, FM, FN, BKB, OCC, KG, NS, LW>;
-    if ((K / 2) % (KG * BKB) != 0) return SQ_ERR_SHAPE;      // every K group walks whole tiles
+    if ((K / 2) % BKB != 0) return SQ_ERR_SHAPE;             // every K group walks whole tiles
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return SQ_ERR_LAUNCH;
     const int tiles_m = (T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int vec_store = (((uintptr_t)Y & 15) == 0 && (ldy % 8) == 0) ? 1 : 0;
@@ -823,16 +836,18 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // the tile kernel are faster than its token blocks (T = 64, K = 8192, N = 28672: 48.7 -> 32.2 us).
     // With at most 256 tiles (one per CU) the tile kernel's two-K-group form is faster still: eight
     // waves per CU, each walking half of K (T = 64, K = N = 8192: 18.3 -> 16.7 us; T = 64, K = 8192,
-    // N = 28672: 31.2 -> 28.9 us).  It needs K % 512 == 0.
-    const bool two_k_groups = (K % 512) == 0;
+    // N = 28672: 31.2 -> 28.9 us).  With an odd number of K tiles one is walked for nothing, which pays from seven tiles on
+    // (T = 128, N = 4096, K = 11008 21.8 -> 17.0 us; T = 37, K = 7936, N = 8448 22.2 -> 13.2; K = 1280 5.35 / 5.44, K = 768 4.8 / 5.2),
+    // but not for at most 32 tokens (T = 18, K = 6912, N = 12224 11.1 / 12.3).
+    const bool even_k_groups = (K % 512) == 0, two_k_groups = even_k_groups || K >= 1536;
     if (choice < 0 && Ti > 32 && Ti <= 64 && N >= 8192 && N <= 64 * 256 && two_k_groups) choice = 14;
     // The same two tile forms win below 33 tokens as well where their tiles number 192 .. 256 (nearly one
     // per CU) and K is long: with 24576 .. 32768 channels and K >= 8192 the 64x128 tiles with two K groups
     // take 25.5 - 26.3 us for 1 .. 32 tokens at N = 28672 (the decode-shaped kernel 27.2 - 28.6 us up to 16
     // tokens, 64x64 tiles 29.6 - 32.0 us from 17 on; at K = 4096 all are within 0.5 us); with 10240 .. 16384
     // channels and 17 .. 32 tokens the 64x64 tiles with two K groups (T = 32, K = 4096, N = 14336: 10.7 -> 10.0 us).
-    if (choice < 0 && Ti <= 32 && N >= 64 * 384 && N <= 128 * 256 && two_k_groups && K >= 8192) choice = 15;
-    if (choice < 0 && Ti > 16 && Ti <= 32 && N >= 10240 && N <= 64 * 256 && two_k_groups) choice = 14;
+    if (choice < 0 && Ti <= 32 && N >= 64 * 384 && N <= 128 * 256 && even_k_groups && K >= 8192) choice = 15;
+    if (choice < 0 && Ti > 16 && Ti <= 32 && N >= 10240 && N <= 64 * 256 && even_k_groups) choice = 14;
     if (choice < 0 && Ti <= 64 && N >= 10240 && (Ti > 32 || (Ti > 16 && N >= 64 * 384))) {
         choice = (N >= 64 * 384 && Ti > 32) ? 11 : 10;
         if (choice == 11 && N <= 128 * 256 && two_k_groups) choice = 15;
@@ -892,8 +907,8 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         case 11: return sq::launch_main<2, 2, 1, 2, 128, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 16: return sq::launch_main<2, 4, 2, 2, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 17: return sq::launch_main<2, 2, 2, 4, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
-        case 14: if (K % 512 == 0) return sq::launch_main<2, 2, 1, 1, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
-        case 15: if (K % 512 == 0) return sq::launch_main<2, 2, 1, 2, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
+        case 14: return sq::launch_main<2, 2, 1, 1, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        case 15: return sq::launch_main<2, 2, 1, 2, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 7: if (Ti <= 32) return sq::launch_skinny<1, 1, 16>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 8: if (Ti <= 32) return sq::launch_skinny<1, 2, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 9: if (Ti <= 32) return sq::launch_skinny<1, 1, 8>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;

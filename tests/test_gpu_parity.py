@@ -490,6 +490,26 @@ def test_gemm_six_bit_float_kernel_without_accumulators(case, T, K, N, pad):
         assert np.array_equal(host(Y[0]).view(np.uint16), host(Y[1]).view(np.uint16))
 
 
+@pytest.mark.parametrize("case", [14, 15])
+@pytest.mark.parametrize("T,K,N", [(64, 256, 64), (33, 768, 130), (130, 1280, 257), (65, 1792, 100), (64, 11008, 128)])
+def test_gemm_two_k_groups_with_an_odd_number_of_tiles(oracle, case, T, K, N):
+    """Both K groups walk the middle K tile, the second one with zeros for its tokens' codes (one tile alone: all of its
+    share); codes that are zero nowhere, so that a tile counted twice shows in every sum."""
+    print(f"case gemm two K groups, odd tiles: {case} T={T} K={K} N={N}", flush=True)
+    import paper_2511_22316_amd as sq
+    g = np.random.default_rng(T + K)
+    sx, sw = g.uniform(0.05, 4.0, T).astype(np.float32), g.uniform(1e-5, 5e-4, N).astype(np.float32)
+    Qx, Qw = synth.random_codes(T, K, 61) | np.uint8(0x11), synth.random_codes(N, K, 62) | np.uint8(0x11)
+    Yo, acco = oracle.gemm(Qx, sx, Qw, sw)
+    sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, case + 1)
+    try:
+        Yg, accg = run_gemm(Qx, sx, Qw, sw)
+    finally:
+        sq.sq_debug_set_option(sq.binding.SQ_DEBUG_GEMM_LAUNCH_SHAPE, 0)
+    assert np.array_equal(accg, acco)
+    assert half_ulp_distance(Yg, Yo).max() <= 1
+
+
 def test_gemm_seeded_random_shapes_bit_exact(oracle):
     """Thirty shapes drawn from a seed (T up to 700, K a multiple of 32 up to 2304, N up to 3000, a
     third of them with at most 64 tokens): whatever kernel and launch shape the dispatcher picks,
