@@ -34,12 +34,14 @@ constexpr int kBuildSmallBytes = 6 * kBuildWaves * 4 + 5 * kMaxSide * 8 + 2 * SQ
 // ART candidates: the 2 P largest and the 2 P smallest channels of the calibration row
 constexpr int kMaxCandidates = 4 * SQ_MAX_GIVENS;
 static_assert(kMaxCandidates == 4 * kWave, "one wave holds them, four per lane");
-// two histograms of 256 bins, the candidates, one count per wave, results of the two searches, a counter, the channels of
+// the histograms, the candidates, one count per wave, results of the two searches, a counter, the channels of
 // the P largest and the P smallest in order
-constexpr int kSelectWords = 2 * 256 + kMaxCandidates + kBuildWaves + 4 + 2 + 2 * SQ_MAX_GIVENS;
+// (one histogram of 2048 bins, four words of padding behind every 32, or two of 256)
+constexpr int kFineBins = 2048, kFineWords = kFineBins / 32 * 36;
+constexpr int kSelectWords = kFineWords + kMaxCandidates + kBuildWaves + 4 + 2 + 2 * SQ_MAX_GIVENS;
 constexpr uint32_t kChannelMask = 0x3FFF;      // a candidate: its 15-bit magnitude above its channel
 static_assert(SQ_MAX_K <= kChannelMask + 1 && SQ_MAX_GIVENS <= kWave, "limits");
-static_assert(kBuildSmallBytes % 8 == 0, "the fp64 vectors behind the slots are 8-byte aligned");
+static_assert(kBuildSmallBytes % 16 == 0, "the fp64 vectors behind the slots are 8-byte aligned, the histograms 16");
 
 // workspace, in floats
 struct BuildWorkspace {
@@ -257,6 +259,37 @@ struct Largest {
     }
 };
 
+// One wave: the same over kFineBins bins, a lane 32 of them (at 36 l); `upto`: the count up to and with that bin.
+template <bool DOWN>
+__device__ __forceinline__ int fine_bin_reaching(const uint32_t *hist, uint32_t target, uint32_t &upto)
+{
+    const int lane = threadIdx.x & (kWave - 1), place = DOWN ? kWave - 1 - lane : lane;
+    static_assert(kFineBins == 32 * kWave, "32 bins a lane");
+    uint32_t n[32], sum = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(hist + 36 * place + 4 * u);
+        n[4 * u] = v.x, n[4 * u + 1] = v.y, n[4 * u + 2] = v.z, n[4 * u + 3] = v.w;
+        sum += v.x + v.y + v.z + v.w;
+    }
+    uint32_t run = sum;
+#pragma unroll
+    for (int d = 1; d < kWave; d *= 2) {
+        const uint32_t o = __shfl_up(run, d);
+        if (lane >= d) run += o;
+    }
+    const int owner = __ffsll((unsigned long long)__ballot(run - sum < target && target <= run)) - 1;
+    run -= sum;
+    int steps = 0;                                                 // bins in front of the one that reaches it
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+        const uint32_t c = n[DOWN ? 31 - u : u];
+        if (run < target) run += c, steps = u;
+    }
+    upto = __shfl(run, owner);
+    return 32 * __shfl(place, owner) + (DOWN ? 31 - __shfl(steps, owner) : __shfl(steps, owner));
+}
+
 __device__ __forceinline__ void magnitude_key(double v, uint32_t &hi, uint32_t &lo)
 {
     const uint64_t bits = (uint64_t)__double_as_longlong(fabs(v));
@@ -309,13 +342,14 @@ __device__ __forceinline__ double sum_tails(const double *vec, int n, double *ta
 //
 // What bounds it is the chain of P dependent ART steps.  Step p (from 0) has at most 2 p channels rewritten by the steps
 // before it, so what it picks is one of those or among the first 2 p + 1 in order of the calibration row as it was:
-// the 2 P largest and the 2 P smallest channels are all that can ever be chosen.  A radix selection on the
-// 15-bit magnitudes (two histograms of 256 bins, ties by channel) finds them, 5.6 us; where the two sets are disjoint, counting
-// puts the P outermost of either in order (1.5 us), and one wave takes the steps from those two ends, several at once
-// (T = 2048, K = 4096, P = 32: 0.18 us a step).  What that does not cover (generated values among the smallest, a row nearly all
+// the 2 P largest and the 2 P smallest channels are all that can ever be chosen.  A histogram of the 15-bit magnitudes in
+// 2048 bins finds the outer bins that hold them, 3 us; where the channels of those number more than 256 (P > 48, runs of equals), a
+// radix selection over two histograms of 256 bins, ties by channel, cuts them out exactly, 5.6 us.  Where the two sets are
+// disjoint, counting puts the P outermost of either in order (1.5 us), and one wave takes the steps from those two ends, several at
+// once (T = 2048, K = 4096, P = 32: 0.18 us a step).  What that does not cover (generated values among the smallest, a row nearly all
 // of one magnitude, at most 256 channels) one wave does with the candidates in registers and two reductions a step, 0.73 us each.
 // The whole kernel at that size: 91.5 us with a reduction over all channels by the whole workgroup in every step, 41.5 with
-// the reductions of one wave, 22 now.
+// the reductions of one wave, 22.1 with the steps from the ends, 19.6 with the finer histogram.
 // BY_ALL: that reduction instead, which is faster for few steps over few channels (steps_by_all).
 template <bool BY_ALL>
 __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
@@ -330,8 +364,8 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
     double(*target)[kMaxSide] = reinterpret_cast<double(*)[kMaxSide]>(vec[3]);                     // U1 | U2
     double *pair_a = vec[5], *pair_b = pair_a + SQ_MAX_GIVENS;     // (c_i, c_j) each ART angle is made for
     double *cvec = pair_b + SQ_MAX_GIVENS;
-    uint32_t *hist = reinterpret_cast<uint32_t *>(cvec + K + n1);  // [2][256]
-    uint32_t *cand = hist + 2 * 256;                               // [kMaxCandidates]
+    uint32_t *hist = reinterpret_cast<uint32_t *>(cvec + (K + n1 + 1) / 2 * 2);      // 16-byte aligned
+    uint32_t *cand = hist + kFineWords;                            // [kMaxCandidates]
     uint32_t *wave_ties = cand + kMaxCandidates;                   // [kBuildWaves]
     uint32_t *found = wave_ties + kBuildWaves;                     // bin and count before it, from above and from below
     uint32_t *n_cand = found + 4;
@@ -347,7 +381,7 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
         const uint32_t m = __float_as_uint(rowmax[t]);
         if (m > top || top_at == 0xFFFFFFFFu) top = m, top_at = (uint32_t)t;      // t ascends: ties keep the lower row
     }
-    if (tid < 2 * 256) hist[tid] = 0;
+    for (int w = tid; w < kFineWords; w += kBuildThreads) hist[w] = 0;
     if (tid == 0) *n_cand = 0;
     const int t_star = (int)block_arg<true>(top, 0u, top_at, slots_a);
 
@@ -364,10 +398,39 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
         if (in) cvec[at(k0 + e)] = (double)__half2float(h);
     }
     bool ordered = false;                                          // in_order holds the ends of two disjoint sets
+    bool chosen = false;
+    if (P > 0 && !BY_ALL && K > kMaxCandidates && P <= 48) {
+        // Bins of sixteen magnitudes: where all channels of the outer bins that hold the 2 P largest and the 2 P smallest
+        // number no more than a wave takes, they are the candidates.
+#pragma unroll
+        for (int e = 0; e < kMost; ++e)
+            if (key[e] != 0xFFFFu) atomicAdd(&hist[(key[e] >> 4) + (key[e] >> 9) * 4], 1u);
+        __syncthreads();
+        uint32_t upto;
+        if (wave == 0) {
+            const int b = fine_bin_reaching<true>(hist, 2 * (uint32_t)P, upto);
+            if (lane == 0) found[0] = (uint32_t)b, found[1] = upto;
+        } else if (wave == 1) {
+            const int b = fine_bin_reaching<false>(hist, 2 * (uint32_t)P, upto);
+            if (lane == 0) found[2] = (uint32_t)b, found[3] = upto;
+        }
+        __syncthreads();
+        const uint32_t bin_hi = found[0], bin_lo = found[2];
+        chosen = ordered = bin_hi > bin_lo && found[1] + found[3] <= (uint32_t)kMaxCandidates;
+        if (chosen) {
+#pragma unroll
+            for (int e = 0; e < kMost; ++e)
+                if (key[e] != 0xFFFFu && ((key[e] >> 4) >= bin_hi || (key[e] >> 4) <= bin_lo))
+                    cand[atomicAdd(n_cand, 1u)] = (key[e] << 14) | (uint32_t)(k0 + e);
+        } else if (tid < 2 * 256) {
+            hist[tid] = 0;
+        }
+        __syncthreads();
+    }
     if (P > 0 && !BY_ALL && K <= kMaxCandidates) {
         if (tid < K) cand[tid] = (uint32_t)tid;
         if (tid == 0) *n_cand = (uint32_t)K;
-    } else if (P > 0 && !BY_ALL) {
+    } else if (P > 0 && !BY_ALL && !chosen) {
         const uint32_t wanted = 2 * (uint32_t)P;
 #pragma unroll
         for (int e = 0; e < kMost; ++e)
@@ -425,24 +488,25 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
             if (key[e] == key_lo) take |= rank_lo++ < ties_lo;
             if (take) cand[atomicAdd(n_cand, 1u)] = (key[e] << 14) | (uint32_t)(k0 + e);
         }
-        __syncthreads();
-        // Four threads count how many candidates come before theirs, from above and from below (lower channels first).
         ordered = key_hi > key_lo;
-        if (ordered) {
-            const uint32_t self = (tid >> 2) < 4 * P ? cand[tid >> 2] : 0u;
-            uint32_t larger = 0, smaller = 0;                      // 16 bits each would do
+        __syncthreads();
+    }
+    // Four threads count how many candidates come before theirs, from above and from below (lower channels first).
+    if (ordered) {
+        const int n = (int)*n_cand;
+        const uint32_t self = (tid >> 2) < n ? cand[tid >> 2] : 0u;
+        uint32_t larger = 0, smaller = 0;
 #pragma unroll 8
-            for (int m = 0; m < P; ++m) {
-                const uint32_t o = cand[4 * m + (tid & 3)];
-                larger += (o ^ kChannelMask) > (self ^ kChannelMask);
-                smaller += o < self;
-            }
-            larger += __shfl_xor(larger, 1), smaller += __shfl_xor(smaller, 1);
-            larger += __shfl_xor(larger, 2), smaller += __shfl_xor(smaller, 2);
-            if ((tid & 3) == 0 && (tid >> 2) < 4 * P) {
-                if (larger < (uint32_t)P) in_order[larger] = self & kChannelMask;
-                if (smaller < (uint32_t)P) in_order[SQ_MAX_GIVENS + smaller] = self & kChannelMask;
-            }
+        for (int m = tid & 3; m < n; m += 4) {
+            const uint32_t o = cand[m];
+            larger += (o ^ kChannelMask) > (self ^ kChannelMask);
+            smaller += o < self;
+        }
+        larger += __shfl_xor(larger, 1), smaller += __shfl_xor(smaller, 1);
+        larger += __shfl_xor(larger, 2), smaller += __shfl_xor(smaller, 2);
+        if ((tid & 3) == 0 && (tid >> 2) < n) {
+            if (larger < (uint32_t)P) in_order[larger] = self & kChannelMask;
+            if (smaller < (uint32_t)P) in_order[SQ_MAX_GIVENS + smaller] = self & kChannelMask;
         }
     }
     __syncthreads();
@@ -725,13 +789,13 @@ __global__ __launch_bounds__(kMaxSide) void urt_columns_kernel(const float *__re
         if (r < n && c0 + c < n) R2[r * n + c0 + c] = __float2half_rn(s[c] * inv_sqrt_n2);
 }
 
-// A step over all channels by the whole workgroup takes 1.5 us at K = 512 and 6 us at 16384; the choice of the candidates and
-// their order take 7 us whatever P, and hardly more with every step (whole call in us, in order / all channels: K = 384, P = 4
-// 22.1 / 20.8; K = 1024, P = 4 22.5 / 22.4, P = 5 22.6 / 24.1; K = 2048, P = 3 25.5 / 24.4, P = 4 25.9 / 26.4; K = 8192, P = 2
-// 36.6 / 36.4, P = 3 37.0 / 40.2; K = 16384, P = 1 45.3 / 42.8, P = 2 45.6 / 48.7).
+// A step over all channels by the whole workgroup takes 1.2 us at K = 512 and 6 us at 16384; the choice of the candidates and
+// their order take 5 us whatever P, and hardly more with every step (whole call in us, in order / all channels: K = 288, P = 2
+// 18.7 / 17.7, P = 3 19.1 / 19.4; K = 2048, P = 2 22.6 / 22.6, P = 3 23.0 / 24.8; K = 4096, P = 1 23.3 / 22.3, P = 2 23.6 / 24.6;
+// K = 8192, P = 1 32.8 / 32.8; K = 16384, P = 1 41.2 / 43.0).
 bool steps_by_all(int32_t K, int32_t P)
 {
-    return K > kMaxCandidates && (P <= 1 || (P <= 2 && K <= 8192) || (P <= 3 && K <= 2048) || (P <= 4 && K <= 1024));
+    return K > kMaxCandidates && (P == 0 || (P == 1 && K <= 8192) || (P == 2 && K <= 2048));
 }
 
 bool build_shape_ok(int64_t T, int32_t K, int32_t n1, int32_t n2, int32_t P)
@@ -789,8 +853,8 @@ extern "C" sq_status sq_build_rotation(const void *X, int64_t T, int32_t K, int6
     hipLaunchKernelGGL(sq::row_absmax_kernel, dim3((unsigned)(row_groups < 4096 ? row_groups : 4096)), dim3(256), 0,
                        st, Xh, ldx, (int)T, K, w.rowmax);
     auto art = sq::steps_by_all(K, P) ? sq::art_urt_kernel<true> : sq::art_urt_kernel<false>;
-    // 143.5 KiB at the largest K
-    const size_t lds = sq::kBuildSmallBytes + (size_t)(K + n1) * sizeof(double) + sq::kSelectWords * sizeof(uint32_t);
+    // 151 KiB at the largest K
+    const size_t lds = sq::kBuildSmallBytes + (size_t)((K + n1 + 1) / 2 * 2) * sizeof(double) + sq::kSelectWords * sizeof(uint32_t);
     if (!sq::allow_large_lds(reinterpret_cast<const void *>(art))) return SQ_ERR_LAUNCH;
     hipLaunchKernelGGL(art, dim3(1), dim3(sq::kBuildThreads), lds, st, Xh, ldx, (int)T, K, n1, n2, P, inv_sqrt_n2,
                        w.rowmax, giv_i, giv_j, giv_theta, w.chain);

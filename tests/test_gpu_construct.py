@@ -142,7 +142,10 @@ def test_art_channels_among_equal_magnitudes(oracle, n1, n2, P, values):
     assert np.max(np.abs(g["giv_theta"].astype(np.float64) - gt)) <= 2e-6
 
 
-@pytest.mark.parametrize("n1,n2,P", [(9, 32, 64), (33, 16, 5), (64, 64, 32), (128, 128, 64)])
+@pytest.mark.parametrize("n1,n2,P", [(9, 32, 64), (33, 16, 5), (64, 64, 32), (128, 128, 64),
+                                     # an odd number of doubles ahead of the histograms; the longest list for bins of sixteen
+                                     # magnitudes and the shortest without; either side of the rule for short lists
+                                     (33, 32, 8), (64, 64, 48), (64, 64, 49), (32, 64, 2), (32, 64, 3), (64, 128, 1), (65, 128, 1)])
 @pytest.mark.parametrize("kind", ["clamped", "geometric", "narrow", "two_scales"])
 def test_art_steps_taken_several_at_once(oracle, n1, n2, P, kind):
     """Steps are taken together while nothing they make can come between the channels they take, and one by one by other means

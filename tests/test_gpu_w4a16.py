@@ -132,6 +132,23 @@ def test_w4a16_gemm_random_operands(oracle, T, K, N):
         assert np.array_equal(run_w4a16(Xi, Qw, s4), Yi)
 
 
+@pytest.mark.parametrize("T,K,N", [(3, 1024, 16400), (16, 2048, 16384), (2, 3072, 16390), (9, 4096, 20000), (8, 8192, 16400),
+                                   (1, 6144, 33000)])
+def test_w4a16_gemm_walks_that_begin_anywhere(oracle, T, K, N):
+    """Few tokens and many channels: neighbouring workgroups begin their walk over K in different rounds of four or eight
+    slices (one round, several, several blocks of channels a wave).  One-hot rows in every round and small integers: sums
+    without rounding, equal bits."""
+    print(f"case w4a16 gemm turned walks T={T} K={K} N={N}", flush=True)
+    g = np.random.default_rng(T + K + N)
+    Qw, s4 = synth.random_codes(N, K, 71), np.full(N, 0.25, np.float32)
+    X = np.zeros((T, K), np.float16)
+    X[np.arange(T), g.permutation(K)[:T]] = 1.0
+    X[0] = g.integers(-3, 4, K)
+    Y = oracle.gemm_w4a16(X, Qw, s4)
+    assert np.max(np.abs(Y.astype(np.float64))) < 2048
+    assert np.array_equal(run_w4a16(X, Qw, s4), Y)
+
+
 @pytest.mark.parametrize("shape", [1, 2])
 @pytest.mark.parametrize("T,K,N", [(16, 512, 512), (130, 320, 257), (300, 2048, 130), (257, 128, 520), (1, 64, 1)])
 def test_w4a16_gemm_every_tile_kernel(oracle, shape, T, K, N):
