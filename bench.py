@@ -51,14 +51,14 @@ MIN_BLOCKS = 3
 # summaries profiles/w4a4_gemm_<workload>.md and profiles/rotate_quantize_<workload>.md (FETCH_SIZE
 # and WRITE_SIZE, each scaled by what the counter reads for a plain 256 MiB copy: x2.000, x1.000).
 PROFILED_TRAFFIC = {
-    "attn_proj": {"gemm": {"fetch": 34077390, "write": 16810368},
-                  "rotate_quantize": {"fetch": 17090465, "write": 4227072}},
-    "mlp_down": {"gemm": {"fetch": 96835291, "write": 16804928},
-                 "rotate_quantize": {"fetch": 45757211, "write": 11337728}},
-    "decode": {"gemm": {"fetch": 118147247, "write": 458752},
-               "rotate_quantize": {"fetch": 690089, "write": 33024}},
-    "large_prefill": {"gemm": {"fetch": 1419501906, "write": 632612096},
-                      "rotate_quantize": {"fetch": 134755113, "write": 33816576}},
+    "attn_proj": {"gemm": {"fetch": 34031316, "write": 16795456},
+                  "rotate_quantize": {"fetch": 17071457, "write": 4227072}},
+    "mlp_down": {"gemm": {"fetch": 90645447, "write": 16795776},
+                 "rotate_quantize": {"fetch": 45754271, "write": 11337728}},
+    "decode": {"gemm": {"fetch": 118143816, "write": 458752},
+               "rotate_quantize": {"fetch": 669589, "write": 33024}},
+    "large_prefill": {"gemm": {"fetch": 1419403509, "write": 619908032},
+                      "rotate_quantize": {"fetch": 134747774, "write": 33816576}},
 }
 
 
