@@ -307,7 +307,8 @@ sq_status sq_decode_layer(const void *X, int64_t T, int32_t K, int64_t ldx,
  * sq_decode_layer_status -- has any sq_decode_layer call on this workspace given
  * up a wait (see the error word above)?  The one call of this library that
  * waits: it blocks until `stream` has finished all work enqueued so far, copies
- * the error word to the host and, if it was set, clears it.
+ * the error word to the host and, if it was set, clears it and the counters
+ * beside it, so that the next call on the workspace starts from zero.
  *   workspace  the workspace of the calls in question, or NULL for the array
  *              inside the library that sq_decode_layer_static uses (on the
  *              current device)

@@ -40,8 +40,10 @@ __device__ __forceinline__ void widen_codes(const uint4 w, v4i &first, v4i &seco
     second = v4i{(int)((w.z << 4) & m), (int)(w.z & m), (int)((w.w << 4) & m), (int)(w.w & m)};
 }
 
-// counters in the workspace: [0] token groups done, [1] workgroups with channels past their wait, [3] error word
+// counters in the workspace: [0] token groups done, [1] workgroups that touch [0] no more, [3] error word
 // (a wait gave up)
+constexpr int kSpinLimit = 1 << 20;      // polls of a wait, about a second
+
 template <int N1, int N2, int QS_MAX, int FN>
 __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
     const __half *__restrict__ X, int64_t ldx, int T, RotqPlan plan, const __half *__restrict__ F1,
@@ -76,7 +78,16 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
         // release writes this XCD's L2 back before the count can be seen.
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_add(&ctr[0], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        if (apart) return;
+        if (apart) {
+            // Counted among those that are through, as a block with channels is further down: the last block must not clear
+            // the counters before this one has added to them, also where it and all others gave up waiting for it.  The
+            // first add is complete ahead of the second; nobody waits for either.
+            if (tid == 0) {
+                wait_loads_le<0>();
+                __hip_atomic_fetch_add(&ctr[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            return;
+        }
     }
 
     // ---- decode-shaped GEMM on channels [col0, col0 + BN) ----------------------------------------
@@ -220,12 +231,12 @@ __global__ __launch_bounds__(256, 2) void decode_layer_kernel(
 #undef SQ_DECODE_MULTIPLY
 
     // The last block makes the counters ready for the next launch, once every workgroup is past its
-    // wait (they all were long ago when this block has finished its channels; the wait is bounded
-    // like the other one).
+    // wait, the rotating ones included (they all were long ago when this block has finished its channels).  Every other
+    // block gets there by itself, so the bound of this wait is kSpinLimit whatever the debug option says.
     if (block == (int)gridDim.x - 1 && tid == 0) {
         int spins = 0;
-        while (__hip_atomic_load(&ctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)gridDim.x - (apart ? groups : 0)) {
-            if (++spins > spin_limit) {
+        while (__hip_atomic_load(&ctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (int)gridDim.x) {
+            if (++spins > kSpinLimit) {
                 __hip_atomic_store(&ctr[3], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }
@@ -258,7 +269,7 @@ sq_status launch_decode_layer(const __half *X, int64_t ldx, int T, const RotqPla
     // sets another bound (test aid: the give-up path with a workspace whose "done" counter can never
     // be reached)
     const int option = debug_option(SQ_DEBUG_DECODE_SPIN_LIMIT);
-    const int spin_limit = option > 0 ? option : (1 << 20);
+    const int spin_limit = option > 0 ? option : kSpinLimit;
     // rotating blocks without channels (see the kernel); with one of them beside many others it is better to keep them
     // (T = 1, K = 4096: N = 10240 13.5 us with channels, 13.1 without; N = 14336 14.7 / 15.8, N = 16000 15.7 / 16.1)
     const int apart = FN == 1 && N1 * N2 >= 4096 && (groups > 1 || tiles <= 352);

@@ -557,7 +557,9 @@ extern "C" sq_status sq_decode_layer_status(void *workspace, void *stream)
     int32_t word = 0;
     if (hipMemcpy(&word, ws + 12, sizeof(word), hipMemcpyDeviceToHost) != hipSuccess) return SQ_ERR_LAUNCH;
     if (word == 0) return SQ_OK;
-    word = 0;
-    if (hipMemcpy(ws + 12, &word, sizeof(word), hipMemcpyHostToDevice) != hipSuccess) return SQ_ERR_LAUNCH;
+    // The counters with it: nothing runs on this workspace any more, and a launch whose last block gave up as well may have
+    // left them other than zero.
+    const int32_t zeros[4] = {0, 0, 0, 0};
+    if (hipMemcpy(ws, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess) return SQ_ERR_LAUNCH;
     return SQ_ERR_TIMEOUT;
 }

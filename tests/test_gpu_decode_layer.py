@@ -199,6 +199,41 @@ def test_decode_layer_gives_up_instead_of_waiting_forever():
     sq.sq_decode_layer_status(lay.ws)
 
 
+@pytest.mark.parametrize("n1,n2,T,N", [
+    # rotating blocks without channels: four slices a wave, eight; and with channels: two slices a wave, at most and more than
+    # 256 blocks
+    (64, 64, 32, 4097), (64, 64, 1, 200), (64, 128, 5, 1000), (32, 64, 16, 2050), (32, 64, 32, 9000)])
+def test_decode_layer_gives_up_in_the_forms_that_hold_several_slices(n1, n2, T, N):
+    """A count of tokens that cannot be reached: all blocks give up, with their weights on the way, and leave their channels
+    alone, at the smaller bound before the tokens are rotated.  The counters are cleared behind the last rotating block, late as
+    it is; and the status call clears counters that a launch left behind."""
+    print(f"case decode layer bounded wait {n1}x{n2} T={T} N={N}", flush=True)
+    import torch
+    import paper_2511_22316_amd as sq
+    cfg = synth.LayerConfig(f"w_{n1}x{n2}", T, n1, n2, N, 6, "normal", 2, 300.0, 0.01, 20.0, 0.02, 31 + n1 + n2)
+    L = synth.layer(cfg)
+    lay = Layer(L, N, T)
+    want = lay.two_calls(L.X)
+    for limit, left_behind in [(1, None), (40, [3, 7, 0, 1])]:
+        lay.ws[:16] = torch.from_numpy(np.array([-1000, 0, 0, 0], np.int32).view(np.uint8)).cuda()
+        sq.sq_debug_set_option(sq.binding.SQ_DEBUG_DECODE_SPIN_LIMIT, limit)
+        try:
+            Y = lay.one_launch(L.X)
+        finally:
+            sq.sq_debug_set_option(sq.binding.SQ_DEBUG_DECODE_SPIN_LIMIT, 0)
+        assert torch.all(Y == -5.0)
+        assert list(lay.counters()) == [0, 0, 0, 1]
+        if left_behind:
+            lay.ws[:16] = torch.from_numpy(np.array(left_behind, np.int32).view(np.uint8)).cuda()
+        with pytest.raises(sq.SQError) as e:
+            sq.sq_decode_layer_status(lay.ws)
+        assert e.value.code == 6
+        assert list(lay.counters()) == [0, 0, 0, 0]
+        sq.sq_decode_layer_status(lay.ws)
+        assert torch.equal(lay.one_launch(L.X), want)
+        assert list(lay.counters()) == [0, 0, 0, 0]
+
+
 def test_decode_layer_captured_in_a_graph_replays_correctly():
     """The call records into a HIP graph (it allocates nothing, clears nothing from the host and
     leaves its counters ready for the next launch): three replays in a row on fresh contents of
