@@ -482,6 +482,9 @@ __global__ __launch_bounds__(WM * 2 * KG * kWave, WM * KG / 2) void w4a4_gemm_fp
                         for (int e = 8 * h; e < 8 * h + 8; e += 2) {
                             run[(e / 4) & 1][(e / 2) & 1] = scaled_pair(x[e] * sxt[i], swn[e], x[e + 1] * sxt[i], swn[e + 1]);
                         }
+                        // The swaps read a register two wait states behind the instruction that writes it at the earliest.  The
+                        // compiler keeps that distance from the instructions it knows, not from those in assembly.
+                        asm("s_nop 1" : "+v"(run[0][0]), "+v"(run[0][1]), "+v"(run[1][0]), "+v"(run[1][1]));
                         // lower half-wave: both halves of the first run; upper half-wave: of the second
                         const v2u s0 = __builtin_amdgcn_permlane32_swap(run[0][0], run[1][0], false, false);
                         const v2u s1 = __builtin_amdgcn_permlane32_swap(run[0][1], run[1][1], false, false);
