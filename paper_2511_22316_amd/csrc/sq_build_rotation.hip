@@ -562,7 +562,8 @@ __global__ __launch_bounds__(kBuildThreads) void art_urt_kernel(
             while (p0 < P) {
                 const uint32_t bh = __shfl(low_hi, lane + p0), cj = __shfl(low_ch, lane + p0), ci = largest.channel;
                 const double a = largest.value(), b = value(bh, 0), first = value(lane_of(largest.hi, 0), lane_of(largest.lo, 0));
-                if (first == 0.0) break;
+                // no value left, or one that is not finite (the square root below is for finite ones): the other steps' turn
+                if (first == 0.0 || lane_of(largest.hi, 0) >= 0x7FF00000u) break;
                 int r = __popcll(__ballot(lane < P - p0 && a > 0.73 * first && 4.0 * b <= first && bh < least));
                 if (r == 0) {
                     if (lane_of(bh, 0) >= least) break;

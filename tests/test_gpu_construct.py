@@ -173,6 +173,20 @@ def test_art_steps_taken_several_at_once(oracle, n1, n2, P, kind):
     assert np.max(np.abs(g["giv_theta"].astype(np.float64) - gt)) <= 2e-6
 
 
+@pytest.mark.parametrize("n1,n2,P", [(64, 64, 32), (64, 64, 64), (33, 32, 8), (16, 32, 1), (8, 16, 5)])
+def test_art_steps_on_a_row_with_infinities(oracle, n1, n2, P):
+    """Activations beyond fp16 in the calibration row.  What a step makes of one is infinite, so that the steps go on among
+    infinite channels, each with the next smallest one, at an angle of -pi/4 (or pi from there): channels as the oracle's."""
+    print(f"case ART infinities {n1}x{n2} P={P}", flush=True)
+    x = np.random.default_rng(n1 + P).standard_normal(n1 * n2).astype(np.float16)
+    x[[7, 40, 90]] = [-np.inf, np.inf, -np.inf]
+    g = run_build(x[None], n1, n2, P)
+    with np.errstate(all="ignore"):
+        gi, gj, gt, *_ = oc.art_select(x, P)
+    assert np.array_equal(g["giv_i"], gi) and np.array_equal(g["giv_j"], gj)
+    assert np.all(np.isfinite(gt)) and np.max(np.abs(g["giv_theta"].astype(np.float64) - gt)) <= 2e-6
+
+
 def test_build_rotation_full_size_and_its_use_on_the_hot_path(oracle):
     """Full attn_proj calibration batch; then the constructed list and factors drive the online
     kernel, checked against the oracle's rotation with the same list and factors."""
