@@ -85,9 +85,10 @@ __device__ __forceinline__ void store_tile(const v16i (&acc)[FM][FN], int row_ba
 // every launch shape: deeper rings measured no faster, for large tiles or small).  The epilogue
 // stages the fp16 tile in LDS and writes it out in full 16-byte, row-contiguous stores.
 // ------------------------------------------------------------------------------------------
-// KG = 2: two groups of WM x WN waves share the block tile and split K in halves (with an odd number
-// of K tiles both walk the middle one, the second group with zeros for its tokens' codes); the second group's accumulators are added to the
-// first's through LDS before the epilogue.  For tiles so small that the time is the walk over K.
+// KG = 2: two groups of WM x WN waves share the block tile and split K in halves; the second group's accumulators are
+// added to the first's through LDS before the epilogue.  For tiles so small that the time is the walk over K.
+// ODD: an odd number of K tiles.  Both groups walk the middle one, the second with zeros for its tokens' codes.  (A kernel of its
+// own: with one for both, even numbers paid up to 3 % for another schedule of the loop, T = 100, K = 12288, N = 3000 17.3 -> 17.8 us.)
 // LW > 0: LW more waves that do nothing but move the tiles (global -> LDS, the waits for them) while
 // the WM x WN others never issue a memory instruction inside the loop.  A global -> LDS load holds
 // the wave that issues it for some tens of ns, in which it issues no MFMA either; with the loads
@@ -95,7 +96,7 @@ __device__ __forceinline__ void store_tile(const v16i (&acc)[FM][FN], int row_ba
 // timing-only build without the weights' loads: 28.3 against 31.5 us with them cache-hot).  The
 // loading waves cost registers (every wave of a workgroup gets the same allocation), so this form
 // needs at most 168 of them per wave: three waves per SIMD.
-template <int WM, int WN, int FM, int FN, int BKB, int OCC, int KG, int NS, int LW>
+template <int WM, int WN, int FM, int FN, int BKB, int OCC, int KG, int NS, int LW, bool ODD>
 __global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a4_gemm_kernel(
     const uint8_t *__restrict__ Qx, const float *__restrict__ sx, int T, int Kb,
     const uint8_t *__restrict__ Qw, const float *__restrict__ sw, int N, __half *__restrict__ Y,
@@ -104,6 +105,7 @@ __global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a4_gemm_ke
     static_assert(NS >= 3 && NS <= 6, "ring of three to six stages");
     static_assert(KG == 1 || KG == 2, "one or two K groups");
     static_assert(LW == 0 || KG == 1, "loading waves: one K group");
+    static_assert(!ODD || KG == 2, "one K group walks any number of tiles");
     constexpr int NW = WM * WN;                                // NW: multiplying waves of one K group
     constexpr int NTC = KG * NW * kWave, NT = NTC + LW * kWave;  // multiplying threads; all threads
     constexpr int NL = LW > 0 ? LW : NW;                       // waves that share the loads of a tile
@@ -125,17 +127,14 @@ __global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a4_gemm_ke
     const bool loader = LW > 0 && tid / kWave >= NW;
     const int kg = LW > 0 ? 0 : (tid / kWave) / NW, wave = (tid / kWave) % NW;
     const int wm = wave / WN, wn = wave % WN;
-    const int row_bytes = Kb;                // distance between rows in memory
-    bool repeats = false;
-    if constexpr (KG == 2) {
-        // This group's half of K.  With an odd number of tiles the second group begins with the last one of the first, and
-        // takes its tokens' codes for zeros there (below).
-        const int all = Kb / BKB, mine = (all + 1) / 2;
-        repeats = kg == 1 && (all & 1);
-        Qx += kg * (all - mine) * BKB;
-        Qw += kg * (all - mine) * BKB;
-        Kb = mine * BKB;
+    const int all_bytes = Kb;
+    if constexpr (KG == 2) {                 // this group's half of K
+        const int begin = ODD ? (Kb / BKB - 1) / 2 * BKB : Kb / 2;      // where the second group begins
+        Kb = ODD ? Kb - begin : begin;
+        Qx += kg * begin;
+        Qw += kg * begin;
     }
+    const int row_bytes = ODD ? all_bytes : KG * Kb;         // distance between rows in memory
     int bm, bn;
     tile_of_workgroup(tiles_m, tiles_n, bm, bn);
     const int row0 = bm * BM, col0 = bn * BN;
@@ -298,8 +297,8 @@ __global__ __launch_bounds__((KG * WM * WN + LW) * kWave, OCC) void w4a4_gemm_ke
         }
         block_barrier();                   // tile 0 has landed (the loading waves waited for it)
     } else {
-        if constexpr (KG == 2) {
-            if (repeats) {
+        if constexpr (ODD) {
+            if (kg == 1) {
                 wait_vmcnt<0>();           // this wave's part of the tokens' tile has landed: zeros in its place
                 uint4 *own = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(smem) + group_byte + wave_u * 1024) + lane;
 #pragma unroll
@@ -677,7 +676,7 @@ __global__ __launch_bounds__(256) void w4a4_gemm_generic_kernel(
     store_tile<FM, FN>(acc, row0 + wm * FM * 32, col0 + wn * FN * 32, lane, sx, sw, T, N, Y, ldy, acc_dbg);
 }
 
-template <int WM, int WN, int FM, int FN, int BKB, int OCC, int KG = 1, int NS = 3, int LW = 0>
+template <int WM, int WN, int FM, int FN, int BKB, int OCC, int KG = 1, int NS = 3, int LW = 0, bool ODD = false>
 static sq_status launch_main(const uint8_t *Qx, const float *sx, int T, int K, const uint8_t *Qw,
                              const float *sw, int N, __half *Y, int64_t ldy, int32_t *acc_dbg,
                              hipStream_t st)
@@ -687,8 +686,8 @@ static sq_status launch_main(const uint8_t *Qx, const float *sx, int T, int K, c
     // the epilogue reuses the ring for the output tile; the scales sit behind both
     constexpr size_t lds = (ring > out_tile ? ring : out_tile) + (size_t)(BM + BN) * 4;
     static_assert(lds <= (size_t)kMaxDynamicLds, "ring does not fit in LDS");
-    auto kernel = w4a4_gemm_kernel<WM, WN, FM, FN, BKB, OCC, KG, NS, LW>;
-    if ((K / 2) % BKB != 0) return SQ_ERR_SHAPE;             // every K group walks whole tiles
+    auto kernel = w4a4_gemm_kernel<WM, WN, FM, FN, BKB, OCC, KG, NS, LW, ODD>;
+    if ((K / 2) % BKB != 0 || (K / 2 / BKB % KG != 0) != ODD) return SQ_ERR_SHAPE;   // every K group walks whole tiles
     if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return SQ_ERR_LAUNCH;
     const int tiles_m = (T + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int vec_store = (((uintptr_t)Y & 15) == 0 && (ldy % 8) == 0) ? 1 : 0;
@@ -837,7 +836,7 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // With at most 256 tiles (one per CU) the tile kernel's two-K-group form is faster still: eight
     // waves per CU, each walking half of K (T = 64, K = N = 8192: 18.3 -> 16.7 us; T = 64, K = 8192,
     // N = 28672: 31.2 -> 28.9 us).  With an odd number of K tiles one is walked for nothing, which pays from seven tiles on
-    // (T = 128, N = 4096, K = 11008 21.8 -> 17.0 us; T = 37, K = 7936, N = 8448 22.2 -> 13.2; K = 1280 5.35 / 5.44, K = 768 4.8 / 5.2),
+    // (T = 128, N = 4096, K = 11008 21.8 -> 16.3 us; T = 37, K = 7936, N = 8448 22.2 -> 12.9; K = 1280 5.35 / 5.44, K = 768 4.8 / 5.2),
     // but not for at most 32 tokens (T = 18, K = 6912, N = 12224 11.1 / 12.3).
     const bool even_k_groups = (K % 512) == 0, two_k_groups = even_k_groups || K >= 1536;
     if (choice < 0 && Ti > 32 && Ti <= 64 && N >= 8192 && N <= 64 * 256 && two_k_groups) choice = 14;
@@ -907,8 +906,12 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
         case 11: return sq::launch_main<2, 2, 1, 2, 128, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 16: return sq::launch_main<2, 4, 2, 2, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 17: return sq::launch_main<2, 2, 2, 4, 128, 1, 1, 3, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
-        case 14: return sq::launch_main<2, 2, 1, 1, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
-        case 15: return sq::launch_main<2, 2, 1, 2, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        case 14:
+            if (even_k_groups) return sq::launch_main<2, 2, 1, 1, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+            return sq::launch_main<2, 2, 1, 1, 128, 1, 2, 3, 0, true>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+        case 15:
+            if (even_k_groups) return sq::launch_main<2, 2, 1, 2, 128, 1, 2>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
+            return sq::launch_main<2, 2, 1, 2, 128, 1, 2, 3, 0, true>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
         case 7: if (Ti <= 32) return sq::launch_skinny<1, 1, 16>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 8: if (Ti <= 32) return sq::launch_skinny<1, 2, 4>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
         case 9: if (Ti <= 32) return sq::launch_skinny<1, 1, 8>(Qx, sx, Ti, K, Qw, sw, N, Yh, ldy, acc_dbg, st); break;
