@@ -835,11 +835,13 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // the tile kernel are faster than its token blocks (T = 64, K = 8192, N = 28672: 48.7 -> 32.2 us).
     // With at most 256 tiles (one per CU) the tile kernel's two-K-group form is faster still: eight
     // waves per CU, each walking half of K (T = 64, K = N = 8192: 18.3 -> 16.7 us; T = 64, K = 8192,
-    // N = 28672: 31.2 -> 28.9 us).  With an odd number of K tiles one is walked for nothing, which pays from seven tiles on
-    // (T = 128, N = 4096, K = 11008 21.8 -> 16.3 us; T = 37, K = 7936, N = 8448 22.2 -> 12.9; K = 1280 5.35 / 5.44, K = 768 4.8 / 5.2),
+    // N = 28672: 31.2 -> 28.9 us).  With an odd number of K tiles one is walked for nothing: 64x64 tiles pay from seven
+    // tiles on (T = 128, N = 4096, K = 11008 21.8 -> 16.3 us; T = 37, K = 7936, N = 8448 22.2 -> 12.9; 121 shapes, the best one-group form
+    // is 1: 3 tiles 1.01 - 1.09, 5 0.99 - 1.04, 7 0.96 - 1.00, 9 0.93 - 0.97), 64x128 tiles, a pair of which shares a CU without
+    // groups, from eleven on (7 tiles 1.03 - 1.05, 9 1.00 - 1.03, 11 0.97 - 1.00, 13 0.96; T = 987, K = 1792, N = 1248 8.2 / 7.9 us);
     // but not for at most 32 tokens (T = 18, K = 6912, N = 12224 11.1 / 12.3).
-    const bool even_k_groups = (K % 512) == 0, two_k_groups = even_k_groups || K >= 1536;
-    if (choice < 0 && Ti > 32 && Ti <= 64 && N >= 8192 && N <= 64 * 256 && two_k_groups) choice = 14;
+    const bool even_k_groups = (K % 512) == 0, two_groups_64 = even_k_groups || K >= 1792, two_groups_128 = even_k_groups || K >= 2816;
+    if (choice < 0 && Ti > 32 && Ti <= 64 && N >= 8192 && N <= 64 * 256 && two_groups_64) choice = 14;
     // The same two tile forms win below 33 tokens as well where their tiles number 192 .. 256 (nearly one
     // per CU) and K is long: with 24576 .. 32768 channels and K >= 8192 the 64x128 tiles with two K groups
     // take 25.5 - 26.3 us for 1 .. 32 tokens at N = 28672 (the decode-shaped kernel 27.2 - 28.6 us up to 16
@@ -849,7 +851,7 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     if (choice < 0 && Ti > 16 && Ti <= 32 && N >= 10240 && N <= 64 * 256 && even_k_groups) choice = 14;
     if (choice < 0 && Ti <= 64 && N >= 10240 && (Ti > 32 || (Ti > 16 && N >= 64 * 384))) {
         choice = (N >= 64 * 384 && Ti > 32) ? 11 : 10;
-        if (choice == 11 && N <= 128 * 256 && two_k_groups) choice = 15;
+        if (choice == 11 && N <= 128 * 256 && two_groups_128) choice = 15;
     }
     // (with the token rows in LDS -- they fit up to 64 KB -- eight waves on 32 channels beat four waves on 64:
     // T = 8, K = 8192, N = 28672 27.1 against 27.4 us, and 27.6 us for the latter without the rows in LDS)
@@ -859,12 +861,14 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // Few tokens times few output channels: even 128x128 tiles would be too few for 256 CUs, and the
     // time is one workgroup's walk over K.  64x64 tiles, else 64x128 tiles, while they number at most one per CU
     // (T = 200, K = N = 4096: 13.3 -> 11.6 us against 128x128 tiles; T = 384 16.8 -> 15.5; T = 675, K = 2048, N = 2752, 132 tiles
-    // of 128x128 or 242 of 64x128: 12.1 -> 8.7).  Without two K groups they run two per CU, and pay up to 128 tiles of 128x128.
+    // of 128x128 or 242 of 64x128: 12.1 -> 8.7).  Without two K groups 64x64 tiles run two per CU, and pay up to 64 tiles of
+    // 128x128; 64x128 tiles pay as with them (K = 768 - 2304, odd numbers of K tiles, 132 - 170 tiles of 128x128: 0.69 - 0.76 of
+    // their time).
     if (choice < 0) {
         const int64_t n64 = (int64_t)((Ti + 63) / 64) * ((N + 63) / 64), n64x128 = (int64_t)((Ti + 63) / 64) * ((N + 127) / 128);
         const int64_t n128 = (int64_t)((Ti + 127) / 128) * ((N + 127) / 128);
-        if (two_k_groups ? n64 <= 256 : n128 <= 64) choice = two_k_groups ? 14 : 10;
-        else if (two_k_groups ? n64x128 <= 256 : n128 <= 128) choice = two_k_groups ? 15 : 11;
+        if (two_groups_64 ? n64 <= 256 : n128 <= 64) choice = two_groups_64 ? 14 : 10;
+        else if (n64x128 <= 256) choice = two_groups_128 ? 15 : 11;
     }
     // Many tokens or channels: the tile that needs the least time for its rounds of 256 workgroups, one per CU.  A full round
     // takes fixed + slope per 256 codes of K; a last round of n tiles (5 + n / 256) / 6 of that, since fewer CUs at work run
