@@ -873,29 +873,34 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     // Many tokens or channels: the tile that needs the least time for its rounds of 256 workgroups, one per CU.  A full round
     // takes fixed + slope per 256 codes of K; a last round of n tiles (5 + n / 256) / 6 of that, since fewer CUs at work run
     // at a higher clock.  The constants are the best fit to 314 shapes (T = 128 .. 3100, K = 1024 .. 12288, N = 512 .. 30000),
-    // in ns; the choice takes at most 3 % longer than the best of the forms there (but where rows of Y begin at any element,
-    // below), 0.9 % in the mean.  The 6-bit forms have the smaller slope, for power; the int8 ones the shorter start.
+    // in ns; on 211 others (T = 65 .. 3500, K = 768 .. 14336) the choice takes 0.13 % longer than the best of these forms in the
+    // mean and at most 5 %.  The 6-bit forms have the smaller slope, for power; the int8 ones the shorter start.
+    // Where rows of Y begin at any element, all epilogues store two bytes at a time: an int8 tile row by row, 0.19 ns per
+    // entry; a 6-bit one 32 rows at a time, 0.07 ns, or 0.17 ns if these rows lie within two elements of a multiple of 128
+    // bytes apart and meet in the same memory channels.  (137 shapes with Y one element off or N odd: 0.06 % longer than the best form in
+    // the mean, at most 4 %; on 176 others at most 8 %.  With 4 us for the int8 forms alone some single rounds went to the slower
+    // form: T = 217, K = 1024, N = 11456 12.1 -> 14.3 us, T = 1578, K = 2048, N = 1536 15.5 -> 17.3.)
     if (choice < 0) {
-        auto time = [&](int rows, int columns, int64_t fixed, int64_t slope) {
+        const bool unaligned = ((uintptr_t)Y & 15) != 0 || (ldy % 8) != 0, same_channels = (ldy + 2) % 64 <= 4;
+        auto time = [&](int rows, int columns, int64_t fixed, int64_t slope, bool six_bit) {
             const int64_t n = (int64_t)((Ti + rows - 1) / rows) * ((N + columns - 1) / columns), rest = n % 256;
-            return (fixed + slope * (K / 256)) * (1536 * (n / 256) + (rest ? 1280 + rest : 0));
+            const int64_t stores = unaligned ? rows * columns * (!six_bit ? 19 : same_channels ? 17 : 7) / 100 : 0;
+            return (fixed + stores + slope * (K / 256)) * (1536 * (n / 256) + (rest ? 1280 + rest : 0));
         };
         // int8: 128x128 tiles (four waves, K tiles twice as long) while 128x256 ones would leave half of the CUs idle; else 128x256
         // with four loading waves (32.0 -> 31.5 us at T = 2048, K = N = 4096 against the loads in the multiplying waves), eight
         // multiplying waves of 64x64 or, with long K, four of 64x128 (T = 2048, N = 4096, K = 65792 396 -> 376 us); or 256x256.
-        // The int8 epilogue stores rows that begin at any element two bytes at a time: 4 us a round.
         const int64_t n_small = (int64_t)((Ti + 127) / 128) * ((N + 255) / 256), n_large = (int64_t)((Ti + 255) / 256) * ((N + 255) / 256);
-        const int64_t unaligned = ((uintptr_t)Y & 15) == 0 && (ldy % 8) == 0 ? 0 : 4000;
         int64_t best;
-        if (n_small <= 128) choice = 5, best = time(128, 128, 6200 + unaligned, 900);
-        else if (20 * ((n_small + 255) / 256) > 37 * ((n_large + 255) / 256)) choice = 4, best = time(256, 256, 12440 + unaligned, 2361);
-        else choice = K >= 6144 ? 17 : 16, best = time(128, 256, 8120 + unaligned, 1319);
+        if (n_small <= 128) choice = 5, best = time(128, 128, 6200, 900, false);
+        else if (20 * ((n_small + 255) / 256) > 37 * ((n_large + 255) / 256)) choice = 4, best = time(256, 256, 12440, 2361, false);
+        else choice = K >= 6144 ? 17 : 16, best = time(128, 256, 8120, 1319, false);
         const struct { int choice; sq::Fp6Tile tile; int64_t fixed, slope; } forms[] = {
             {20, sq::Fp6Tile::k128x192, 7590, 866}, {18, sq::Fp6Tile::k128x256, 10330, 931},
             {21, sq::Fp6Tile::k256x192, 10060, 1536}, {19, sq::Fp6Tile::k256x256, 12520, 1692}};
         for (const auto &form : forms) {
             if (!sq::w4a4_fp6_takes(form.tile, Ti, K, N)) continue;
-            const int64_t t = time(sq::fp6_tile_tokens(form.tile), sq::fp6_tile_channels(form.tile), form.fixed, form.slope);
+            const int64_t t = time(sq::fp6_tile_tokens(form.tile), sq::fp6_tile_channels(form.tile), form.fixed, form.slope, true);
             if (t < best) choice = form.choice, best = t;
         }
     }
