@@ -533,7 +533,11 @@ constexpr int kXldsWaves = 8;
 // 16-byte chunks of the rows per thread, at most
 constexpr int kXldsChunks = (kMaxDynamicLds / 16 + kXldsWaves * kWave - 1) / (kXldsWaves * kWave);
 
-template <bool W3, int D>
+// does the walk over K begin with another round in neighbouring workgroups?  (see the kernel)
+__host__ __device__ constexpr bool w4a16_xlds_turns(int K) { return K % 8192 == 0 && K < 32768; }
+
+// TURNS: it may
+template <bool W3, int D, bool TURNS>
 __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
     const __half *__restrict__ X, int64_t ldx, int T, int K, const uint8_t *__restrict__ Qw,
     const float *__restrict__ sw, int N, __half *__restrict__ Y, int64_t ldy)
@@ -576,11 +580,15 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
     // what fits in LDS), then the first D slices of codes; loads complete in order, so the rows
     // can be written to LDS while the codes are still on their way.  All requests are
     // unconditional (clamped), which keeps the compiler's count of outstanding loads exact.
-    // The walk over K begins with another round in neighbouring workgroups, which sit on different XCDs: rows of codes lie a
-    // power of two apart for the usual K, and with every wave of the chip at the same place of its row the requests of a
-    // moment meet in a few memory channels (T = 8, N = 28672: K = 8192 31.6 -> 27.7 us; K = 4096 19.5 -> 19.1, K = 11264, K = 14336 the
-    // same within 1 %; by slices instead of whole rounds, or by wave: slower again).
-    const int turn = (int)blockIdx.x % (slices / D) * D;
+    // Where rows of codes lie a multiple of 4 KB apart, every wave of the chip at the same place of its row means that the requests of
+    // a moment meet in a few memory channels.  The walk over K begins with another round in neighbouring workgroups there, which
+    // sit on different XCDs (N = 28672, us: T = 8, K = 8192 31.6 -> 27.7; T = 1, K = 16384 50.8 -> 46.2, K = 24576 72.4 -> 63.5; by slices
+    // instead of whole rounds, or by wave: slower again).  Not from 16 KB on (T = 1: K = 32768 99 / 123, K = 65536 189 / 195), nor
+    // elsewhere (T = 1, N = 32000: K = 3072 14.5 / 14.7, K = 4096 19.3 / 19.6, K = 5120 20.0 / 21.2; K = 14336, N = 16384 26.8 / 27.4).
+    // The three-bit storage, whose rows of these K lie 3 KB and more apart, goes along for the same order of additions (T = 1:
+    // N = 16384, K = 8192 17.4 -> 17.0, K = 24576 37.5 -> 35.8; N = 50000, K = 8192 46.7 / 48.9).
+    // A channel's sum is rounded in the order of its workgroup's walk, so its last bit may depend on the channel's number there.
+    const int turn = TURNS && w4a16_xlds_turns(K) ? (int)blockIdx.x % (slices / D) * D : 0;
     const int chunks_per_row = K / 8, chunks = T * chunks_per_row;
     {
         uint4 xv[kXldsChunks];
@@ -643,7 +651,7 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
         }
     };
     v8h ta[2][8];                                      // token chunks of this slice and of the next
-    read_tokens(ta[0], turn);
+    read_tokens(ta[0], TURNS ? turn : 0);
     for (int bi = 0; bi < my_blocks; ++bi) {
         const int n = 16 * (first + bi * step) + l16;
         const float step_n = sw[min(n, N - 1)];
@@ -651,23 +659,25 @@ __global__ __launch_bounds__(kXldsWaves *kWave) void w4a16_gemm_xlds_kernel(
         const uint8_t *row_after = row_of(bi + 1 < my_blocks ? bi + 1 : bi);
         acc0 = v4f{0.f, 0.f, 0.f, 0.f};
         acc1 = v4f{0.f, 0.f, 0.f, 0.f};
-        int S0 = turn;
+        int place = turn;
         for (int done = 0; done < slices; done += D) {
             const bool wrap = done + D >= slices;          // the round D slices ahead opens the next block
             const uint8_t *row_n = wrap ? row_after : row;
+            const int S0 = TURNS ? place : done;
             const int after = S0 + D == slices ? 0 : S0 + D;       // behind the last round of a block: its first one, `turn`, again
-            const int S_n = wrap && bi + 1 == my_blocks ? S0 : after;
+            // (without turns the same said by `wrap`, of which the compiler makes another loop: T = 1, K = 5120, N = 32000 20.9 / 20.0 us)
+            const int S_n = TURNS ? (wrap && bi + 1 == my_blocks ? S0 : after) : wrap ? (bi + 1 < my_blocks ? 0 : S0) : S0 + D;
 #pragma unroll
             for (int i = 0; i < D; ++i) {
                 // the slice after this one (the token rows are the same for every block)
-                read_tokens(ta[(i + 1) & 1], i + 1 == D ? after : S0 + i + 1);
+                read_tokens(ta[(i + 1) & 1], TURNS ? (i + 1 == D ? after : S0 + i + 1) : (i + 1 == D && wrap) ? 0 : S0 + i + 1);
                 multiply(rb[i], ta[i & 1]);
                 issue(rb[i], row_n, S_n + i);
                 // keep the requests here, one slice behind another: collected at the end of the
                 // round (where the scheduler puts them) they would all be waited for at once
                 __builtin_amdgcn_sched_barrier(0);
             }
-            S0 = after;
+            place = after;
         }
         // 16 x 16 accumulator layout: lane holds channel l16, register r holds token 4 q + r
 #pragma unroll
@@ -686,17 +696,18 @@ sq_status launch_w4a16_xlds(const __half *X, int64_t ldx, int T, int K, const ui
     const int nblocks = (N + 15) / 16;
     const int grid = nblocks < 256 ? nblocks : 256;
     const size_t lds = (size_t)T * (2 * K + kXldsRowPad);
-    // eight slices in flight per wave where the slices of a row come in eights (K % 2048 == 0), else four
-    if ((K / 256) % 8 == 0) {
-        auto kernel = w4a16_gemm_xlds_kernel<W3, 8>;
+    // Eight slices in flight per wave where the slices of a row come in eights (K % 2048 == 0, which holds where walks turn), else
+    // four.  The kernel whose walks may turn is the faster one for four bits anyway (T = 1, N = 16384, K = 2048 9.3 -> 8.9 us,
+    // K = 6144 15.9 -> 15.8), for three it is not (T = 1, N = 32000, K = 14336 41.8 / 43.8, K = 32768 94 / 100).
+    auto launch = [&](auto kernel) {
         if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return SQ_ERR_LAUNCH;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kXldsWaves * kWave), lds, st, X, ldx, T, K, Qw, sw, N, Y, ldy);
-    } else {
-        auto kernel = w4a16_gemm_xlds_kernel<W3, 4>;
-        if (!allow_large_lds(reinterpret_cast<const void *>(kernel))) return SQ_ERR_LAUNCH;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kXldsWaves * kWave), lds, st, X, ldx, T, K, Qw, sw, N, Y, ldy);
-    }
-    return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+        return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+    };
+    if ((K / 256) % 8 != 0) return launch(w4a16_gemm_xlds_kernel<W3, 4, false>);
+    if constexpr (W3)
+        if (!w4a16_xlds_turns(K)) return launch(w4a16_gemm_xlds_kernel<W3, 8, false>);
+    return launch(w4a16_gemm_xlds_kernel<W3, 8, true>);
 }
 
 // does the kernel above take the shape?  Enough blocks of 16 channels that every CU gets several waves

@@ -210,7 +210,9 @@ def run_w3a16(X, Q3, sw, ldy=None):
 
 
 @pytest.mark.parametrize("T,K,N", [(1, 256, 1), (8, 1024, 24700), (32, 768, 10300), (20, 256, 50), (16, 8192, 300),
-                                   (17, 2048, 33), (1, 4096, 4096), (40, 512, 100), (100, 256, 31), (8, 11008, 70)])
+                                   (17, 2048, 33), (1, 4096, 4096), (40, 512, 100), (100, 256, 31), (8, 11008, 70),
+                                   # several rounds of four and of eight slices a row; walks that begin in different ones
+                                   (3, 3072, 16390), (16, 2048, 16384), (8, 8192, 16400), (2, 24576, 16390)])
 def test_w3a16_gemm_random_operands(oracle, T, K, N):
     print(f"case w3a16 gemm random T={T} K={K} N={N}", flush=True)
     g = np.random.default_rng(T + 3 * K + 5 * N)

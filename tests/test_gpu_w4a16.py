@@ -133,10 +133,10 @@ def test_w4a16_gemm_random_operands(oracle, T, K, N):
 
 
 @pytest.mark.parametrize("T,K,N", [(3, 1024, 16400), (16, 2048, 16384), (2, 3072, 16390), (9, 4096, 20000), (8, 8192, 16400),
-                                   (1, 6144, 33000)])
+                                   (1, 6144, 33000), (4, 16384, 16390), (2, 24576, 16400)])
 def test_w4a16_gemm_walks_that_begin_anywhere(oracle, T, K, N):
-    """Few tokens and many channels: neighbouring workgroups begin their walk over K in different rounds of four or eight
-    slices (one round, several, several blocks of channels a wave).  One-hot rows in every round and small integers: sums
+    """Few tokens and many channels, rounds of four or eight slices (one round, several, several blocks of channels a wave):
+    where K is a multiple of 8192 neighbouring workgroups begin their walk over K in different ones.  One-hot rows in every round and small integers: sums
     without rounding, equal bits."""
     print(f"case w4a16 gemm turned walks T={T} K={K} N={N}", flush=True)
     g = np.random.default_rng(T + K + N)
