@@ -204,7 +204,10 @@ sq_status sq_w4a4_gemm_decode(const uint8_t *Qx, const float *sx, int64_t T, int
  *     Xrot   device out, fp16 [T, ldo], 16-byte aligned, ldo >= K, ldo % 8 == 0
  *
  * sq_w4a16_gemm    Y[t, n] = fp16( sw[n] * sum_k X[t, k] * Qw[n, k] ), products
- *   exact, sums in fp32 on the matrix cores.
+ *   exact, sums in fp32 on the matrix cores.  The order of the additions goes with
+ *   the sizes, and at most 16 tokens of K = 8192, 16384 or 24576 channels with the
+ *   output channel's number too (N >= 16384): the same weight row at another n, or in
+ *   a shard of N, may differ in the last bit there.
  *     X        device, fp16 [T, ldx] (what sq_rotate_fp16 wrote); rows 16-byte
  *              aligned (ldx % 8 == 0), ldx >= K
  *     Qw, sw   device, uint8 [N, K/2] (16-byte aligned) and float [N]
@@ -264,8 +267,8 @@ sq_status sq_w3a16_gemm(const void *X, int64_t T, int32_t K, int64_t ldx,
  * where the layer is one pass over the weights and the rotation of a few tokens
  * is pure latency in front of it).  Same operation, same results bit for bit
  * as the two calls: the first workgroups rotate and quantize one token group
- * each into `workspace`, every workgroup then multiplies its block of output
- * channels once all groups are done.
+ * each into `workspace`; these (where they own channels at all) and the others
+ * multiply a block of output channels each once all groups are done.
  *
  *   X, T, K, ldx, giv_*, P, prepared, n1, n2   as sq_rotate_quantize_prepared;
  *              (n1, n2) one of 16x32, 32x32, 32x64, 64x64, 64x128, else
@@ -293,7 +296,8 @@ sq_status sq_w3a16_gemm(const void *X, int64_t T, int32_t K, int64_t ldx,
  * has to be invalidated).  Use it where the host's launch path is the bound
  * (a handful of tokens on small layers), otherwise use the two calls.
  * Needs at least as many blocks of 32 (N < 16384) or 64 output channels as there
- * are token groups (N >= 32 T is always enough), else SQ_ERR_SHAPE.
+ * are token groups (N >= 32 T is always enough), else SQ_ERR_SHAPE, whether the
+ * rotating workgroups of the shape own channels or not.
  */
 int64_t sq_decode_layer_workspace_bytes(int64_t T, int32_t K);
 sq_status sq_decode_layer(const void *X, int64_t T, int32_t K, int64_t ldx,

@@ -12,8 +12,9 @@
 //   * the last block clears the counters for the next launch once every block is past its wait.
 // The waits are bounded: a block that has polled for about a second skips its channels and raises
 // the error word instead.  That bound is also what stands behind the one assumption made here,
-// that the blocks with the lowest indices are not dispatched after the others (every block of a
-// decode-sized launch is resident at once anyway: two per CU, 512 on the chip).
+// that the blocks with the lowest indices, which rotate and wait for nobody, are not dispatched after the
+// others.  The others need not all be resident at once (two per CU, 512 on the chip; 32 groups beside
+// 512 blocks of channels are more): one that begins late finds the count complete.
 // Device-wide atomics and cache maintenance are expensive on this part (eight L2s): a ticket per
 // block instead of the block index cost 7 us and an exit count with acquire-release ordering 16 us
 // of a 34 us layer, and even a single acquire load per block behind the last poll (one cache
@@ -269,8 +270,10 @@ sq_status launch_decode_layer(const __half *X, int64_t ldx, int T, const RotqPla
     // be reached)
     const int option = debug_option(SQ_DEBUG_DECODE_SPIN_LIMIT);
     const int spin_limit = option > 0 ? option : kSpinLimit;
-    // rotating blocks without channels (see the kernel); with one of them beside many others it is better to keep them
-    // (T = 1, K = 4096: N = 10240 13.5 us with channels, 13.1 without; N = 14336 14.7 / 15.8, N = 16000 15.7 / 16.1)
+    // Rotating blocks without channels (see the kernel).  One of them beside many others keeps its channels: T = 1, K = 4096, us with
+    // channels / without, N = 9000 13.2 / 12.3, N = 11264 13.8 / 13.3, N = 12288 14.0 / 14.0, N = 14336 14.6 / 15.3, N = 16000 15.8 / 15.8.
+    // At K = 8192 the same line costs up to 3 %: N = 9000 18.1 / 17.9, N = 12288 20.4 / 20.5, N = 14336 22.6 / 21.9, N = 16000 24.7 / 24.1.
+    // With several of them, T = 2, K = 8192: N = 10240 19.2 / 18.7, N = 14336 22.7 / 22.4, N = 16000 25.0 / 24.6.
     const int apart = FN == 1 && N1 * N2 >= 4096 && (groups > 1 || tiles <= 352);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(apart ? groups + tiles : tiles)), dim3(256), lds, st, X, ldx, T, plan, F1, F2, Qx, sx, ctr, Qw, sw,
                        N, Y, ldy, lds_main, spin_limit, sides, apart);

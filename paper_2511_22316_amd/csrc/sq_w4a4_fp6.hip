@@ -27,7 +27,10 @@
 // T = 1001, K = 3072, N = 9216, 192 or 144 tiles: 29.3 -> 26.2).
 // The conversion is done in registers, by every wave for itself: one that is shared through LDS (24 bytes per 32 codes
 // written once and read by all) moves 1.5 times the bytes out of LDS, writes them at a quarter of the read rate, and was
-// 10 - 15 % slower.  T = 8192, K = 8192, N = 28672: int8 instruction 1359 us, here 980.
+// 10 - 15 % slower.  T = 8192, K = 8192, N = 28672: int8 instruction 1359 us, here 980 - 1005.
+//   The times above are of launches one behind the other on the same operands.  With operands and outputs out of a ring beyond the
+// caches the same calls take up to 8 % longer (T = 2048, N = 4096: K = 4096 25.9 / 26.9 us, K = 11008 54.3 / 55.1; T = 333,
+// K = 5120, N = 13824 23.5 / 25.4; T = 1001, K = 3072, N = 9216 26.6 / 29.0), and with other kernels between them T = 2048, K = N = 4096 takes 28.4.
 #include "sq_fp6_store.h"
 #include "sq_gemm_tile.h"
 #include "sq_w4a4_fp6.h"

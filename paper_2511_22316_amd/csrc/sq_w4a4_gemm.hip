@@ -801,11 +801,10 @@ extern "C" sq_status sq_w4a4_gemm(const uint8_t *Qx, const float *sx, int64_t T,
     hipStream_t st = static_cast<hipStream_t>(stream);
     __half *Yh = static_cast<__half *>(Y);
     if ((K % 128) != 0) return sq::launch_generic(Qx, sx, (int)T, K, Qw, sw, N, Yh, ldy, acc_dbg, st);
-    // Kernel choice, from few tokens to many.  The two large tile shapes run eight waves per CU
-    // (two per SIMD): the VALU work of widening nibbles issues nearly twice as fast from two waves
-    // as from one.  256x256 tiles (64x128 per wave: fewer VALU ops per MFMA) or 128x256 tiles,
-    // whichever needs less time for its rounds over the CUs.  The debug option SQ_DEBUG_GEMM_LAUNCH_SHAPE (case number
-    // below plus one) overrides the choice.
+    // Kernel choice, from few tokens to many.  The large int8 tiles run eight multiplying waves per CU (two per SIMD: the VALU work of
+    // widening nibbles issues nearly twice as fast from two waves as from one) or four with four that load; the 6-bit
+    // float tiles four waves, one per SIMD, whose registers hold a larger tile each.  The debug option SQ_DEBUG_GEMM_LAUNCH_SHAPE
+    // (case number below plus one) overrides the choice; cases 0, 1, 2, 3 and 6 are forms that only it reaches.
     const int forced = sq::debug_option(SQ_DEBUG_GEMM_LAUNCH_SHAPE) - 1;
     const int Ti = (int)T;
     int choice = forced;
