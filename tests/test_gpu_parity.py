@@ -530,6 +530,35 @@ def test_gemm_seeded_random_shapes_bit_exact(oracle):
         assert half_ulp_distance(Yg, Yo).max() <= 1
 
 
+@pytest.mark.parametrize("T,K,N", [
+    # either side of the rules for two K groups with an odd number of K tiles: 64 x 64 tiles, then 64 x 128
+    (65, 1280, 300), (65, 1792, 300), (65, 768, 8300), (65, 2304, 8300), (65, 2816, 8300), (48, 2304, 24600), (48, 2816, 24600),
+    # just beyond one round of 64 x 128 tiles; a single round of 128 x 128 against 128 x 192 tiles
+    (130, 1280, 11400), (217, 1024, 11457)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_gemm_either_side_of_the_rules(oracle, T, K, N, offset):
+    """What the dispatcher picks where its rules for few tiles meet, with rows of Y that begin at 16 bytes and at any element (which
+    has a cost of its own in the choice): the oracle's accumulators, and the same Y without asking for them."""
+    print(f"case gemm rules T={T} K={K} N={N} offset={offset}", flush=True)
+    import torch
+    import paper_2511_22316_amd as sq
+    g = np.random.default_rng(T + K + N)
+    Qx, Qw = synth.random_codes(T, K, 81), synth.random_codes(N, K, 82)
+    sx, sw = g.uniform(0.05, 4.0, T).astype(np.float32), g.uniform(1e-4, 5e-3, N).astype(np.float32)
+    Yo, acco = oracle.gemm(Qx, sx, Qw, sw)
+    ldy = (N + 7) // 8 * 8
+    buffers = [torch.full((T * ldy + 8,), -77.0, dtype=torch.float16, device="cuda") for _ in range(2)]
+    Y = [b[offset:offset + T * ldy].view(T, ldy) for b in buffers]
+    acc = torch.empty((T, N), dtype=torch.int32, device="cuda")
+    sq.sq_w4a4_gemm(dev(Qx), dev(sx), dev(Qw), dev(sw), Y[0][:, :N], acc)
+    sq.sq_w4a4_gemm(dev(Qx), dev(sx), dev(Qw), dev(sw), Y[1][:, :N])
+    torch.cuda.synchronize()
+    assert np.array_equal(host(acc), acco)
+    assert half_ulp_distance(host(Y[0])[:, :N], Yo).max() <= 1
+    assert torch.equal(buffers[0].view(torch.int16), buffers[1].view(torch.int16))
+    assert torch.all(Y[0][:, N:] == -77.0) and torch.all(buffers[0][:offset] == -77.0) and torch.all(buffers[0][offset + T * ldy:] == -77.0)
+
+
 def test_gemm_strided_output_and_empty(oracle):
     print("case gemm strided output / empty", flush=True)
     import torch
