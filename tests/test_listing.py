@@ -63,6 +63,13 @@ def too_close(lines):
     return found, readers
 
 
+def loads_behind_m0(lines):
+    """Global -> LDS loads directly behind the scalar instruction that sets M0, which they read one wait state later at the earliest."""
+    seen = [text for text, _ in instructions(lines)]
+    loads = [k for k, text in enumerate(seen) if "_load_lds_" in text]
+    return [(seen[k - 1], seen[k]) for k in loads if re.match(r"s_\w+ m0,", seen[k - 1])], len(loads)
+
+
 def test_scan_sees_a_write_that_is_too_close():
     asm = [";;#ASMSTART", "v_fma_mixhi_f16 v7, v66, v25, 0", ";;#ASMEND"]
     swap = ["v_permlane32_swap_b32_e32 v5, v7"]
@@ -71,10 +78,16 @@ def test_scan_sees_a_write_that_is_too_close():
     assert not too_close(asm + ["s_nop 1"] + swap)[0]
     assert not too_close(asm + ["s_nop 0", "v_mov_b32_e32 v1, v2"] + swap)[0]
     assert too_close(asm + ["v_mfma_f32_32x32x16_f16 a[0:15], v[4:7], v[8:11], a[0:15]"])[0]
+    load = "global_load_lds_dwordx4 v1, s[2:3]"
+    assert loads_behind_m0(["s_add_u32 m0, m0, 0x1000", ";;#ASMEND", ";;#ASMSTART", load])[0]
+    assert not loads_behind_m0(["s_mov_b32 m0, s1", "s_nop 0", load])[0]
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 def test_six_bit_float_kernel_keeps_its_distances(tmp_path):
-    found, readers = too_close(listing("sq_w4a4_fp6.hip", tmp_path))
+    lines = listing("sq_w4a4_fp6.hip", tmp_path)
+    found, readers = too_close(lines)
     assert readers > 1000, "the kernels are in the listing"
     assert not found, found[:4]
+    found, loads = loads_behind_m0(lines)
+    assert loads > 100 and not found, found[:4]
